@@ -647,11 +647,11 @@ static int set_coeffs_impl(amgg_ctx* c, int lvl, int degree, const double* coeff
     Level& L = c->lv[lvl];
     hipError_t e = hipSetDevice(c->device);
     if (e == hipSuccess && L.nblk > 0)  // the same coefficients on every block, each with its own scale
-        e = assemble_smoother_blocks(L.n, L.ptr, L.col, L.val, L.diag, L.nblk, L.blk_off, L.blk_scale, L.blk_crow, pc,
+        e = assemble_smoother_blocks(L.n, L.nnz, L.ptr, L.col, L.val, L.diag, L.nblk, L.blk_off, L.blk_scale, L.blk_crow, pc,
                                      coeffs ? nullptr : dev, 0, L.q64, L.q32, L.qd64, L.qd32,
                                      static_cast<hipStream_t>(stream));
     else if (e == hipSuccess)
-        e = assemble_smoother(L.n, L.ptr, L.col, L.val, L.diag, L.scale, pc, coeffs ? nullptr : dev, L.q64, L.q32,
+        e = assemble_smoother(L.n, L.nnz, L.ptr, L.col, L.val, L.diag, L.scale, pc, coeffs ? nullptr : dev, L.q64, L.q32,
                               L.qd64, L.qd32, static_cast<hipStream_t>(stream));
     if (e == hipSuccess && L.hrows > 0)
         e = gather_values(L.nhent, L.hent, L.q64, L.q32, L.hq64, L.hq32, static_cast<hipStream_t>(stream));
@@ -713,7 +713,7 @@ static int set_coeffs_blocks_impl(amgg_ctx* c, int lvl, int degree, const float*
         const hipStream_t st = static_cast<hipStream_t>(stream);
         hipError_t e = hipSetDevice(c->device);
         if (e == hipSuccess)
-            e = assemble_smoother_blocks(L.n, L.ptr, L.col, L.val, L.diag, L.nblk, L.blk_off, L.blk_scale, L.blk_crow,
+            e = assemble_smoother_blocks(L.n, L.nnz, L.ptr, L.col, L.val, L.diag, L.nblk, L.blk_off, L.blk_scale, L.blk_crow,
                                          pc, coeffs_dev, stride, L.q64, L.q32, L.qd64, L.qd32, st);
         if (e == hipSuccess && L.hrows > 0) e = gather_values(L.nhent, L.hent, L.q64, L.q32, L.hq64, L.hq32, st);
         if (e != hipSuccess) return hip_fail(e, "amgg_set_smoother_coeffs_blocks");

@@ -297,14 +297,14 @@ struct PolyCoeffs {
     int diag_only = 0;  // the diagonal form of Eq. 5: f_o taken as 0 whatever the coefficients say
 };
 // Eq. (5) smoother values on A's pattern; also the diagonal of Q^{-1} in both precisions.
-hipError_t assemble_smoother(int32_t n, const int32_t* ptr, const int32_t* col, const double* val,
+hipError_t assemble_smoother(int32_t n, int32_t nnz, const int32_t* ptr, const int32_t* col, const double* val,
                              const double* diag, const double* scale, const PolyCoeffs& pc,
                              const float* coeffs_dev, double* q64, float* q32, double* qd64, float* qd32,
                              hipStream_t stream);
 // The same values on a block-diagonal level: block b (rows off[b]..off[b+1]) uses scale[b]
 // and the coefficients coeffs_dev + crow[b] * stride (or pc when coeffs_dev is null);
 // crow[b] < 0 gives Q = 0 on that block.
-hipError_t assemble_smoother_blocks(int32_t n, const int32_t* ptr, const int32_t* col, const double* val,
+hipError_t assemble_smoother_blocks(int32_t n, int32_t nnz, const int32_t* ptr, const int32_t* col, const double* val,
                                     const double* diag, int32_t nblk, const int32_t* off, const double* scale,
                                     const int32_t* crow, const PolyCoeffs& pc, const float* coeffs_dev,
                                     int32_t stride, double* q64, float* q32, double* qd64, float* qd32,

@@ -19,6 +19,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "amggnn.h"
@@ -252,71 +253,87 @@ __device__ __forceinline__ double wave4_sum(double v, double (*sh)[HD]) {
 // ------------------------------------------------------------------------------------------
 // batch construction
 // ------------------------------------------------------------------------------------------
-// A workgroup owns 256 consecutive rows of the level graph. Each thread writes its row's
-// pointer and degree feature and marks the row's entries in an LDS map; the entries are then
-// copied with unit stride (columns shifted to the graph's first batch row, weights a_ij, 1 for
-// the self-loop of A_hat, whose entry also writes the a_ii feature). The map holds 64 entries per
-// row on average (the coarse levels of the 3D hierarchies have 25-60); a block whose entries do
-// not fit it is copied row by row.
-constexpr int kFillCap = 16384;
+// One launch builds the batched graph of every level: a workgroup owns one 64-row tile (four threads
+// per row) and looks its graph's arrays up. It writes the rows' pointers and degree features (pad rows
+// of a graph's last tile carry no entries), marks the rows' entries in an LDS map and copies the
+// entries with unit stride (columns shifted to the graph's first batch row, weights a_ij, 1 for the
+// self-loop of A_hat, whose entry also writes the a_ii feature). A copy: bound by memory on large
+// levels, by the latency of its few dependent loads on small ones, which is why the levels share one
+// launch (one launch per level of 256-row workgroups took 157 us on the hierarchy of 998k tetrahedral
+// cells, 83 of them on levels below 25k rows, and 28 us more for the pad rows; this one takes 85). A
+// tile whose entries do not fit the map (more than 64 per row on average) is copied row by row.
+struct FillGraph {
+    const int32_t* rp;
+    const int32_t* cl;
+    const double* va;
+    int32_t n, row0, e0;  // rows; first batch row and first batch entry
+};
+constexpr int kFillCap = 4096;
+constexpr int kFillChunk = 4;  // entries per thread whose loads are issued together
 
-__global__ __launch_bounds__(256) void fill_graph_kernel(int32_t n, const int32_t* __restrict__ rp,
-                                                        const int32_t* __restrict__ cl,
-                                                        const double* __restrict__ va, int32_t row0, int32_t e0,
-                                                        int32_t* __restrict__ ptr, int32_t* __restrict__ col,
-                                                        float* __restrict__ w, float* __restrict__ x0) {
+__global__ __launch_bounds__(256) void fill_graph_kernel(int ntiles, const int32_t* __restrict__ tile_graph,
+                                                        const FillGraph* __restrict__ fg, int32_t* __restrict__ ptr,
+                                                        int32_t* __restrict__ col, float* __restrict__ w,
+                                                        float* __restrict__ x0) {
     __shared__ uint8_t rowof[kFillCap];
     const int t = static_cast<int>(threadIdx.x);
-    const int32_t r0 = static_cast<int32_t>(blockIdx.x) * 256;
-    const int32_t r1 = min(r0 + 256, n);
-    const int32_t b0 = rp[r0];
-    const int32_t ne = rp[r1] - b0;
+    const FillGraph g = fg[tile_graph[blockIdx.x]];
+    const int32_t r0 = static_cast<int32_t>(blockIdx.x) * TILE - g.row0;  // rows of the level matrix
+    const int32_t r1 = min(r0 + TILE, g.n);
+    const int32_t b0 = g.rp[r0];
+    const int32_t ne = g.rp[r1] - b0;
     const bool fits = ne <= kFillCap;
-    const int32_t i = r0 + t;
+    const int lr = t / 4, q = t % 4;
+    const int32_t i = r0 + lr;
     int32_t b = 0, e = 0;
     if (i < r1) {
-        b = rp[i];
-        e = rp[i + 1];
-        ptr[row0 + i] = e0 + b;
-        x0[2 * (row0 + i)] = 0.0f;  // a_ii; the diagonal entry writes it below
-        x0[2 * (row0 + i) + 1] = static_cast<float>(e - b - 1);
+        b = g.rp[i];
+        e = g.rp[i + 1];
         if (fits)
-            for (int32_t k = b - b0; k < e - b0; ++k) rowof[k] = static_cast<uint8_t>(t);
+            for (int32_t k = b - b0 + q; k < e - b0; k += 4) rowof[k] = static_cast<uint8_t>(lr);
+    } else {
+        b = e = g.rp[g.n];  // a pad row
+    }
+    if (q == 0) {
+        ptr[g.row0 + i] = g.e0 + b;
+        x0[2 * (g.row0 + i)] = 0.0f;  // a_ii; the diagonal entry writes it below
+        x0[2 * (g.row0 + i) + 1] = i < r1 ? static_cast<float>(e - b - 1) : 0.0f;
+        if (static_cast<int>(blockIdx.x) == ntiles - 1 && lr == TILE - 1) ptr[g.row0 + i + 1] = g.e0 + e;
     }
     __syncthreads();
     if (!fits) {
-        if (i < r1)
-            for (int32_t p = b; p < e; ++p) {
-                const int32_t j = cl[p];
-                col[e0 + p] = row0 + j;
-                w[e0 + p] = j == i ? 1.0f : static_cast<float>(va[p]);
-                if (j == i) x0[2 * (row0 + i)] = static_cast<float>(va[p]);
-            }
+        for (int32_t p = b + q; p < e; p += 4) {
+            const int32_t j = g.cl[p];
+            col[g.e0 + p] = g.row0 + j;
+            w[g.e0 + p] = j == i ? 1.0f : static_cast<float>(g.va[p]);
+            if (j == i) x0[2 * (g.row0 + i)] = static_cast<float>(g.va[p]);
+        }
         return;
     }
-    for (int32_t k = t; k < ne; k += 256) {
-        const int32_t p = b0 + k;
-        const int32_t j = cl[p];
-        const int32_t row = r0 + rowof[k];
-        col[e0 + p] = row0 + j;
-        if (j == row) {
-            w[e0 + p] = 1.0f;  // self-loop of A_hat
-            x0[2 * (row0 + row)] = static_cast<float>(va[p]);
-        } else {
-            w[e0 + p] = static_cast<float>(va[p]);
+    for (int32_t base = 0; base < ne; base += kFillChunk * 256) {
+        int32_t j[kFillChunk];
+        double a[kFillChunk];
+#pragma unroll
+        for (int u = 0; u < kFillChunk; ++u) {
+            const int32_t p = b0 + min(base + t + u * 256, ne - 1);
+            j[u] = g.cl[p];
+            a[u] = g.va[p];
+        }
+#pragma unroll
+        for (int u = 0; u < kFillChunk; ++u) {
+            const int32_t k = base + t + u * 256;
+            if (k < ne) {
+                const int32_t row = r0 + rowof[k];
+                col[g.e0 + b0 + k] = g.row0 + j[u];
+                if (j[u] == row) {
+                    w[g.e0 + b0 + k] = 1.0f;  // self-loop of A_hat
+                    x0[2 * (g.row0 + row)] = static_cast<float>(a[u]);
+                } else {
+                    w[g.e0 + b0 + k] = static_cast<float>(a[u]);
+                }
+            }
         }
     }
-}
-
-__global__ void set_int_kernel(int32_t* __restrict__ p, int32_t v) { p[0] = v; }
-
-__global__ void pad_rows_kernel(int32_t from, int32_t to, int32_t eptr, int32_t* __restrict__ ptr,
-                                float* __restrict__ x0) {
-    const int32_t i = from + blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= to) return;
-    ptr[i] = eptr;
-    x0[2 * i] = 0.0f;
-    x0[2 * i + 1] = 0.0f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1368,8 +1385,11 @@ struct gcin_batch {
     std::vector<int32_t> cbound, gchunk;  // chunk tile bounds [nchunks + 1], graph chunk bounds [G + 1]
     int nchunks = 0;
     // device
-    int32_t *d_gend = nullptr, *d_gtile = nullptr, *d_tile_graph = nullptr;
+    // tables, one contiguous part of the workspace that is uploaded at once
+    int32_t *d_gend = nullptr, *d_tile_graph = nullptr;
     int32_t *d_cbound = nullptr, *d_gchunk = nullptr;
+    FillGraph* d_fill = nullptr;
+    size_t table_bytes = 0;
     double* cbuf = nullptr;  // chunk partial sums (up to 4 HD doubles per chunk)
     float* cmax = nullptr;
     int32_t* carg = nullptr;
@@ -1418,11 +1438,12 @@ size_t layout_batch(gcin_batch* b, uintptr_t base) {
     Carve cv{base};
     const size_t G = b->G, N = b->N, E = b->E, T = b->ntiles, HD = b->hd;
     b->d_gend = cv.take<int32_t>(G);
-    b->d_gtile = cv.take<int32_t>(G + 1);
     b->d_tile_graph = cv.take<int32_t>(T);
     b->d_gcnt = cv.take<float>(G);
     b->d_cbound = cv.take<int32_t>(static_cast<size_t>(b->nchunks) + 1);
     b->d_gchunk = cv.take<int32_t>(G + 1);
+    b->d_fill = cv.take<FillGraph>(G);
+    b->table_bytes = cv.off;
     b->cbuf = cv.take<double>(static_cast<size_t>(b->nchunks) * 4 * HD);
     b->cmax = cv.take<float>(static_cast<size_t>(b->nchunks) * HD);
     b->carg = cv.take<int32_t>(static_cast<size_t>(b->nchunks) * HD);
@@ -1575,41 +1596,33 @@ extern "C" int gcin_batch_create_ex(int hidden, int flags, int ngraphs, const gc
         }
         layout_batch(b, reinterpret_cast<uintptr_t>(workspace));
         hipStream_t st = static_cast<hipStream_t>(stream);
-        // tables
-        std::vector<int32_t> tile_graph(b->ntiles);
-        std::vector<float> cnt(ngraphs);
+        // tables, laid out on the host as in the workspace and uploaded in one copy
+        std::vector<unsigned char> tab(b->table_bytes);
+        auto host = [&](auto* dev) {
+            return reinterpret_cast<std::remove_reference_t<decltype(dev)>>(
+                tab.data() + (reinterpret_cast<uintptr_t>(dev) - reinterpret_cast<uintptr_t>(workspace)));
+        };
+        int32_t *gend = host(b->d_gend), *tile_graph = host(b->d_tile_graph);
+        float* cnt = host(b->d_gcnt);
+        FillGraph* fill = host(b->d_fill);
+        int64_t e0 = 0;
         for (int g = 0; g < ngraphs; ++g) {
+            gend[g] = b->gend[g];
             for (int t = b->gtile[g]; t < b->gtile[g + 1]; ++t) tile_graph[t] = g;
             cnt[g] = static_cast<float>(b->gn[g]);
-        }
-        hipError_t e = hipMemcpyAsync(b->d_gend, b->gend.data(), sizeof(int32_t) * ngraphs, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->d_gtile, b->gtile.data(), sizeof(int32_t) * (ngraphs + 1), hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->d_tile_graph, tile_graph.data(), sizeof(int32_t) * b->ntiles, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess) e = hipMemcpyAsync(b->d_gcnt, cnt.data(), sizeof(float) * ngraphs, hipMemcpyHostToDevice, st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->d_cbound, b->cbound.data(), sizeof(int32_t) * b->cbound.size(), hipMemcpyHostToDevice,
-                               st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(b->d_gchunk, b->gchunk.data(), sizeof(int32_t) * b->gchunk.size(), hipMemcpyHostToDevice,
-                               st);
-        int64_t e0 = 0;
-        for (int g = 0; g < ngraphs && e == hipSuccess; ++g) {
-            fill_graph_kernel<<<grid_of(n[g], 256), 256, 0, st>>>(n[g], graphs[g].rowptr, graphs[g].col, graphs[g].val,
-                                                                 b->goff[g], static_cast<int32_t>(e0), b->ptr, b->col,
-                                                                 b->w, b->x0);
-            const int32_t from = b->gend[g], to = b->goff[g + 1];
+            fill[g] = FillGraph{graphs[g].rowptr, graphs[g].col, graphs[g].val, n[g], b->goff[g],
+                                static_cast<int32_t>(e0)};
             e0 += z[g];
-            if (to > from)
-                pad_rows_kernel<<<grid_of(to - from, 256), 256, 0, st>>>(from, to, static_cast<int32_t>(e0), b->ptr, b->x0);
-            e = hipGetLastError();
         }
+        std::memcpy(host(b->d_cbound), b->cbound.data(), sizeof(int32_t) * b->cbound.size());
+        std::memcpy(host(b->d_gchunk), b->gchunk.data(), sizeof(int32_t) * b->gchunk.size());
+        hipError_t e = hipMemcpyAsync(workspace, tab.data(), tab.size(), hipMemcpyHostToDevice, st);
         if (e == hipSuccess) {
-            set_int_kernel<<<1, 1, 0, st>>>(b->ptr + b->N, static_cast<int32_t>(b->E));
+            fill_graph_kernel<<<b->ntiles, 256, 0, st>>>(b->ntiles, b->d_tile_graph, b->d_fill, b->ptr, b->col, b->w,
+                                                         b->x0);
             e = hipGetLastError();
         }
-        // the host tables above must stay alive until the copies complete
+        // the host tables must stay alive until the copy completes, the graphs' arrays until they are read
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) {
             delete b;

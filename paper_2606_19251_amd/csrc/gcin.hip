@@ -516,21 +516,22 @@ __device__ __forceinline__ void stage_bf16_split_t(const float* __restrict__ M, 
 
 // Y0: the layer below is layer 0, whose output is formed from H0 (y0_of) instead of read from Yp.
 // bf16 hi / lo parts of the 64 x 64 weights of layers 1 .. NL-1, transposed ([col][k]) for
-// tile_gemm's global-memory operand: block l - 1 forms layer l into wbf + (l - 1) 2 HD^2 (hi) and
-// the HD^2 entries after it (lo).
+// tile_gemm's global-memory operand: blocks (l - 1, *) form layer l into wbf + (l - 1) 2 HD^2 (hi) and
+// the HD^2 entries after it (lo). One element per thread: with one workgroup per layer its 16 rounds
+// of dependent loads took 13 us, spread over 16 workgroups 3.
 template <int HD>
 __global__ __launch_bounds__(256) void weights_bf16_kernel(const float* __restrict__ P, Offs o,
                                                          unsigned short* __restrict__ wbf) {
     const int l = blockIdx.x + 1;
     const float* W = P + o.convW[l];
     unsigned short* hi = wbf + static_cast<int64_t>(blockIdx.x) * 2 * HD * HD;
-    for (int e = threadIdx.x; e < HD * HD; e += blockDim.x) {
-        const int k = e / HD, c = e % HD;
-        unsigned short h, lo;
-        split_bf16(W[e], h, lo);
-        hi[c * HD + k] = h;
-        hi[HD * HD + c * HD + k] = lo;
-    }
+    const int e = static_cast<int>(blockIdx.y) * 256 + threadIdx.x;
+    if (e >= HD * HD) return;
+    const int k = e / HD, c = e % HD;
+    unsigned short h, lo;
+    split_bf16(W[e], h, lo);
+    hi[c * HD + k] = h;
+    hi[HD * HD + c * HD + k] = lo;
 }
 
 template <int HD, bool MFMA, bool X3, bool Y0>
@@ -677,69 +678,152 @@ __global__ __launch_bounds__(4 * HD) void layer_kernel(const int32_t* __restrict
 // (at most kChunkTiles consecutive tiles of one graph, chunks counted from the graph's first
 // tile), stage 2 the chunks of each graph. In both, wave w of the workgroup sums items w, w+4,
 // w+8, ... in order and the four wave sums are added in wave order: deterministic, and a
-// graph's result does not depend on the other graphs of the batch.
+// graph's result does not depend on the other graphs of the batch. A full chunk is 64 dependent
+// additions per wave whose loads decide the time, so kAhead items' loads are issued together, and
+// what can be summed apart (y, y^2, the readout; blockIdx.y) gets its own workgroup: one workgroup
+// reads only some 50 GB/s. The statistics of a layer and the readout of the layer below it share their
+// launches, and where every graph is one chunk, stage 1 finishes it and there is no stage 2. On the
+// 998k-cell hierarchy the forward's reductions went from 16 launches and 180 us to 10 and 92, on the
+// 32-mesh training batch from 16 and 130 to 5 and 50; the backward's per-chunk sums from 13 to 7 us.
 constexpr int kChunkTiles = 256;
+constexpr int kAhead = 16;
 
-// out[k][j][c] = sum over items i in [bounds[k], bounds[k+1]) of in[i][j][c], j < K, c < HD
-template <int HD, int K>
-__global__ __launch_bounds__(4 * HD) void chunk_sum_kernel(const double* __restrict__ in, const int32_t* __restrict__ bounds,
-                                                       double* __restrict__ out) {
-    __shared__ double sh[4][K][HD];
-    const int k = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    double s[K];
+// Sum of in[i][c] over the items i = i0 + wv, i0 + wv + 4, ... < i1 in order, rows `stride` apart, the
+// four waves' sums added in wave order; the same value in every wave.
+template <int HD>
+__device__ __forceinline__ double sum_items(const double* __restrict__ in, int64_t stride, int32_t i0, int32_t i1,
+                                            int wv, int c, double (*sh)[HD]) {
+    double s = 0.0;
+    for (int32_t i = i0 + wv; i < i1; i += 4 * kAhead) {
+        double v[kAhead];  // a slot past the end re-reads the last item and is not used
 #pragma unroll
-    for (int j = 0; j < K; ++j) s[j] = 0.0;
-    // items wv, wv + 4, ... in order; four items' loads are issued ahead of their additions
-    const int32_t i1 = bounds[k + 1];
-    int32_t i = bounds[k] + wv;
-    for (; i + 12 < i1; i += 16) {
-        double v[4][K];
+        for (int u = 0; u < kAhead; ++u) v[u] = in[min(i + 4 * u, i1 - 1) * stride + c];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int j = 0; j < K; ++j) v[u][j] = in[(static_cast<int64_t>(i + 4 * u) * K + j) * HD + c];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int j = 0; j < K; ++j) s[j] += v[u][j];
+        for (int u = 0; u < kAhead; ++u)
+            if (i + 4 * u < i1) s += v[u];
     }
-    for (; i < i1; i += 4)
-#pragma unroll
-        for (int j = 0; j < K; ++j) s[j] += in[(static_cast<int64_t>(i) * K + j) * HD + c];
-#pragma unroll
-    for (int j = 0; j < K; ++j) sh[wv][j][c] = s[j];
+    sh[wv][c] = s;
     __syncthreads();
-    if (wv == 0)
-#pragma unroll
-        for (int j = 0; j < K; ++j)
-            out[(static_cast<int64_t>(k) * K + j) * HD + c] = ((sh[0][j][c] + sh[1][j][c]) + sh[2][j][c]) + sh[3][j][c];
+    return ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
 }
 
-// Per graph and channel: mean and 1/sqrt(biased variance + eps) from the chunk sums.
-template <int HD>
-__global__ __launch_bounds__(4 * HD) void stats_final_kernel(const double* __restrict__ cstat,
-                                                         const int32_t* __restrict__ gchunk,
-                                                         const float* __restrict__ gcnt, float* __restrict__ mu,
-                                                         float* __restrict__ rstd) {
-    __shared__ double sh[4][2][HD];
-    const int g = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    double s1 = 0.0, s2 = 0.0;
-    for (int32_t k = gchunk[g] + wv; k < gchunk[g + 1]; k += 4) {
-        s1 += cstat[static_cast<int64_t>(k) * 2 * HD + c];
-        s2 += cstat[static_cast<int64_t>(k) * 2 * HD + HD + c];
-    }
-    sh[wv][0][c] = s1;
-    sh[wv][1][c] = s2;
-    __syncthreads();
-    if (wv != 0) return;
-    s1 = ((sh[0][0][c] + sh[1][0][c]) + sh[2][0][c]) + sh[3][0][c];
-    s2 = ((sh[0][1][c] + sh[1][1][c]) + sh[2][1][c]) + sh[3][1][c];
-    const double n = gcnt[g];
+// Mean and 1/sqrt(biased variance + eps) of a graph's channel from its sums of y and y^2.
+__device__ __forceinline__ void norm_of(double s1, double s2, double n, float* mu, float* rstd) {
     const double m = s1 / n;
     double var = s2 / n - m * m;
     if (var < 0.0) var = 0.0;
-    mu[g * HD + c] = static_cast<float>(m);
-    rstd[g * HD + c] = static_cast<float>(1.0 / sqrt(var + static_cast<double>(kEps)));
+    *mu = static_cast<float>(m);
+    *rstd = static_cast<float>(1.0 / sqrt(var + static_cast<double>(kEps)));
+}
+
+// Max with its arg-max, ties to the lowest node index (any combination order gives the same).
+__device__ __forceinline__ void max_merge(float& mx, int32_t& am, float m2, int32_t a2) {
+    if (m2 > mx || (m2 == mx && a2 < am)) {
+        mx = m2;
+        am = a2;
+    }
+}
+
+// Sum, max and arg-max over the items as sum_items takes them, the waves combined; valid in wave 0.
+template <int HD>
+__device__ __forceinline__ void pool_items(const double* __restrict__ isum, const float* __restrict__ imax,
+                                           const int32_t* __restrict__ iarg, int32_t i0, int32_t i1, int wv, int c,
+                                           double& s, float& mx, int32_t& am) {
+    __shared__ double ss[4][HD];
+    __shared__ float sm[4][HD];
+    __shared__ int32_t sa[4][HD];
+    s = 0.0;
+    mx = -INFINITY;
+    am = INT32_MAX;
+    for (int32_t i = i0 + wv; i < i1; i += 4 * kAhead) {
+        double vs[kAhead];
+        float vm[kAhead];
+        int32_t va[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int64_t e = static_cast<int64_t>(min(i + 4 * u, i1 - 1)) * HD + c;
+            vs[u] = isum[e];
+            vm[u] = imax[e];
+            va[u] = iarg[e];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (i + 4 * u < i1) {
+                s += vs[u];
+                max_merge(mx, am, vm[u], va[u]);
+            }
+    }
+    ss[wv][c] = s;
+    sm[wv][c] = mx;
+    sa[wv][c] = am;
+    __syncthreads();
+    if (wv != 0) return;
+    for (int w = 1; w < 4; ++w) max_merge(mx, am, sm[w][c], sa[w][c]);
+    s = ((ss[0][c] + ss[1][c]) + ss[2][c]) + ss[3][c];
+}
+
+// What a reduction of the forward takes and writes: the statistics of layer `layer` (stats) and the
+// readout of layer `layer` - 1 or of the last layer (pool).
+struct Reduce {
+    const double* tstat;  // per tile (stage 1) or chunk (stage 2)
+    const double* psum;
+    const float* pmax;
+    const int32_t* parg;
+    double* cstat;        // stage 1: per chunk
+    double* csum;
+    float* cmax;
+    int32_t* carg;
+    const float* gcnt;    // the stage that finishes: per graph
+    float *mu, *rstd, *pooled;
+    int32_t* argmax;
+    int pool_layer;
+};
+
+// FINAL: blockIdx.x is a graph and the items are its own (its tiles where it is one chunk, else its
+// chunks); otherwise a chunk and its tiles. blockIdx.y + first selects the part: 0 = statistics (the
+// first stage takes y and y^2 apart, 0 and 1), then the readout.
+template <int HD, bool FINAL>
+__global__ __launch_bounds__(4 * HD) void reduce_kernel(const int32_t* __restrict__ bounds, Reduce r, int first) {
+    __shared__ double sh[2][4][HD];
+    constexpr int NSTAT = FINAL ? 1 : 2;
+    const int k = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const int part = blockIdx.y + first;
+    const int32_t i0 = bounds[k], i1 = bounds[k + 1];
+    if (part < NSTAT) {
+        if constexpr (FINAL) {
+            const double s1 = sum_items<HD>(r.tstat, 2 * HD, i0, i1, wv, c, sh[0]);
+            const double s2 = sum_items<HD>(r.tstat + HD, 2 * HD, i0, i1, wv, c, sh[1]);
+            if (wv == 0) norm_of(s1, s2, r.gcnt[k], r.mu + k * HD + c, r.rstd + k * HD + c);
+        } else {
+            const double s = sum_items<HD>(r.tstat + part * HD, 2 * HD, i0, i1, wv, c, sh[0]);
+            if (wv == 0) r.cstat[(static_cast<int64_t>(k) * 2 + part) * HD + c] = s;
+        }
+    } else {
+        double s;
+        float mx;
+        int32_t am;
+        pool_items<HD>(r.psum, r.pmax, r.parg, i0, i1, wv, c, s, mx, am);
+        if (wv != 0) return;
+        if constexpr (FINAL) {
+            r.pooled[(k * NL + r.pool_layer) * 2 * HD + c] = static_cast<float>(s / r.gcnt[k]);
+            r.pooled[(k * NL + r.pool_layer) * 2 * HD + HD + c] = mx;
+            r.argmax[(k * NL + r.pool_layer) * HD + c] = am;
+        } else {
+            r.csum[static_cast<int64_t>(k) * HD + c] = s;
+            r.cmax[static_cast<int64_t>(k) * HD + c] = mx;
+            r.carg[static_cast<int64_t>(k) * HD + c] = am;
+        }
+    }
+}
+
+// out[k][j][c] = sum over items i in [bounds[k], bounds[k+1]) of in[i][j][c], j = blockIdx.y < K, c < HD
+template <int HD, int K>
+__global__ __launch_bounds__(4 * HD) void chunk_sum_kernel(const double* __restrict__ in, const int32_t* __restrict__ bounds,
+                                                       double* __restrict__ out) {
+    __shared__ double sh[4][HD];
+    const int k = blockIdx.x, j = blockIdx.y, wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const double s = sum_items<HD>(in + j * HD, K * HD, bounds[k], bounds[k + 1], wv, c, sh);
+    if (wv == 0) out[(static_cast<int64_t>(k) * K + j) * HD + c] = s;
 }
 
 // y of rows r0 .. r0 + 15 in channel c (0 past the graph's end): read from Y, or formed from H0
@@ -762,12 +846,10 @@ __device__ __forceinline__ void load_rows(float (&yv)[16], int32_t r0, int32_t e
     }
 }
 
-// Per tile: sum, max and first arg-max of x = ReLU(IN(y)) per channel.
-template <int HD, bool Y0>
+// Per tile: sum, max and first arg-max of x = ReLU(IN(y)) per channel (the last layer's readout).
+template <int HD>
 __global__ __launch_bounds__(4 * HD) void pool_tile_kernel(const int32_t* __restrict__ tile_graph,
                                                        const int32_t* __restrict__ gend, const float* __restrict__ Y,
-                                                       const float* __restrict__ H0, const float* __restrict__ W0,
-                                                       const float* __restrict__ b0,
                                                        const float* __restrict__ mu, const float* __restrict__ rstd,
                                                        const float* __restrict__ gam, const float* __restrict__ bet,
                                                        double* __restrict__ tsum, float* __restrict__ tmax,
@@ -783,7 +865,7 @@ __global__ __launch_bounds__(4 * HD) void pool_tile_kernel(const int32_t* __rest
     float mx = -INFINITY;
     int32_t am = INT32_MAX;
     float yv[16];  // the 16 rows' loads are issued together
-    load_rows<HD, Y0>(yv, tile * TILE + wv * 16, end, c, Y, H0, W0, b0);
+    load_rows<HD, false>(yv, tile * TILE + wv * 16, end, c, Y, nullptr, nullptr, nullptr);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int32_t row = tile * TILE + wv * 16 + r;
@@ -811,91 +893,6 @@ __global__ __launch_bounds__(4 * HD) void pool_tile_kernel(const int32_t* __rest
     }
 }
 
-// Max with its arg-max, ties to the lowest node index (any combination order gives the same).
-__device__ __forceinline__ void max_merge(float& mx, int32_t& am, float m2, int32_t a2) {
-    if (m2 > mx || (m2 == mx && a2 < am)) {
-        mx = m2;
-        am = a2;
-    }
-}
-
-// Stage 1 of the pooling reduction (see chunk_sum_kernel): per chunk, sum, max and arg-max.
-template <int HD>
-__global__ __launch_bounds__(4 * HD) void pool_chunk_kernel(const double* __restrict__ tsum, const float* __restrict__ tmax,
-                                                        const int32_t* __restrict__ targ,
-                                                        const int32_t* __restrict__ bounds, double* __restrict__ csum,
-                                                        float* __restrict__ cmax, int32_t* __restrict__ carg) {
-    __shared__ double ss[4][HD];
-    __shared__ float sm[4][HD];
-    __shared__ int32_t sa[4][HD];
-    const int k = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    double s = 0.0;
-    float mx = -INFINITY;
-    int32_t am = INT32_MAX;
-    // tiles wv, wv + 4, ... in order; four tiles' loads are issued ahead of their use
-    const int32_t t1 = bounds[k + 1];
-    int32_t t = bounds[k] + wv;
-    for (; t + 12 < t1; t += 16) {
-        double vs[4];
-        float vm[4];
-        int32_t va[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t e = static_cast<int64_t>(t + 4 * u) * HD + c;
-            vs[u] = tsum[e];
-            vm[u] = tmax[e];
-            va[u] = targ[e];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            s += vs[u];
-            max_merge(mx, am, vm[u], va[u]);
-        }
-    }
-    for (; t < t1; t += 4) {
-        s += tsum[static_cast<int64_t>(t) * HD + c];
-        max_merge(mx, am, tmax[static_cast<int64_t>(t) * HD + c], targ[static_cast<int64_t>(t) * HD + c]);
-    }
-    ss[wv][c] = s;
-    sm[wv][c] = mx;
-    sa[wv][c] = am;
-    __syncthreads();
-    if (wv != 0) return;
-    for (int w = 1; w < 4; ++w) max_merge(mx, am, sm[w][c], sa[w][c]);
-    csum[static_cast<int64_t>(k) * HD + c] = ((ss[0][c] + ss[1][c]) + ss[2][c]) + ss[3][c];
-    cmax[static_cast<int64_t>(k) * HD + c] = mx;
-    carg[static_cast<int64_t>(k) * HD + c] = am;
-}
-
-template <int HD>
-__global__ __launch_bounds__(4 * HD) void pool_final_kernel(const double* __restrict__ csum, const float* __restrict__ cmax,
-                                                        const int32_t* __restrict__ carg,
-                                                        const int32_t* __restrict__ gchunk,
-                                                        const float* __restrict__ gcnt, int layer,
-                                                        float* __restrict__ pooled, int32_t* __restrict__ argmax) {
-    __shared__ double ss[4][HD];
-    __shared__ float sm[4][HD];
-    __shared__ int32_t sa[4][HD];
-    const int g = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    double s = 0.0;
-    float mx = -INFINITY;
-    int32_t am = INT32_MAX;
-    for (int32_t k = gchunk[g] + wv; k < gchunk[g + 1]; k += 4) {
-        s += csum[static_cast<int64_t>(k) * HD + c];
-        max_merge(mx, am, cmax[static_cast<int64_t>(k) * HD + c], carg[static_cast<int64_t>(k) * HD + c]);
-    }
-    ss[wv][c] = s;
-    sm[wv][c] = mx;
-    sa[wv][c] = am;
-    __syncthreads();
-    if (wv != 0) return;
-    for (int w = 1; w < 4; ++w) max_merge(mx, am, sm[w][c], sa[w][c]);
-    s = ((ss[0][c] + ss[1][c]) + ss[2][c]) + ss[3][c];
-    pooled[(g * NL + layer) * 2 * HD + c] = static_cast<float>(s / gcnt[g]);
-    pooled[(g * NL + layer) * 2 * HD + HD + c] = mx;
-    argmax[(g * NL + layer) * HD + c] = am;
-}
-
 __device__ __forceinline__ float block128_sum(float v, float* red) {
     // 128 threads
     red[threadIdx.x] = v;
@@ -918,6 +915,7 @@ struct HeadSave {
 };
 
 // Readout, LayerNorm, sigmoid and predictive MLP of one graph per workgroup (128 threads).
+// Each output is one sequential sum over weights in memory: 32 of its loads are issued together.
 template <int HD>
 __global__ __launch_bounds__(128) void head_fwd_kernel(const float* __restrict__ P, Offs o,
                                                        const float* __restrict__ pooled, HeadSave hs,
@@ -929,6 +927,7 @@ __global__ __launch_bounds__(128) void head_fwd_kernel(const float* __restrict__
     {
         const int l = t / RO, oo = t % RO;
         float acc = P[o.rob[l] + oo];
+#pragma unroll 32
         for (int k = 0; k < 2 * HD; ++k) acc += p[l * 2 * HD + k] * P[o.roW[l] + k * RO + oo];
         z[t] = acc;
     }
@@ -942,18 +941,21 @@ __global__ __launch_bounds__(128) void head_fwd_kernel(const float* __restrict__
     __syncthreads();
     {
         float acc = P[o.m0b + t];
+#pragma unroll 32
         for (int k = 0; k < JK; ++k) acc += s[k] * P[o.m0W + k * M1 + t];
         a1[t] = fmaxf(acc, 0.0f);
     }
     __syncthreads();
     if (t < M2) {
         float acc = P[o.m1b + t];
+#pragma unroll 32
         for (int k = 0; k < M1; ++k) acc += a1[k] * P[o.m1W + k * M2 + t];
         a2[t] = fmaxf(acc, 0.0f);
     }
     __syncthreads();
     if (t < o.nout) {
         float acc = P[o.m2b + t];
+#pragma unroll 32
         for (int k = 0; k < M2; ++k) acc += a2[k] * P[o.m2W + k * o.nout + t];
         out[g * o.nout + t] = acc;
     }
@@ -1659,29 +1661,33 @@ void forward_impl(gcin_batch* b, int degree, int precision, const float* P, floa
     const float *W0 = P + o.convW[0], *b0 = P + o.convb[0];
     layer0_kernel<HD><<<T, NT, 0, st>>>(b->ptr, b->col, b->w, b->x0, b->d_tile_graph, b->d_gend, W0, b0, b->H0,
                                         b->tstat);
-    const int C = b->nchunks;
     // Statistics of layer l, then its readout, which feeds no later layer: pooling each layer as
     // soon as its statistics exist leaves every result as it is and lets an inference-only batch
     // reuse the buffer of layer l - 1 for layer l + 1. The readout partials of layer l are formed
     // by the kernel of layer l + 1 (from the rows' own entries of A_hat), the last layer's by a
-    // pooling pass; the per-graph reductions follow.
-    auto stats = [&](int l) {
-        chunk_sum_kernel<HD, 2><<<C, NT, 0, st>>>(b->tstat, b->d_cbound, b->cbuf);
-        stats_final_kernel<HD><<<G, NT, 0, st>>>(b->cbuf, b->d_gchunk, b->d_gcnt, b->mu[l], b->rstd[l]);
+    // pooling pass; the per-graph reductions of a layer's statistics and of the readout below it
+    // share their launches (reduce_kernel).
+    const int C = b->nchunks;
+    const bool one = C == G;  // every graph is one chunk
+    auto reduce = [&](int stat_layer, int pool_layer) {  // -1: none
+        Reduce r{b->tstat, b->tpsum, b->tpmax, b->tparg, b->cbuf, b->cbuf + static_cast<int64_t>(C) * 2 * HD, b->cmax,
+                 b->carg, b->d_gcnt, stat_layer < 0 ? nullptr : b->mu[stat_layer],
+                 stat_layer < 0 ? nullptr : b->rstd[stat_layer], b->pooled, b->argmax, pool_layer};
+        const int stat = stat_layer >= 0, pool = pool_layer >= 0;
+        if (one) {
+            reduce_kernel<HD, true><<<dim3(G, stat + pool), NT, 0, st>>>(b->d_cbound, r, 1 - stat);
+            return;
+        }
+        reduce_kernel<HD, false><<<dim3(C, 2 * stat + pool), NT, 0, st>>>(b->d_cbound, r, 2 - 2 * stat);
+        r.tstat = r.cstat;
+        r.psum = r.csum;
+        r.pmax = r.cmax;
+        r.parg = r.carg;
+        reduce_kernel<HD, true><<<dim3(G, stat + pool), NT, 0, st>>>(b->d_gchunk, r, 1 - stat);
     };
-    auto pool_tiles = [&](int l) {
-        (l == 0 ? pool_tile_kernel<HD, true> : pool_tile_kernel<HD, false>)<<<T, NT, 0, st>>>(
-            b->d_tile_graph, b->d_gend, b->Y[l], b->H0, W0, b0, b->mu[l], b->rstd[l], P + o.gam[l], P + o.bet[l],
-            b->tpsum, b->tpmax, b->tparg);
-    };
-    auto pool_graphs = [&](int l) {
-        pool_chunk_kernel<HD><<<C, NT, 0, st>>>(b->tpsum, b->tpmax, b->tparg, b->d_cbound, b->cbuf, b->cmax, b->carg);
-        pool_final_kernel<HD><<<G, NT, 0, st>>>(b->cbuf, b->cmax, b->carg, b->d_gchunk, b->d_gcnt, l, b->pooled,
-                                                b->argmax);
-    };
-    stats(0);
+    reduce(0, -1);
     const bool mfma = HD == 64 && precision != GCIN_FP32;
-    if (mfma) weights_bf16_kernel<HD><<<NL - 1, 256, 0, st>>>(P, o, b->wbf);
+    if (mfma) weights_bf16_kernel<HD><<<dim3(NL - 1, HD * HD / 256), 256, 0, st>>>(P, o, b->wbf);
     for (int l = 1; l < NL; ++l) {
         const bool y0 = l == 1;
         auto kern = y0 ? layer_kernel<HD, false, false, true> : layer_kernel<HD, false, false, false>;
@@ -1695,11 +1701,11 @@ void forward_impl(gcin_batch* b, int degree, int precision, const float* P, floa
                                b->mu[l - 1], b->rstd[l - 1], P + o.gam[l - 1], P + o.bet[l - 1], P + o.convW[l],
                                P + o.convb[l], b->wbf + static_cast<int64_t>(l - 1) * 2 * HD * HD, b->H[l], b->Y[l],
                                b->tstat, b->tpsum, b->tpmax, b->tparg);
-        pool_graphs(l - 1);
-        stats(l);
+        reduce(l, l - 1);
     }
-    pool_tiles(NL - 1);
-    pool_graphs(NL - 1);
+    pool_tile_kernel<HD><<<T, NT, 0, st>>>(b->d_tile_graph, b->d_gend, b->Y[NL - 1], b->mu[NL - 1], b->rstd[NL - 1],
+                                           P + o.gam[NL - 1], P + o.bet[NL - 1], b->tpsum, b->tpmax, b->tparg);
+    reduce(-1, NL - 1);
     head_fwd_kernel<HD><<<G, 128, 0, st>>>(P, o, b->pooled, b->hs, coeffs_out);
 }
 
@@ -1720,7 +1726,7 @@ void backward_impl(gcin_batch* b, int degree, int precision, const float* P, con
         (l == 0 ? bwd_a_kernel<HD, true> : bwd_a_kernel<HD, false>)<<<T, NT, 0, st>>>(
             b->ptr, b->col, b->w, b->d_tile_graph, b->d_gend, b->d_gcnt, b->Y[l], b->H0, W0, b0, b->mu[l], b->rstd[l],
             P + o.gam[l], P + o.bet[l], b->dpooled, b->argmax, l, dHn, b->dxh, b->tb);
-        chunk_sum_kernel<HD, 4><<<b->nchunks, NT, 0, st>>>(b->tb, b->d_cbound, b->cbuf);
+        chunk_sum_kernel<HD, 4><<<dim3(b->nchunks, 4), NT, 0, st>>>(b->tb, b->d_cbound, b->cbuf);
         bwd_final_kernel<HD><<<G, NT, 0, st>>>(b->cbuf, b->d_gchunk, b->d_gcnt, b->gmean, b->ggb);
         // gamma / beta of this layer
         reduce_parts<double>(b->ggb, G, 2 * HD, HD, grads + o.gam[l], st);

@@ -20,6 +20,7 @@
 #include <mutex>
 #include <string>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "amggnn.h"
@@ -43,6 +44,7 @@ constexpr float kEps = 1e-5f;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------------------------------
 // parameter offsets (order documented in gcin.h)
@@ -179,64 +181,176 @@ __device__ __forceinline__ void visit_rows(const int32_t* __restrict__ ptr, cons
     for (; r < r1; ++r) done(r);
 }
 
-// The same walk with 16-byte gathers: the HD / 4 = G lanes of group q (of the 4 HD lanes that own
-// rows [r0, r0 + 16)) own the rows [r0 + 4 q, r0 + 4 q + 4) and lane p of the group holds channels
-// 4 p .. 4 p + 3, so that one load instruction brings 64 / G neighbour rows (the load units
-// process a wavefront's addresses a few lanes per cycle, which bounds a gather of one 4-byte
-// channel per lane). Each row's entries are still visited in stored order, so every channel's sum
-// is the one visit_rows forms. A group takes its entries kBatchX4 at a time, their indices and
-// weights held by its first lanes; use(w, v, s) gets the four channels as a float4 and s = the
-// row when the entry is the row's own (column = row), else -1; done(row) is called once per row
-// of the group.
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>): an unrolled loop whose index is a
+// constant expression (the DPP controls below have to be).
+template <int... I, class F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+    static_for_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+// Orders a wavefront's LDS accesses where its lanes exchange values among themselves only.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Reductions over the four groups of G lanes of 4 G lanes (16 rows of HD = 4 G channels), four values per
+// lane: every exchange adds (or merges) two values' halves at once, so that three exchanges leave each
+// lane with one value's total, the value reduced_channel() of its group.
+template <int G>
+__device__ __forceinline__ int reduced_channel() {
+    const int q = static_cast<int>(threadIdx.x % (4 * G)) / G;
+    return (q & 1) * 2 + q / 2;
+}
+// Exchanges b's lower half of every 2 S lanes with a's upper half.
+template <int S>
+__device__ __forceinline__ void swap_halves(unsigned int& a, unsigned int& b) {
+    if constexpr (S == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else if constexpr (S == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        const bool up = (threadIdx.x & S) != 0;
+        const unsigned int got = __shfl_xor(up ? a : b, S, 64);
+        if (up)
+            a = got;
+        else
+            b = got;
+    }
+}
+template <int S>
+__device__ __forceinline__ double add_halves(double a, double b) {
+    uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+    swap_halves<S>(x.x, y.x);
+    swap_halves<S>(x.y, y.y);
+    return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+}
+template <int G>
+__device__ __forceinline__ double reduce_groups(const double (&v)[4]) {
+    return add_halves<G>(add_halves<2 * G>(v[0], v[1]), add_halves<2 * G>(v[2], v[3]));
+}
+
+// Max with its arg-max, ties to the lowest node index (any combination order gives the same).
+__device__ __forceinline__ void max_merge(float& mx, int32_t& am, float m2, int32_t a2) {
+    if (m2 > mx || (m2 == mx && a2 < am)) {
+        mx = m2;
+        am = a2;
+    }
+}
+template <int S>
+__device__ __forceinline__ void max_halves(float& m, int32_t& a, float m2, int32_t a2) {
+    unsigned int x = __float_as_uint(m), y = __float_as_uint(m2), i = static_cast<unsigned int>(a),
+                 j = static_cast<unsigned int>(a2);
+    swap_halves<S>(x, y);
+    swap_halves<S>(i, j);
+    m = __uint_as_float(x);
+    a = static_cast<int32_t>(i);
+    max_merge(m, a, __uint_as_float(y), static_cast<int32_t>(j));
+}
+// The result is left in mx[0], am[0].
+template <int G>
+__device__ __forceinline__ void reduce_groups_max(float (&mx)[4], int32_t (&am)[4]) {
+    max_halves<2 * G>(mx[0], am[0], mx[1], am[1]);
+    max_halves<2 * G>(mx[2], am[2], mx[3], am[3]);
+    max_halves<G>(mx[0], am[0], mx[2], am[2]);
+}
+
+// Lane Q's value of each group of G lanes (16 or 8), by DPP row broadcasts (a DPP row is 16 lanes, a bank
+// 4): a vector instruction or two where a shuffle goes through the LDS unit.
+template <int Q, int G>
+__device__ __forceinline__ int group_bcast(int v) {
+    constexpr int kRowNewBcast = 0x150;
+    if constexpr (G == 16) {
+        return __builtin_amdgcn_update_dpp(0, v, kRowNewBcast + Q, 0xf, 0xf, true);
+    } else {
+        const int lo = __builtin_amdgcn_update_dpp(0, v, kRowNewBcast + Q, 0xf, 0x3, true);
+        return __builtin_amdgcn_update_dpp(lo, v, kRowNewBcast + 8 + Q, 0xf, 0xc, false);
+    }
+}
+template <int Q, int G>
+__device__ __forceinline__ float group_bcast(float v) {
+    return __builtin_bit_cast(float, group_bcast<Q, G>(__builtin_bit_cast(int, v)));
+}
+
+// The same walk with 16-byte gathers: group q of G = HD / 4 lanes (of the HD lanes that own rows
+// [r0, r0 + 16)) owns the rows [r0 + 4 q, r0 + 4 q + 4) and lane p of the group holds channels
+// 4 p .. 4 p + 3, so that one load instruction brings 64 / G neighbour rows. Each row's entries are
+// visited in stored order, so every channel's sum is the one visit_rows forms. A group's lanes hold
+// its next G entries (column, weight, row); eight gathers are in flight at a time, and the next
+// entries load meanwhile. What is bound here is instructions and latency, not bytes, so the steps are
+// straight-line code: entries are broadcast by DPP, a slot past the group's end has weight 0 and ends
+// no row, and whether any group ends a row at a step is a scalar test of a mask formed once per G
+// entries. rp is the lane's row pointer, ptr[g0 + min(p, 4)] of the group's first row g0; init() is called
+// once the first entries are on their way. use(w, v) gets what load(column) returned; with PAIR, load brings
+// two floats per node, which each lane then loads for the entry it holds (one load instruction per G
+// entries instead of one per entry: the address units take a wavefront's lanes four a cycle, whatever
+// they load). done(i) is called after the last entry of the
+// group's row i = 0..3 and never for a row without entries (the caller presets those).
 constexpr int kBatchX4 = 8;
 
-template <int G, class Load, class Use, class Done>
-__device__ __forceinline__ void visit_rows_x4(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
-                                              const float* __restrict__ w, int32_t r0, Load load, Use use,
-                                              Done done) {
+template <int G, bool PAIR, class Init, class Load, class Use, class Done>
+__device__ __forceinline__ void visit_rows_x4(int rp, const int32_t* __restrict__ col, const float* __restrict__ w,
+                                              Init init, Load load, Use use, Done done) {
     static_assert(G == 16 || G == 8, "groups of 16 (64 channels) or 8 (32 channels) lanes");
-    constexpr int B = kBatchX4;
     const int p = static_cast<int>(threadIdx.x % G);
-    const int32_t g0 = r0 + 4 * static_cast<int32_t>((threadIdx.x % (4 * G)) / G);  // the group's first row
-    const int32_t rp = ptr[g0 + min(p, 4)];
-    auto bound = [&](int32_t i) { return __shfl(rp, i, G); };  // ptr[g0 + i], i <= 4
-    const int32_t kbeg = bound(0), kend = bound(4);
-    int32_t r = g0;
-    int32_t rnext = bound(1);
-    const int32_t l = p % B;
-    int32_t cl = 0;
-    float wl = 0.0f;
-    if (kbeg < kend) {
-        const int32_t kk = min(kbeg + l, kend - 1);
-        cl = col[kk];
-        wl = w[kk];
-    }
-    for (int32_t k = kbeg; k < kend; k += B) {
-        float4 vj[B];
-#pragma unroll
-        for (int q = 0; q < B; ++q) vj[q] = load(__shfl(cl, q, G));
-        const float wcur = wl;
-        const int32_t ccur = cl;
-        if (k + B < kend) {
-            const int32_t kk = min(k + B + l, kend - 1);
-            cl = col[kk];
-            wl = w[kk];
+    const int32_t b0 = group_bcast<0, G>(rp), b1 = group_bcast<1, G>(rp), b2 = group_bcast<2, G>(rp),
+                  b3 = group_bcast<3, G>(rp), b4 = group_bcast<4, G>(rp);
+    const int32_t last = max(b4 - 1, 0);
+    int32_t longest = 0;  // entries of the wavefront's longest group
+    static_for<64 / G>([&](auto q) { longest = max(longest, __builtin_amdgcn_readlane(b4 - b0, q * G)); });
+    int32_t e = b0 + p;
+    int cl = col[min(e, last)];
+    float wl = w[min(e, last)];
+    init();
+    for (int32_t base = 0; base < longest; base += G, e += G) {
+        const int ccur = cl;
+        const float wcur = e < b4 ? wl : 0.0f;
+        const int ri = (e >= b1) + (e >= b2) + (e >= b3);
+        const int32_t rend = ri == 0 ? b1 : ri == 1 ? b2 : ri == 2 ? b3 : b4;
+        const int info = e + 1 == rend ? 4 + ri : 0;
+        const uint64_t ends = __builtin_amdgcn_ballot_w64(info != 0);
+        if (base + G < longest) {
+            cl = col[min(e + G, last)];
+            wl = w[min(e + G, last)];
         }
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            const float wq = __shfl(wcur, q, G);
-            const int32_t jq = __shfl(ccur, q, G);
-            if (k + q < kend) {
-                while (k + q >= rnext) {
-                    done(r);
-                    ++r;
-                    rnext = bound(r + 1 - g0);
+        constexpr uint64_t kFirst = G == 16 ? 0x0001000100010001ull : 0x0101010101010101ull;
+        float2 own = make_float2(0.0f, 0.0f);
+        if constexpr (PAIR) own = load(ccur);
+        static_for<G / kBatchX4>([&](auto half) {
+            constexpr int H = half * kBatchX4;
+            if (H > 0 && base + H >= longest) return;
+            decltype(load(0)) vj[kBatchX4];
+            if constexpr (!PAIR) static_for<kBatchX4>([&](auto q) { vj[q] = load(group_bcast<H + q, G>(ccur)); });
+            static_for<kBatchX4>([&](auto q) {
+                if (q > 0 && base + H + q >= longest) return;
+                if constexpr (PAIR)
+                    use(group_bcast<H + q, G>(wcur),
+                        make_float2(group_bcast<H + q, G>(own.x), group_bcast<H + q, G>(own.y)));
+                else
+                    use(group_bcast<H + q, G>(wcur), vj[q]);
+                if (ends & (kFirst << (H + q))) {
+                    const int f = group_bcast<H + q, G>(info);
+                    if (f != 0) done(f - 4);
                 }
-                use(wq, vj[q], jq == r ? r : -1);
-            }
-        }
+            });
+        });
     }
-    for (; r < g0 + 4; ++r) done(r);
+}
+
+// Bounds of a group's rows for the callers of visit_rows_x4 that preset rows without entries.
+template <class Empty>
+__device__ __forceinline__ void for_empty_rows(const int32_t* __restrict__ ptr, int32_t g0, Empty empty) {
+    for (int i = 0; i < 4; ++i)
+        if (ptr[g0 + i] == ptr[g0 + i + 1]) empty(i);
 }
 
 // Sum over the 4 wavefronts of a workgroup, per channel (lane), into out[c] (thread wave 0).
@@ -347,6 +461,11 @@ __device__ __forceinline__ float y0_of(float2 h, float w0, float w1, float bb) {
     return __builtin_fmaf(h.y, w1, __builtin_fmaf(h.x, w0, bb));
 }
 
+__device__ __forceinline__ float4 y0_of4(float2 h, const float4& w0, const float4& w1, const float4& bb) {
+    return make_float4(y0_of(h, w0.x, w1.x, bb.x), y0_of(h, w0.y, w1.y, bb.y), y0_of(h, w0.z, w1.z, bb.z),
+                       y0_of(h, w0.w, w1.w, bb.w));
+}
+
 // Layer 0 of a tile: H0 = A_hat x0 (two features per node; 4 HD / 64 lanes per row, each summing
 // every such entry of the row, combined in a fixed butterfly) and the per-tile sums of y and
 // y^2 for the InstanceNorm statistics.
@@ -421,20 +540,19 @@ __device__ __forceinline__ void split_bf16(float x, unsigned short& hi, unsigned
     lo = f2bf(x - __uint_as_float(static_cast<unsigned int>(hi) << 16));
 }
 
-// SPLITB: B is passed as b_hi + b_lo as well and the product a_hi b_lo is added (the
-// a_lo b_lo term is below FP32 resolution): an FP32-accurate product on the BF16 MFMA
-// units, used where the result feeds non-smooth operations (ReLU masks, arg-max pooling)
-// whose gradients must match an FP32/FP64 evaluation.
-// GB: the bf16 copies of B (and of its low parts) are read from global memory, row-major [col][k]
-// with row stride HD (Bg, Bglo; formed once per forward by weights_bf16_kernel), not from LDS:
-// the weights are shared by every tile and stay in cache, and a workgroup's LDS holds no copy of
-// them.
-template <int HD, bool MFMA, bool SPLIT = false, bool SPLITB = false, bool GB = false>
-__device__ __forceinline__ void tile_gemm(const float (*A)[HD + 1], const float* __restrict__ Bf,
-                                          const unsigned short (*Bt)[HD + 8], float (*D)[HD + 1],
-                                          const unsigned short (*Btlo)[HD + 8] = nullptr,
-                                          const unsigned short* __restrict__ Bg = nullptr,
-                                          const unsigned short* __restrict__ Bglo = nullptr) {
+// The same for two (finite) numbers by the packed conversion, which rounds to nearest even as f2bf
+// does, in a third of the instructions.
+__device__ __forceinline__ void split_bf16_pair(float x0, float x1, unsigned int& hi, unsigned int& lo) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    hi = __builtin_bit_cast(unsigned int, __builtin_convertvector((f32x2{x0, x1}), bf16x2));
+    const f32x2 r{x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xFFFF0000u)};
+    lo = __builtin_bit_cast(unsigned int, __builtin_convertvector(r, bf16x2));
+}
+
+template <int HD, bool MFMA, bool SPLIT = false, int LD = HD + 1>
+__device__ __forceinline__ void tile_gemm(const float (*A)[LD], const float* __restrict__ Bf,
+                                          const unsigned short (*Bt)[HD + 8], float (*D)[LD]) {
     static_assert(!MFMA || HD == 64, "the MFMA tiling is written for 64 channels");
     const int wv = threadIdx.x / HD, lane = threadIdx.x % HD;
     if constexpr (!MFMA) {
@@ -450,41 +568,78 @@ __device__ __forceinline__ void tile_gemm(const float (*A)[HD + 1], const float*
         f32x4 acc[4];
         for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int ks = 0; ks < HD; ks += 32) {
-            u16x8 av, alv;
-            for (int e = 0; e < 8; ++e) {
-                if constexpr (SPLIT) {
-                    unsigned short h, l;
-                    split_bf16(A[wv * 16 + i][ks + kq + e], h, l);
+            bf16x8 a, al;
+            if constexpr (SPLIT) {
+                u32x4 av, alv;
+                for (int e = 0; e < 4; ++e) {
+                    unsigned int h, l;
+                    split_bf16_pair(A[wv * 16 + i][ks + kq + 2 * e], A[wv * 16 + i][ks + kq + 2 * e + 1], h, l);
                     av[e] = h;
                     alv[e] = l;
-                } else {
-                    av[e] = f2bf(A[wv * 16 + i][ks + kq + e]);
                 }
+                a = __builtin_bit_cast(bf16x8, av);
+                al = __builtin_bit_cast(bf16x8, alv);
+            } else {
+                u16x8 av;
+                for (int e = 0; e < 8; ++e) av[e] = f2bf(A[wv * 16 + i][ks + kq + e]);
+                a = __builtin_bit_cast(bf16x8, av);
             }
-            const bf16x8 a = __builtin_bit_cast(bf16x8, av);
-            const bf16x8 al = __builtin_bit_cast(bf16x8, alv);
             for (int nb = 0; nb < 4; ++nb) {
                 u16x8 bv;
-                if constexpr (GB)
-                    bv = *reinterpret_cast<const u16x8*>(Bg + (nb * 16 + i) * HD + ks + kq);
-                else
-                    for (int e = 0; e < 8; ++e) bv[e] = Bt[nb * 16 + i][ks + kq + e];
+                for (int e = 0; e < 8; ++e) bv[e] = Bt[nb * 16 + i][ks + kq + e];
                 const bf16x8 b = __builtin_bit_cast(bf16x8, bv);
                 acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nb], 0, 0, 0);
                 if constexpr (SPLIT) acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[nb], 0, 0, 0);
-                if constexpr (SPLITB) {
-                    u16x8 blv;
-                    if constexpr (GB)
-                        blv = *reinterpret_cast<const u16x8*>(Bglo + (nb * 16 + i) * HD + ks + kq);
-                    else
-                        for (int e = 0; e < 8; ++e) blv[e] = Btlo[nb * 16 + i][ks + kq + e];
-                    const bf16x8 bl = __builtin_bit_cast(bf16x8, blv);
-                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[nb], 0, 0, 0);
-                }
             }
         }
         for (int nb = 0; nb < 4; ++nb)
             for (int e = 0; e < 4; ++e) D[wv * 16 + (lane / 16) * 4 + e][nb * 16 + i] = acc[nb][e];
+    }
+}
+
+// The wavefront's 16 rows of A (64 channels, LD apart) times B on MFMA, A split as above: acc[nb][e] is the
+// row 4 (lane / 16) + e and the column 4 (lane % 16) + nb, so that a lane's four blocks are neighbouring
+// columns. B's bf16 hi parts and its lo parts (added with SPLITB) are read from global memory,
+// [column][k] (formed once per forward by weights_bf16_kernel): every tile shares them, so they
+// stay in cache and take no LDS. SPLITB: a_hi b_lo is added as well (a_lo b_lo is below FP32
+// resolution): an FP32-accurate product on the BF16 MFMA units, used where the result feeds
+// non-smooth operations (ReLU masks, arg-max pooling) whose gradients must match an FP32/FP64
+// evaluation.
+template <int HD, bool SPLITB, int LD>
+__device__ __forceinline__ void tile_product(const float (*A)[LD], const unsigned short* __restrict__ Bg,
+                                             f32x4 (&acc)[4]) {
+    static_assert(HD == 64, "the MFMA tiling is written for 64 channels");
+    const int wv = threadIdx.x / HD, lane = threadIdx.x % HD;
+    const int i = lane % 16, kq = (lane / 16) * 8;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < HD; ks += 32) {
+        const float* ar = &A[wv * 16 + i][ks + kq];
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(ar), a1 = *reinterpret_cast<const f32x4*>(ar + 4);
+        u32x4 av, alv;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            unsigned int h, l;
+            split_bf16_pair(a0[2 * e], a0[2 * e + 1], h, l);
+            av[e] = h;
+            alv[e] = l;
+            split_bf16_pair(a1[2 * e], a1[2 * e + 1], h, l);
+            av[2 + e] = h;
+            alv[2 + e] = l;
+        }
+        const bf16x8 a = __builtin_bit_cast(bf16x8, av), al = __builtin_bit_cast(bf16x8, alv);
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb) {
+            const unsigned short* bp = Bg + (4 * i + nb) * HD + ks + kq;
+            const bf16x8 b = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(bp));
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nb], 0, 0, 0);
+            acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[nb], 0, 0, 0);
+            if constexpr (SPLITB) {
+                const bf16x8 bl = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(bp + HD * HD));
+                acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[nb], 0, 0, 0);
+            }
+        }
     }
 }
 
@@ -501,22 +656,28 @@ __device__ __forceinline__ void stage_bf16(const float* __restrict__ M, bool tra
     }
 }
 
-// hi/lo bf16 pair of M^T (Bt[c][k] = hi, Btlo[c][k] = lo of M[k][c]).
-template <int HD>
-__device__ __forceinline__ void stage_bf16_split_t(const float* __restrict__ M, unsigned short (*Bt)[HD + 8],
-                                                   unsigned short (*Btlo)[HD + 8]) {
-    for (int e = threadIdx.x; e < HD * HD; e += 4 * HD) {
-        const int k = e / HD, c = e % HD;
-        unsigned short h, l;
-        split_bf16(M[e], h, l);
-        Bt[c][k] = h;
-        Btlo[c][k] = l;
+// y of rows r0 .. r0 + 15 in channel c (0 past the graph's end): read from Y, or formed from H0
+// for layer 0; the 16 loads are issued together.
+template <int HD, bool Y0>
+__device__ __forceinline__ void load_rows(float (&yv)[16], int32_t r0, int32_t end, int c, const float* __restrict__ Y,
+                                          const float* __restrict__ H0, const float* __restrict__ W0,
+                                          const float* __restrict__ b0) {
+    if constexpr (Y0) {
+        const float w0 = W0[c], w1 = W0[HD + c], bb = b0[c];
+        float2 hv[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            hv[r] = r0 + r < end ? reinterpret_cast<const float2*>(H0)[r0 + r] : make_float2(0.0f, 0.0f);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? y0_of(hv[r], w0, w1, bb) : 0.0f;
+    } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? Y[static_cast<int64_t>(r0 + r) * HD + c] : 0.0f;
     }
 }
 
-// Y0: the layer below is layer 0, whose output is formed from H0 (y0_of) instead of read from Yp.
 // bf16 hi / lo parts of the 64 x 64 weights of layers 1 .. NL-1, transposed ([col][k]) for
-// tile_gemm's global-memory operand: blocks (l - 1, *) form layer l into wbf + (l - 1) 2 HD^2 (hi) and
+// tile_product: blocks (l - 1, *) form layer l into wbf + (l - 1) 2 HD^2 (hi) and
 // the HD^2 entries after it (lo). One element per thread: with one workgroup per layer its 16 rounds
 // of dependent loads took 13 us, spread over 16 workgroups 3.
 template <int HD>
@@ -534,8 +695,27 @@ __global__ __launch_bounds__(256) void weights_bf16_kernel(const float* __restri
     hi[HD * HD + c * HD + k] = lo;
 }
 
-template <int HD, bool MFMA, bool X3, bool Y0>
-__global__ __launch_bounds__(4 * HD) void layer_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+// Tile of a workgroup. Workgroups go to the 8 XCDs in turn, each with an L2 of its own: within every 256
+// tiles an XCD takes 32 neighbouring ones, whose rows gather mostly each other's neighbours (layers of
+// the 998k-cell hierarchy 476 -> 457 us). One contiguous range per XCD would give one of them the
+// coarse levels with their long rows.
+__device__ __forceinline__ int dealt_tile() {
+    constexpr int kRun = 32, kXcd = 8;
+    const int b = blockIdx.x, r = b % (kRun * kXcd), base = b - r;
+    if (base + kRun * kXcd > static_cast<int>(gridDim.x)) return b;  // the last, partial 256
+    return base + (r % kXcd) * kRun + r / kXcd;
+}
+
+// A layer above the first, one tile per workgroup. Layer 1, whose input is formed from 8 bytes per node,
+// is bound by the vector instructions of the walk (23 an entry, of which 16 normalise it; 95 % busy);
+// the others by the gathers' traffic from the L2s (256 bytes an entry at about 9 TB/s). On the
+// 998k-cell hierarchy (1.64M nodes, 14.5M entries) layer 1 went from 468 to 360 us and the others from
+// 500 to 462 against a form that passed the batch's entries through LDS shuffles, kept the rows' own
+// inputs in LDS and summed the tile one row at a time.
+// Y0: the layer below is layer 0, whose output is formed from H0 (y0_of) instead of read from Yp. Off: type
+// of the byte offsets into Yp (32 bits where they suffice).
+template <int HD, bool MFMA, bool X3, bool Y0, typename Off>
+__global__ __launch_bounds__(4 * HD, Y0 || X3 ? 5 : 4) void layer_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, const int32_t* __restrict__ tile_graph,
                                                    const int32_t* __restrict__ gend, const float* __restrict__ Yp,
                                                    const float* __restrict__ H0, const float* __restrict__ W0,
@@ -548,128 +728,156 @@ __global__ __launch_bounds__(4 * HD) void layer_kernel(const int32_t* __restrict
                                                    double* __restrict__ tstat, double* __restrict__ psum,
                                                    float* __restrict__ pmax, int32_t* __restrict__ parg) {
     // The kernel also forms the per-tile readout partials of the layer below (psum / pmax / parg
-    // as pool_tile_kernel writes them): every row's own entry of A_hat brings that row's
-    // normalised, rectified input x, which is kept in Xs and pooled in the output loop in
-    // pool_tile_kernel's order, so the layer below needs no pooling pass.
-    // The product overwrites the aggregates in place: every wavefront reads only its own 16
+    // as pool_tile_kernel writes them) from the tile's own rows of that layer, which the gathers have
+    // just brought into cache, so the layer below needs no pooling pass.
+    // The product overwrites the aggregates in place: every group of HD lanes reads only its own 16
     // rows of Hs and writes the same rows, each output after all of its row's reads (the
-    // stores depend on them), so one tile buffer serves both, and after the output loop it holds
-    // the per-tile reductions; with the weights' bf16 parts read from global memory (wbf: hi,
-    // then lo) the tile and the rows' own inputs Xs are all the LDS a workgroup holds (33 KB with
-    // 64 channels: 4 workgroups per CU, as many as the registers admit).
-    __shared__ __align__(16) float Hs[TILE][HD + 1];  // aggregates, products, then the reductions
-    float (*Ds)[HD + 1] = Hs;
-    __shared__ float Xs[TILE][HD + 1];
-    const int tile = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    // stores depend on them), so one tile buffer serves both and the wavefronts of a tile meet only
+    // at the end, when the buffer takes the per-tile reductions.
+    constexpr int LD = HD + 4;  // rows stay aligned to 16 bytes
+    __shared__ __align__(16) float Hs[TILE][LD];  // aggregates, products, then the reductions
+    constexpr int G = HD / 4;
+    const int tile = dealt_tile(), wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const int32_t r0 = tile * TILE + wv * 16;
+    const int32_t g0 = r0 + 4 * (c / G);  // the first row of the lane's group (see visit_rows_x4)
+    const int rp = ptr[g0 + min(static_cast<int>(threadIdx.x % G), 4)];  // first in the chain of loads
     const int g = tile_graph[tile];
     const int32_t end = gend[g];
-    const int32_t r0 = tile * TILE + wv * 16;
-    {
-        // channels 4 p .. 4 p + 3 of the lane's group (see visit_rows_x4)
-        constexpr int G = HD / 4;
-        const int c4 = 4 * static_cast<int>(threadIdx.x % G);
-        const float4 mu4 = *reinterpret_cast<const float4*>(mup + g * HD + c4);
-        const float4 rs4 = *reinterpret_cast<const float4*>(rsp + g * HD + c4);
-        const float4 ga4 = *reinterpret_cast<const float4*>(gam + c4);
-        const float4 be4 = *reinterpret_cast<const float4*>(bet + c4);
-        float4 w04 = make_float4(0.f, 0.f, 0.f, 0.f), w14 = w04, bb4 = w04;
-        if constexpr (Y0) {
-            w04 = *reinterpret_cast<const float4*>(W0 + c4);
-            w14 = *reinterpret_cast<const float4*>(W0 + HD + c4);
-            bb4 = *reinterpret_cast<const float4*>(b0 + c4);
-        }
-        float4 h4 = make_float4(0.f, 0.f, 0.f, 0.f);
-        visit_rows_x4<G>(
-            ptr, col, w, r0,
-            [&](int32_t j) {
-                if constexpr (Y0) {
-                    const float2 hv = reinterpret_cast<const float2*>(H0)[j];
-                    return make_float4(y0_of(hv, w04.x, w14.x, bb4.x), y0_of(hv, w04.y, w14.y, bb4.y),
-                                       y0_of(hv, w04.z, w14.z, bb4.z), y0_of(hv, w04.w, w14.w, bb4.w));
-                } else {
-                    return *reinterpret_cast<const float4*>(Yp + static_cast<int64_t>(j) * HD + c4);
-                }
-            },
-            [&](float wp, const float4& v, int32_t self) {
-                const float4 x = make_float4(normrelu(v.x, mu4.x, rs4.x, ga4.x, be4.x),
-                                             normrelu(v.y, mu4.y, rs4.y, ga4.y, be4.y),
-                                             normrelu(v.z, mu4.z, rs4.z, ga4.z, be4.z),
-                                             normrelu(v.w, mu4.w, rs4.w, ga4.w, be4.w));
-                h4.x += wp * x.x;
-                h4.y += wp * x.y;
-                h4.z += wp * x.z;
-                h4.w += wp * x.w;
-                if (self >= 0) {
-                    float* xs = &Xs[self - tile * TILE][c4];
-                    xs[0] = x.x;
-                    xs[1] = x.y;
-                    xs[2] = x.z;
-                    xs[3] = x.w;
-                }
-            },
-            [&](int32_t row) {
-                const float4 hv = row < end ? h4 : make_float4(0.f, 0.f, 0.f, 0.f);
-                float* hs = &Hs[row - tile * TILE][c4];
-                hs[0] = hv.x;
-                hs[1] = hv.y;
-                hs[2] = hv.z;
-                hs[3] = hv.w;
-                if (Hout) *reinterpret_cast<float4*>(Hout + static_cast<int64_t>(row) * HD + c4) = hv;
-                h4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            });
+    const int c4 = 4 * static_cast<int>(threadIdx.x % G);  // the lane's channels: c4 .. c4 + 3
+    float* const hs = &Hs[g0 - tile * TILE][c4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(hs + i * LD) = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (Hout)
+        for_empty_rows(ptr, g0, [&](int i) {
+            *reinterpret_cast<float4*>(Hout + static_cast<int64_t>(g0 + i) * HD + c4) = make_float4(0.f, 0.f, 0.f, 0.f);
+        });
+    float4 mu4, rs4, ga4, be4;
+    float4 w04 = make_float4(0.f, 0.f, 0.f, 0.f), w14 = w04, bb4 = w04;
+    float4 h4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    visit_rows_x4<G, Y0>(
+        rp, col, w,
+        [&] {
+            mu4 = *reinterpret_cast<const float4*>(mup + g * HD + c4);
+            rs4 = *reinterpret_cast<const float4*>(rsp + g * HD + c4);
+            ga4 = *reinterpret_cast<const float4*>(gam + c4);
+            be4 = *reinterpret_cast<const float4*>(bet + c4);
+            if constexpr (Y0) {
+                w04 = *reinterpret_cast<const float4*>(W0 + c4);
+                w14 = *reinterpret_cast<const float4*>(W0 + HD + c4);
+                bb4 = *reinterpret_cast<const float4*>(b0 + c4);
+            }
+        },
+        [&](int32_t j) {
+            if constexpr (Y0) {
+                return reinterpret_cast<const float2*>(H0)[j];
+            } else {
+                const Off at = static_cast<Off>(j) * (HD * 4) + c4 * 4;
+                return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(Yp) + at);
+            }
+        },
+        [&](float wp, const auto& in) {
+            float4 v;
+            if constexpr (Y0)
+                v = make_float4(y0_of(in, w04.x, w14.x, bb4.x), y0_of(in, w04.y, w14.y, bb4.y),
+                                y0_of(in, w04.z, w14.z, bb4.z), y0_of(in, w04.w, w14.w, bb4.w));
+            else
+                v = in;
+            h4.x += wp * normrelu(v.x, mu4.x, rs4.x, ga4.x, be4.x);
+            h4.y += wp * normrelu(v.y, mu4.y, rs4.y, ga4.y, be4.y);
+            h4.z += wp * normrelu(v.z, mu4.z, rs4.z, ga4.z, be4.z);
+            h4.w += wp * normrelu(v.w, mu4.w, rs4.w, ga4.w, be4.w);
+        },
+        [&](int i) {
+            *reinterpret_cast<float4*>(hs + i * LD) = h4;
+            if (Hout) *reinterpret_cast<float4*>(Hout + static_cast<int64_t>(g0 + i) * HD + c4) = h4;
+            h4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        });
+    // From here on a lane holds the same rows g0 .. g0 + 3 and channels c4 .. c4 + 3 as in the walk:
+    // the product's column block nb covers the channels 4 i + nb, so that its 16 results per lane
+    // are four rows of four neighbouring channels.
+    float4 xv[4];  // the rows' own inputs, loaded while the product runs
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (Y0)
+            xv[e] = y0_of4(reinterpret_cast<const float2*>(H0)[g0 + e], w04, w14, bb4);
+        else
+            xv[e] = *reinterpret_cast<const float4*>(Yp + static_cast<int64_t>(g0 + e) * HD + c4);
     }
-    __syncthreads();
-    tile_gemm<HD, MFMA, true, X3, true>(Hs, W, nullptr, Ds, nullptr, wbf, wbf + HD * HD);
-    __syncthreads();
-    // y of the wave's rows with the per-tile sums of y and y^2 and the readout partials of the
-    // layer below (sum, max and first arg-max of x per channel; each row's x came with its own
-    // entry, rows past the graph have none), each summed over the rows in order
-    const float bc = b[c];
-    double s1 = 0.0, s2 = 0.0, ps = 0.0;
-    float mx = -INFINITY;
-    int32_t am = INT32_MAX;
-    for (int r = 0; r < 16; ++r) {
-        const int lr = wv * 16 + r;
-        const int32_t row = tile * TILE + lr;
-        float y = 0.0f;
-        if (row < end) {
-            y = Ds[lr][c] + bc;
-            s1 += y;
-            s2 += static_cast<double>(y) * y;
-            const float x = Xs[lr][c];
-            ps += x;
-            if (x > mx) {
-                mx = x;
-                am = row;
+    const float4 b4 = *reinterpret_cast<const float4*>(b + c4);
+    wave_sync();
+    float4 yv[4];
+    if constexpr (MFMA) {
+        f32x4 acc[4];
+        tile_product<HD, X3, LD>(Hs, wbf, acc);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) yv[e] = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
+    } else {
+        tile_gemm<HD, false, false, LD>(Hs, W, nullptr, Hs);
+        wave_sync();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) yv[e] = *reinterpret_cast<const float4*>(hs + e * LD);
+    }
+    // y of the lane's rows, the sums of y and y^2 and the readout partials of the layer below (sum,
+    // max and first arg-max of x per channel): over the lane's rows, then the 16 rows of the HD
+    // lanes, then the tile, in a fixed order
+    double s1[4] = {}, s2[4] = {}, ps[4] = {};
+    float mx[4];
+    int32_t am[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        mx[k] = -INFINITY;
+        am[k] = INT32_MAX;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int32_t row = g0 + e;
+        const bool ok = row < end;
+        const float y[4] = {ok ? yv[e].x + b4.x : 0.0f, ok ? yv[e].y + b4.y : 0.0f, ok ? yv[e].z + b4.z : 0.0f,
+                            ok ? yv[e].w + b4.w : 0.0f};
+        const float x[4] = {normrelu(xv[e].x, mu4.x, rs4.x, ga4.x, be4.x), normrelu(xv[e].y, mu4.y, rs4.y, ga4.y, be4.y),
+                            normrelu(xv[e].z, mu4.z, rs4.z, ga4.z, be4.z), normrelu(xv[e].w, mu4.w, rs4.w, ga4.w, be4.w)};
+        *reinterpret_cast<float4*>(Y + static_cast<int64_t>(row) * HD + c4) = make_float4(y[0], y[1], y[2], y[3]);
+        if (!ok) continue;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            s1[k] += y[k];
+            s2[k] += static_cast<double>(y[k]) * y[k];
+            ps[k] += x[k];
+            if (x[k] > mx[k]) {
+                mx[k] = x[k];
+                am[k] = row;
             }
         }
-        Y[static_cast<int64_t>(row) * HD + c] = y;
     }
-    // every wave has read its rows of the tile, whose space now holds the four waves' partials;
-    // wave 0 combines them in wave order
-    __syncthreads();
-    double (*r1)[HD] = reinterpret_cast<double (*)[HD]>(&Hs[0][0]);
-    double (*r2)[HD] = r1 + 4;
-    double (*rp)[HD] = r1 + 8;
-    float (*rmax)[HD] = reinterpret_cast<float (*)[HD]>(r1 + 12);
-    int32_t (*rarg)[HD] = reinterpret_cast<int32_t (*)[HD]>(rmax + 4);
-    r1[wv][c] = s1;
-    r2[wv][c] = s2;
-    rp[wv][c] = ps;
-    rmax[wv][c] = mx;
-    rarg[wv][c] = am;
+    const int cc = c4 + reduced_channel<G>();
+    const double t1 = reduce_groups<G>(s1), t2 = reduce_groups<G>(s2), tp = reduce_groups<G>(ps);
+    reduce_groups_max<G>(mx, am);
+    // each group of HD lanes puts its partials where its rows of the tile were; the first adds them
+    // up in order
+    auto part = [&](int k) { return reinterpret_cast<double*>(&Hs[16 * k][0]); };
+    static_assert(16 * LD * sizeof(float) >= HD * (3 * sizeof(double) + sizeof(float) + sizeof(int32_t)), "they fit");
+    {
+        double* r = part(wv);
+        r[cc] = t1;
+        r[HD + cc] = t2;
+        r[2 * HD + cc] = tp;
+        float* rm = reinterpret_cast<float*>(r + 3 * HD);
+        rm[cc] = mx[0];
+        reinterpret_cast<int32_t*>(rm + HD)[cc] = am[0];
+    }
     __syncthreads();
     if (wv == 0) {
-        tstat[tile * 2 * HD + c] = r1[0][c] + r1[1][c] + r1[2][c] + r1[3][c];
-        tstat[tile * 2 * HD + HD + c] = r2[0][c] + r2[1][c] + r2[2][c] + r2[3][c];
-        for (int k = 1; k < 4; ++k)
-            if (rmax[k][c] > mx) {
-                mx = rmax[k][c];
-                am = rarg[k][c];
-            }
-        psum[tile * HD + c] = rp[0][c] + rp[1][c] + rp[2][c] + rp[3][c];
-        pmax[tile * HD + c] = mx;
-        parg[tile * HD + c] = am;
+        tstat[tile * 2 * HD + c] = part(0)[c] + part(1)[c] + part(2)[c] + part(3)[c];
+        tstat[tile * 2 * HD + HD + c] = part(0)[HD + c] + part(1)[HD + c] + part(2)[HD + c] + part(3)[HD + c];
+        psum[tile * HD + c] = part(0)[2 * HD + c] + part(1)[2 * HD + c] + part(2)[2 * HD + c] + part(3)[2 * HD + c];
+        float m = -INFINITY;
+        int32_t a = INT32_MAX;
+        for (int k = 0; k < 4; ++k) {
+            const float* rm = reinterpret_cast<const float*>(part(k) + 3 * HD);
+            max_merge(m, a, rm[c], reinterpret_cast<const int32_t*>(rm + HD)[c]);
+        }
+        pmax[tile * HD + c] = m;
+        parg[tile * HD + c] = a;
     }
 }
 
@@ -714,14 +922,6 @@ __device__ __forceinline__ void norm_of(double s1, double s2, double n, float* m
     if (var < 0.0) var = 0.0;
     *mu = static_cast<float>(m);
     *rstd = static_cast<float>(1.0 / sqrt(var + static_cast<double>(kEps)));
-}
-
-// Max with its arg-max, ties to the lowest node index (any combination order gives the same).
-__device__ __forceinline__ void max_merge(float& mx, int32_t& am, float m2, int32_t a2) {
-    if (m2 > mx || (m2 == mx && a2 < am)) {
-        mx = m2;
-        am = a2;
-    }
 }
 
 // Sum, max and arg-max over the items as sum_items takes them, the waves combined; valid in wave 0.
@@ -824,26 +1024,6 @@ __global__ __launch_bounds__(4 * HD) void chunk_sum_kernel(const double* __restr
     const int k = blockIdx.x, j = blockIdx.y, wv = threadIdx.x / HD, c = threadIdx.x % HD;
     const double s = sum_items<HD>(in + j * HD, K * HD, bounds[k], bounds[k + 1], wv, c, sh);
     if (wv == 0) out[(static_cast<int64_t>(k) * K + j) * HD + c] = s;
-}
-
-// y of rows r0 .. r0 + 15 in channel c (0 past the graph's end): read from Y, or formed from H0
-// for layer 0; the 16 loads are issued together.
-template <int HD, bool Y0>
-__device__ __forceinline__ void load_rows(float (&yv)[16], int32_t r0, int32_t end, int c, const float* __restrict__ Y,
-                                          const float* __restrict__ H0, const float* __restrict__ W0,
-                                          const float* __restrict__ b0) {
-    if constexpr (Y0) {
-        const float w0 = W0[c], w1 = W0[HD + c], bb = b0[c];
-        float2 hv[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            hv[r] = r0 + r < end ? reinterpret_cast<const float2*>(H0)[r0 + r] : make_float2(0.0f, 0.0f);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? y0_of(hv[r], w0, w1, bb) : 0.0f;
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? Y[static_cast<int64_t>(r0 + r) * HD + c] : 0.0f;
-    }
 }
 
 // Per tile: sum, max and first arg-max of x = ReLU(IN(y)) per channel (the last layer's readout).
@@ -1690,13 +1870,17 @@ void forward_impl(gcin_batch* b, int degree, int precision, const float* P, floa
     if (mfma) weights_bf16_kernel<HD><<<dim3(NL - 1, HD * HD / 256), 256, 0, st>>>(P, o, b->wbf);
     for (int l = 1; l < NL; ++l) {
         const bool y0 = l == 1;
-        auto kern = y0 ? layer_kernel<HD, false, false, true> : layer_kernel<HD, false, false, false>;
-        if constexpr (HD == 64) {
-            if (precision == GCIN_BF16X3)
-                kern = y0 ? layer_kernel<HD, true, true, true> : layer_kernel<HD, true, true, false>;
-            else if (precision == GCIN_BF16)
-                kern = y0 ? layer_kernel<HD, true, false, true> : layer_kernel<HD, true, false, false>;
-        }
+        auto pick = [&](auto off) {
+            using Off = decltype(off);
+            if constexpr (HD == 64) {
+                if (precision == GCIN_BF16X3)
+                    return y0 ? layer_kernel<HD, true, true, true, uint32_t> : layer_kernel<HD, true, true, false, Off>;
+                if (precision == GCIN_BF16)
+                    return y0 ? layer_kernel<HD, true, false, true, uint32_t> : layer_kernel<HD, true, false, false, Off>;
+            }
+            return y0 ? layer_kernel<HD, false, false, true, uint32_t> : layer_kernel<HD, false, false, false, Off>;
+        };
+        auto kern = b->N * HD * 4 <= UINT32_MAX ? pick(uint32_t{}) : pick(uint64_t{});
         kern<<<T, NT, 0, st>>>(b->ptr, b->col, b->w, b->d_tile_graph, b->d_gend, b->Y[l - 1], b->H0, W0, b0,
                                b->mu[l - 1], b->rstd[l - 1], P + o.gam[l - 1], P + o.bet[l - 1], P + o.convW[l],
                                P + o.convb[l], b->wbf + static_cast<int64_t>(l - 1) * 2 * HD * HD, b->H[l], b->Y[l],

@@ -32,6 +32,7 @@ HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math
 
 HIP_SOURCES = {
     "k_csr.hip": ["-ffp-contract=off"],  # same rounding as a plain sequential CSR product
+    "k_pair.hip": ["-ffp-contract=off"],
     "k_vec.hip": [],
     "k_setup.hip": [],
     "k_smoother.hip": ["-ffp-contract=off"],

@@ -92,6 +92,19 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
             L.rval = b.take<double>(pz);
             L.rval32 = b.take<float>(pz);
             max_nc = std::max(max_nc, L.nc);
+            // padded rows, up to two and a half times the mean length (a wider matrix is mostly padding)
+            auto take_pad = [&](Level::Pad& pd, int32_t rows_m, int32_t nz, int widest) {
+                pd = Level::Pad{};
+                if (L.n > kPairMaxRows || stream_rows_for(rows_m, nz) <= 0) return;
+                pd.cap = static_cast<int>(std::min<int64_t>(widest, (5 * static_cast<int64_t>(nz) / (2 * rows_m) + 7) / 4 * 4));
+                const size_t m = static_cast<size_t>(rows_m) * pd.cap;
+                pd.col = b.take<int32_t>(m);
+                pd.v64 = b.take<double>(m);
+                pd.v32 = b.take<float>(m);
+            };
+            take_pad(L.pad_a, L.n, L.nnz, kPairMaxWidthA);
+            take_pad(L.pad_p, L.n, L.pnnz, kPairMaxWidthA);
+            take_pad(L.pad_r, L.nc, L.pnnz, kPairMaxWidthR);
             L.dense = L.inv = nullptr;
             L.piv = nullptr;
             const int rows = L.n <= kFuseMaxRows ? stream_rows_for(L.n, L.nnz) : 0;
@@ -141,7 +154,7 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
     c->flags = b.take<int32_t>(8);
     c->cursor = b.take<int32_t>(max_nc + 1);
     c->pack_parts = b.take<int32_t>(kScanPartsMax + 1);
-    c->blkmax = b.take<int32_t>(3 * AMGG_MAX_LEVELS);
+    c->blkmax = b.take<int32_t>(6 * AMGG_MAX_LEVELS);
     c->ra = b.take<double>(n0);
     c->rb = b.take<double>(n0);
     c->z = b.take<double>(n0);
@@ -220,11 +233,7 @@ hipError_t vcycle_level(amgg_ctx* c, int l, const T* f, T* u, T* t, bool zero, i
     int k0 = 0;
     bool have_r = false;
     if (u_ready) {
-        if (nu1 == 1) {
-            if ((e = csr_apply<T>(L.A(), L.aval<T>(), cur, r, f, nullptr, nullptr, Epi::Resid, st)) != hipSuccess)
-                return e;
-            have_r = true;
-        } else {
+        if (nu1 != 1) {
             if ((e = csr_apply<T>(L.A(), L.aval<T>(), cur, oth, f, L.qd<T>(), cur, Epi::Jacobi, st)) != hipSuccess)
                 return e;
             std::swap(cur, oth);
@@ -251,30 +260,43 @@ hipError_t vcycle_level(amgg_ctx* c, int l, const T* f, T* u, T* t, bool zero, i
     for (int k = k0; k < nu1; ++k)
         if ((e = smooth_step<T>(L, f, cur, oth, r, zero && k == 0, st)) != hipSuccess) return e;
     const bool still_zero = zero && nu1 == 0;
+    Level& C = c->lv[l + 1];
+    // the restriction also forms the coarse level's first smoothing step where that is diagonal
+    const bool ready = takes_ready_u(c, l + 1, nu1);
+    const bool down = !still_zero && !have_r && L.pairs();
     const T* res = f;
     if (!still_zero && have_r) {
         res = r;
-    } else if (!still_zero) {
+    } else if (!still_zero && !down) {
         if ((e = csr_apply<T>(L.A(), L.aval<T>(), cur, r, f, nullptr, nullptr, Epi::Resid, st)) != hipSuccess)
             return e;
         res = r;
     }
-    Level& C = c->lv[l + 1];
-    // the restriction also forms the coarse level's first smoothing step where that is diagonal
-    const bool ready = takes_ready_u(c, l + 1, nu1);
-    if ((e = csr_apply<T>(L.R(), L.rv<T>(), res, C.f<T>(), nullptr, ready ? C.qd<T>() : nullptr, nullptr,
+    if (down) {
+        if ((e = resid_restrict<T>(L.nc, L.pad_r.view<T>(), L.pad_a.view<T>(), cur, f, C.f<T>(),
+                                   ready ? C.qd<T>() : nullptr, ready ? C.u<T>() : nullptr, st)) != hipSuccess)
+            return e;
+    } else if ((e = csr_apply<T>(L.R(), L.rv<T>(), res, C.f<T>(), nullptr, ready ? C.qd<T>() : nullptr, nullptr,
                           ready ? Epi::StoreScaled : Epi::Store, st, ready ? C.u<T>() : nullptr)) != hipSuccess)
         return e;
     T* ec = nullptr;
     if ((e = vcycle_level<T>(c, l + 1, C.f<T>(), C.u<T>(), C.t<T>(), true, nu1, nu2, st, &ec, store, ready)) !=
         hipSuccess)
         return e;
-    if ((e = csr_apply<T>(L.P(), L.pv<T>(), ec, cur, nullptr, nullptr, nullptr, still_zero ? Epi::Store : Epi::Add,
-                          st)) != hipSuccess)
+    int m0 = 0;  // post-smoothing steps done
+    if (!still_zero && !store && nu2 >= 1 && L.smoother == kSmootherDiagonal && L.pairs()) {
+        if ((e = prolong_jacobi<T>(L.n, L.pad_a.view<T>(), L.pad_p.view<T>(), ec, cur, f, L.qd<T>(), oth, st)) !=
+            hipSuccess)
+            return e;
+        std::swap(cur, oth);
+        m0 = 1;
+    } else if ((e = csr_apply<T>(L.P(), L.pv<T>(), ec, cur, nullptr, nullptr, nullptr,
+                                 still_zero ? Epi::Store : Epi::Add, st)) != hipSuccess) {
         return e;
+    }
     // the adjoint recomputes post-smoothing from this iterate
     if (store && (e = vec_copy<T>(L.n, cur, L.adj<T>(kAdjUmid), st)) != hipSuccess) return e;
-    for (int k = 0; k < nu2; ++k)
+    for (int k = m0; k < nu2; ++k)
         if ((e = smooth_step<T>(L, f, cur, oth, r, false, st)) != hipSuccess) return e;
     *result = cur;
     return hipSuccess;
@@ -541,7 +563,7 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
         }
         if (e != hipSuccess) return hip_fail(e, "amgg_finalize (column packing)");
         // largest row block of every CSR-stream matrix: sizes the kernels' LDS product buffers
-        ok(vec_zero_bytes(c->blkmax, sizeof(int32_t) * 3 * AMGG_MAX_LEVELS, st));
+        ok(vec_zero_bytes(c->blkmax, sizeof(int32_t) * 6 * AMGG_MAX_LEVELS, st));
         for (int l = 0; l < c->nlevels && e == hipSuccess; ++l) {
             Level& L = c->lv[l];
             int32_t* m = c->blkmax + 3 * l;
@@ -550,11 +572,17 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
                 ok(block_max_entries(L.n, L.pptr, stream_rows_for(L.n, L.pnnz), m + 1, st));
                 ok(block_max_entries(L.nc, L.rptr, stream_rows_for(L.nc, L.pnnz), m + 2, st));
             }
+            if (L.pad_a.cap > 0 && L.pad_p.cap > 0 && L.pad_r.cap > 0) {  // longest rows
+                int32_t* w = c->blkmax + 3 * (AMGG_MAX_LEVELS + l);
+                ok(block_max_entries(L.n, L.ptr, 1, w, st));
+                ok(block_max_entries(L.n, L.pptr, 1, w + 1, st));
+                ok(block_max_entries(L.nc, L.rptr, 1, w + 2, st));
+            }
         }
         if (e != hipSuccess) return hip_fail(e, "amgg_finalize (row blocks)");
         if ((e = build_halos(c, st)) != hipSuccess) return hip_fail(e, "amgg_finalize (halo lists)");
         int32_t flags[3] = {0, 0, 0};
-        std::vector<int32_t> bmax(3 * AMGG_MAX_LEVELS, 0);
+        std::vector<int32_t> bmax(6 * AMGG_MAX_LEVELS, 0);
         if ((e = hipMemcpyAsync(flags, c->flags, sizeof(flags), hipMemcpyDeviceToHost, st)) != hipSuccess ||
             (e = hipMemcpyAsync(bmax.data(), c->blkmax, sizeof(int32_t) * bmax.size(), hipMemcpyDeviceToHost, st)) !=
                 hipSuccess ||
@@ -565,6 +593,24 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
             c->lv[l].pcap = stream_cap_for(bmax[3 * l + 1]);
             c->lv[l].rcap = stream_cap_for(bmax[3 * l + 2]);
         }
+        for (int l = 0; l + 1 < c->nlevels; ++l) {
+            Level& L = c->lv[l];
+            const int32_t* longest = bmax.data() + 3 * (AMGG_MAX_LEVELS + l);
+            Level::Pad* pads[3] = {&L.pad_a, &L.pad_p, &L.pad_r};
+            int w[3];
+            bool fit = true;
+            for (int k = 0; k < 3; ++k) {
+                w[k] = std::max(4, (longest[k] + 3) / 4 * 4);
+                fit = fit && w[k] <= pads[k]->cap;
+            }
+            if (!fit || static_cast<int64_t>(L.n) * w[0] > kPairMaxSlots) continue;
+            ok(pad_rows(L.n, w[0], L.ptr, L.col, L.val, L.pad_a.col, L.pad_a.v64, L.pad_a.v32, st));
+            ok(pad_rows(L.n, w[1], L.pptr, L.pcol, L.pval, L.pad_p.col, L.pad_p.v64, L.pad_p.v32, st));
+            ok(pad_rows(L.nc, w[2], L.rptr, L.rcol, L.rval, L.pad_r.col, L.pad_r.v64, L.pad_r.v32, st));
+            for (int k = 0; k < 3; ++k) pads[k]->w = w[k];
+        }
+        ok(hipStreamSynchronize(st));
+        if (e != hipSuccess) return hip_fail(e, "amgg_finalize (padded rows)");
         if (flags[0]) return fail(AMGG_EINVAL, "amgg_finalize: a level matrix has a missing or non-positive diagonal");
         if (flags[1]) return fail(AMGG_EINVAL, "amgg_finalize: coarsest matrix is singular (zero pivot)");
         if (flags[2]) return fail(AMGG_EINVAL, "amgg_finalize: a prolongation couples different blocks");

@@ -86,6 +86,20 @@ struct Level {
     };
     Pack pa, pp, pr;
     int pack = 1;  // packing mode of the CSR-stream kernels (see Pack::view)
+    // padded rows of A_l, P_l and R_l for the paired passes of small levels (k_pair.hip)
+    struct Pad {
+        int cap = 0;  // widest row the workspace has room for (0: none)
+        int w = 0;    // width in use, set at finalize (0: some row is longer)
+        int32_t* col = nullptr;
+        double* v64 = nullptr;
+        float* v32 = nullptr;
+        template <typename T> PadView<T> view() const {
+            if constexpr (std::is_same_v<T, double>) return {w, col, v64};
+            else return {w, col, v32};
+        }
+    };
+    Pad pad_a, pad_p, pad_r;
+    bool pairs() const { return fuse && pad_a.w > 0 && pad_p.w > 0 && pad_r.w > 0; }
     // adjoint scratch, kAdjVecs vectors of n per precision (see AdjVec)
     double* adj64[8] = {};
     float* adj32[8] = {};

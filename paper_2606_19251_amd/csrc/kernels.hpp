@@ -179,6 +179,33 @@ hipError_t jacobi_pre_resid(const CsrView& m, const T* a, const T* d, const T* f
 template <typename T>
 hipError_t jacobi_pre_step(const CsrView& m, const T* a, const T* d, const T* f, T* y, hipStream_t stream);
 
+// Pairs of passes in one kernel on small levels (k_pair.hip), from rows padded to a common width w
+// (a multiple of 4; column -1 past a row's end). They serve levels whose padded matrix A holds at most
+// kPairMaxSlots entries: there both passes are latency and the pair costs little more than one of them.
+// Measured per V-cycle, the four separate passes of a level against the two pairs, us: 1.1k rows of 13
+// entries 12.5 / 8.1, 4.9k 14.2 / 8.6, 21k (w = 24) 14.7 / 13.4; beyond, the pairs' repeated work shows:
+// 24k rows (w = 32) 14.9 / 15.9, 11k rows with some of 60 entries (w = 64) 14.8 / 15.4, 91k 21.3 / 30.
+constexpr int64_t kPairMaxSlots = 1 << 19;
+constexpr int32_t kPairMaxRows = 32768;
+constexpr int kPairMaxWidthA = 64;
+constexpr int kPairMaxWidthR = 32;
+template <typename T>
+struct PadView {
+    int w;  // 0: none
+    const int32_t* col;
+    const T* val;
+};
+hipError_t pad_rows(int32_t n, int w, const int32_t* ptr, const int32_t* col, const double* val, int32_t* pcol,
+                    double* p64, float* p32, hipStream_t stream);
+// f_c = R (f - A u), and with dc also u_c = dc f_c (the coarse level's first diagonal step from zero)
+template <typename T>
+hipError_t resid_restrict(int32_t nc, const PadView<T>& R, const PadView<T>& A, const T* u, const T* f, T* fc,
+                          const T* dc, T* uc, hipStream_t stream);
+// z = u + P e, y = z + d (f - A z); y must not alias u
+template <typename T>
+hipError_t prolong_jacobi(int32_t n, const PadView<T>& A, const PadView<T>& P, const T* e, const T* u, const T* f,
+                          const T* d, T* y, hipStream_t stream);
+
 // q = A p and per-workgroup partial sums of p_i q_i (FP64 outer loop); *count = partials written.
 hipError_t csr_spmv_dot(const CsrView& m, const double* val, const double* p, double* q, double* partial, int* count,
                         hipStream_t stream);

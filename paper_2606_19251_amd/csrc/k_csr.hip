@@ -88,32 +88,56 @@ __device__ __forceinline__ void block_partial(double v, double* partial) {
     }
 }
 
-constexpr int kChunk = 8;  // entries per thread per round of a product stream
+constexpr int kChunk = 8;  // most entries per thread per round of a product stream
+
+// One round of a product stream: out[base + k] = m[base + k] * gather(column(base + k)) for the next
+// CH * kBlock entries (fewer at the end of the block). All value/column loads are issued together and
+// then all gathers, so that each wave keeps many loads in flight; a thread past the end re-reads
+// the last entry (same cache line) and stores its unused product past ne instead of branching.
+// out must hold base + CH * kBlock products.
+template <typename T, int CH, class Column, class Gather>
+__device__ __forceinline__ void stream_round(int32_t base, int32_t ne, const T* __restrict__ m, Column column,
+                                             Gather gather, T* __restrict__ out) {
+    T v[CH];
+    int32_t c[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) {
+        const int32_t k = min(base + static_cast<int32_t>(threadIdx.x) + q * kBlock, ne - 1);
+        v[q] = m[k];
+        c[q] = column(k);
+    }
+    T p[CH];
+#pragma unroll
+    for (int q = 0; q < CH; ++q) p[q] = v[q] * gather(c[q]);
+#pragma unroll
+    for (int q = 0; q < CH; ++q) out[base + static_cast<int32_t>(threadIdx.x) + q * kBlock] = p[q];
+}
+
+// The block's products in rounds of at most kChunk entries per thread, the last of 3 or 5 where that
+// is enough: a thread past the end costs as much as one with an entry (the address units take a
+// wavefront's lanes four a cycle), and blocks seldom hold whole rounds of 2048 (256 rows of 5 entries
+// 1280, of a prolongation 600). 4.5M tetrahedra: FP64 residual 83.7 -> 77.0 us, fine prolongation
+// 36.3 -> 33.4; 1M-point mesh: prolongation 9.6 -> 8.2. Three lengths and not more: the kernels of
+// small levels are so short that fetching more code shows (six lengths: 0.2 us a kernel).
+template <typename T, class Column, class Gather>
+__device__ __forceinline__ void stream_rounds(int32_t ne, const T* __restrict__ m, Column column, Gather gather,
+                                              T* __restrict__ out) {
+    int32_t base = 0;
+    for (; ne - base > 5 * kBlock; base += kChunk * kBlock)
+        stream_round<T, kChunk>(base, ne, m, column, gather, out);
+    const int32_t left = ne - base;  // uniform over the workgroup
+    if (left > 3 * kBlock)
+        stream_round<T, 5>(base, ne, m, column, gather, out);
+    else if (left > 0)
+        stream_round<T, 3>(base, ne, m, column, gather, out);
+}
 
 // out[k] = m[k] * g(col[k]) for k < ne, where m and col are already offset to the block's first
-// entry and g(j) = x[j] (or d[j] * x[j] with SCALED, rounded as a separate product). Every round
-// gives each thread kChunk entries; a thread past the end re-reads the last entry (same cache
-// line) and stores its unused product past ne instead of branching, so that all value/column
-// loads of a round are issued together and then all of its gathers: each wave keeps many loads
-// in flight. out must hold ne rounded up to a multiple of kChunk * kBlock.
+// entry and g(j) = x[j] (or d[j] * x[j], rounded as a separate product).
 template <typename T, class Gather>
 __device__ __forceinline__ void stream_products_g(int32_t ne, const T* __restrict__ m,
                                                   const int32_t* __restrict__ col, Gather gather, T* __restrict__ out) {
-    for (int32_t base = 0; base < ne; base += kChunk * kBlock) {
-        T v[kChunk];
-        int32_t c[kChunk];
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-            const int32_t k = min(base + static_cast<int32_t>(threadIdx.x) + q * kBlock, ne - 1);
-            v[q] = m[k];
-            c[q] = col[k];
-        }
-        T p[kChunk];
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) p[q] = v[q] * gather(c[q]);
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) out[base + static_cast<int32_t>(threadIdx.x) + q * kBlock] = p[q];
-    }
+    stream_rounds<T>(ne, m, [&](int32_t k) { return col[k]; }, gather, out);
 }
 
 // The same products from packed columns (ColPack): a round loads 2-byte offsets instead of
@@ -125,22 +149,13 @@ template <typename T, class Gather>
 __device__ __forceinline__ void stream_products_packed(int32_t ne, const T* __restrict__ m,
                                                        const uint16_t* __restrict__ off, int32_t cbase, Gather gather,
                                                        T* __restrict__ out) {
-    for (int32_t base = 0; base < ne; base += kChunk * kBlock) {
-        T v[kChunk];
-        int32_t c[kChunk];
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-            const int32_t k = min(base + static_cast<int32_t>(threadIdx.x) + q * kBlock, ne - 1);
-            v[q] = m[k];
+    stream_rounds<T>(
+        ne, m,
+        [&](int32_t k) {
             const uint32_t o = off[k];
-            c[q] = cbase + static_cast<int32_t>(o == kFarCol ? 0u : o);
-        }
-        T p[kChunk];
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) p[q] = v[q] * gather(c[q]);
-#pragma unroll
-        for (int q = 0; q < kChunk; ++q) out[base + static_cast<int32_t>(threadIdx.x) + q * kBlock] = p[q];
-    }
+            return cbase + static_cast<int32_t>(o == kFarCol ? 0u : o);
+        },
+        gather, out);
 }
 
 template <typename T, class Gather>
@@ -170,15 +185,6 @@ __device__ __forceinline__ void block_products(int32_t b, int32_t e0, int32_t ne
     }
 }
 
-template <typename T, bool SCALED = false>
-__device__ __forceinline__ void stream_products(int32_t ne, const T* __restrict__ m, const int32_t* __restrict__ col,
-                                                const T* __restrict__ x, const T* __restrict__ d,
-                                                T* __restrict__ out) {
-    if constexpr (SCALED)
-        stream_products_g<T>(ne, m, col, [&](int32_t j) { return d[j] * x[j]; }, out);
-    else
-        stream_products_g<T>(ne, m, col, [&](int32_t j) { return x[j]; }, out);
-}
 static_assert(kStreamCap % (kChunk * kBlock) == 0, "product buffers hold whole rounds");
 static_assert(kStreamRound == kChunk * kBlock, "a product round");
 

@@ -320,8 +320,9 @@ int amgg_set_fusion(amgg_ctx* ctx, int enable);
  * matrix, prolongation and restriction as 2-byte offsets from a base column per row block, the
  * few columns outside a block's 16-bit window kept in a per-block list (a matrix with more
  * than 1/8 of its entries outside keeps its plain 4-byte columns). mode 1 (the default) reads
- * the packed columns of matrices with at least 2^24 entries, which stream from HBM (smaller
- * ones stay in the last-level cache, where the packing does not pay); mode 2 reads them for
+ * the packed columns of matrices with at least 2^24 entries, which stream from HBM, and of those
+ * with at least 2^21 of which at most one in 128 lies outside its window (smaller ones stay in
+ * the last-level cache, where the packing does not pay otherwise); mode 2 reads them for
  * every matrix whose packing fits; mode 0 never. The products and their order are those of
  * the plain CSR walk, so results are bitwise the same in every mode. Drops the captured
  * solve graphs. */

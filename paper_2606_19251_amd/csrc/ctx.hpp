@@ -77,10 +77,11 @@ struct Level {
         int64_t cap = 0;    // far-entry capacity
         int64_t nfar = -1;  // far entries found at finalize (-1: not built)
         bool usable() const { return rows > 0 && nfar >= 0 && nfar <= cap; }
-        // mode 0: plain columns; 1: packed for matrices of at least kPackMinEntries entries;
-        // 2: packed wherever the packing fits
+        // mode 0: plain columns; 1: packed for matrices of at least kPackMinEntries entries, and for
+        // those of at least kPackMinCached with few far entries; 2: packed wherever the packing fits
         ColPack view(int mode, int32_t nz) const {
-            if (mode == 0 || !usable() || (mode == 1 && nz < kPackMinEntries)) return ColPack{};
+            if (mode == 0 || !usable()) return ColPack{};
+            if (mode == 1 && nz < kPackMinEntries && (nz < kPackMinCached || nfar * kPackFarCached > nz)) return ColPack{};
             return ColPack{off, base, foff, fslot, fcol, rows};
         }
     };

@@ -125,11 +125,16 @@ hipError_t pack_columns(int32_t nrows, int32_t nnz, const int32_t* ptr, const in
                         int32_t* base, int32_t* foff, uint16_t* fslot, int32_t* fcol, int64_t cap, int32_t* parts,
                         int64_t* nfar, hipStream_t stream);
 constexpr int64_t kScanPartsMax = 1024;  // scratch of pack_columns: kScanPartsMax + 1 ints
-// Matrices with fewer entries keep their plain columns: measured on one MI355X, packing pays only
-// where a pass streams its matrix from HBM (8M-cell mesh: fine-level residual 91 -> 84 us,
-// solves 1-3 % faster); a matrix that stays in the 256 MB last-level cache is latency-bound,
-// and there the far-entry pass costs more than the saved bytes (1M P1 mesh: solves 2-5 %
-// slower with every matrix packed). 2^24 entries = 128 MB of FP32 values and plain columns.
+// Which matrices read packed columns by default. Those of at least 2^24 entries (128 MB of FP32 values and
+// plain columns) stream from HBM: there the packing pays however many far entries it has (8M-cell
+// mesh: fine-level residual 91 -> 84 us). One that stays in the 256 MB last-level cache gains less, and
+// the pass over its far entries costs it a barrier and two dependent loads: it pays where almost no
+// entry is far and the matrix is no longer latency-bound. us per pass with plain and packed columns:
+// 7.0M entries with 0.35 % far 12.7 / 11.8, 4.4M with 0.30 % 8.6 / 7.5, 5.2M with none 11.2 / 10.5, 2.3M
+// with none 6.4 / 6.2; 8.5M with 2.4 % 13.9 / 14.2, 5.0M with 2.4 % 9.8 / 10.4; below 2M entries equal
+// or slower.
+constexpr int32_t kPackMinCached = 1 << 21;
+constexpr int kPackFarCached = 128;  // at most one far entry in so many
 constexpr int32_t kPackMinEntries = 1 << 24;
 
 int lanes_for(int32_t nrows, int32_t nnz);

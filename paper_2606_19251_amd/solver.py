@@ -217,7 +217,7 @@ class DeviceSolver:
         capi.amgg_set_fusion(self.ctx, enable)
 
     def set_packed_columns(self, mode: int):
-        """0: plain columns; 1: packed for matrices of >= 2^24 entries (default); 2: packed wherever built."""
+        """0: plain columns; 1: packed for large matrices (default); 2: packed wherever built."""
         capi.amgg_set_packed_columns(self.ctx, mode)
 
     def close(self):

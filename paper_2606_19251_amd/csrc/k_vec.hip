@@ -178,15 +178,32 @@ __global__ __launch_bounds__(kBlock) void fcg_update_xr_kernel(int32_t n, double
     block_partial(v, partial);
 }
 
+// COUNT: also counts a stationary iteration
+template <bool COUNT>
 __global__ __launch_bounds__(kFinish) void fcg_finish_rr_kernel(const double* __restrict__ partial, int count,
                                                               double* __restrict__ s) {
     const double rr = sum_partials(partial, count);
     if (threadIdx.x == 0) {
+        if constexpr (COUNT) s[kIter] += 1.0;
         s[kRR] = rr;
         const double nrm = sqrt(rr);
         s[kNorm] = nrm;
         s[kInvNorm] = nrm > 0.0 ? 1.0 / nrm : 0.0;
     }
+}
+
+__global__ void stationary_store_kernel(int32_t n, const double* __restrict__ res, double* __restrict__ x,
+                                        SavedIterates saved, const double* __restrict__ s) {
+    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    const int k = static_cast<int>(s[kIter]) % kSavedIterates;  // uniform
+    const double v = res[i];
+    x[i] = v;
+    (k == 0 ? saved.v[0] : k == 1 ? saved.v[1] : k == 2 ? saved.v[2] : saved.v[3])[i] = v;
+}
+
+__global__ void set_slot_kernel(double* __restrict__ s, int slot, double v) {
+    if (threadIdx.x == 0) s[slot] = v;
 }
 
 __global__ __launch_bounds__(kBlock) void fcg_castback_dots_kernel(int32_t n, const float* __restrict__ u32,
@@ -421,7 +438,23 @@ hipError_t fcg_update_xr(int32_t n, double* x, const double* p, const double* r,
 }
 
 hipError_t fcg_finish_rr(const double* partial, int count, double* s, hipStream_t stream) {
-    fcg_finish_rr_kernel<<<1, kFinish, 0, stream>>>(partial, count, s);
+    fcg_finish_rr_kernel<false><<<1, kFinish, 0, stream>>>(partial, count, s);
+    return hipGetLastError();
+}
+
+hipError_t stationary_finish(const double* partial, int count, double* s, hipStream_t stream) {
+    fcg_finish_rr_kernel<true><<<1, kFinish, 0, stream>>>(partial, count, s);
+    return hipGetLastError();
+}
+
+hipError_t stationary_store(int32_t n, const double* res, double* x, const SavedIterates& saved, const double* s,
+                            hipStream_t stream) {
+    stationary_store_kernel<<<grid_for(n), kBlock, 0, stream>>>(n, res, x, saved, s);
+    return hipGetLastError();
+}
+
+hipError_t stationary_set_iter(double* s, int iter, hipStream_t stream) {
+    set_slot_kernel<<<1, 64, 0, stream>>>(s, kIter, static_cast<double>(iter));
     return hipGetLastError();
 }
 

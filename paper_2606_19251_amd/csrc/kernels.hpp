@@ -276,7 +276,8 @@ enum FcgSlot : int {
     kScaleNext = 15,  // scale for the residual about to be formed
     kScaleCast = 16,  // scale of the residual held in FP32 (or to be cast next)
     kUnscale = 17,    // 1 / kScaleCast, applied to the cycle's output
-    kSlots = 18
+    kIter = 18,       // stationary iterations done (selects the saved iterate, stationary_store)
+    kSlots = 19
 };
 // Halting. An outer iteration may be enqueued before the host has read the previous one's
 // residual; the guarded steps below then leave x and the residual norm unchanged once the
@@ -307,6 +308,16 @@ hipError_t fcg_update_p32(int32_t n, const float* u32, double* p, const double* 
 // IR: x += (double)u32 * norm  (or x += e64); skipped when halted
 hipError_t ir_update_f32(int32_t n, double* x, const float* u32, const double* s, hipStream_t stream);
 hipError_t ir_update_f64(int32_t n, double* x, const double* e, const double* s, hipStream_t stream);
+// Stationary iteration: x = res, and saved[(int)s[kIter] % kSavedIterates] = res
+constexpr int kSavedIterates = 4;
+struct SavedIterates {
+    double* v[kSavedIterates];
+};
+hipError_t stationary_store(int32_t n, const double* res, double* x, const SavedIterates& saved, const double* s,
+                            hipStream_t stream);
+hipError_t stationary_set_iter(double* s, int iter, hipStream_t stream);  // s[kIter] = iter
+// fcg_finish_rr, then s[kIter] += 1
+hipError_t stationary_finish(const double* partial, int count, double* s, hipStream_t stream);
 
 // ---------------------------------------------------------------------------------------
 // Setup kernels

@@ -205,7 +205,7 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         const double div_factor = o->div_factor > 0 ? o->div_factor : 1e3;
         const double stag_ratio = o->stag_ratio > 0 ? o->stag_ratio : 0.99;
         const int stag_window = o->stag_window > 0 ? o->stag_window : 10;
-        const bool use_graph = o->graphs != 0 && o->outer != AMGG_OUTER_STATIONARY;
+        const bool use_graph = o->graphs != 0;
 
         hipStream_t st = static_cast<hipStream_t>(stream);
         Runner R{c, o->nu1, o->nu2, o->inner_precision};
@@ -254,22 +254,68 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         bool first = true;     // (re)start of the recurrence
         size_t stag_base = 0;  // stagnation is judged on the history since the last (re)start
         int k = 0;             // iterations processed
+        // Enqueue ahead only while the `flight` iterations in flight are not expected to converge (the
+        // residual after the last of them, predicted from the last ratio, stays above twice the
+        // tolerance): an iteration enqueued after the converging one would run its whole cycle for
+        // nothing.
+        auto ahead = [&](size_t flight) {
+            if (hist.size() < 3) return true;
+            const double last = hist[hist.size() - 1], ratio = std::min(1.0, last / hist[hist.size() - 2]);
+            double pred = last;
+            for (size_t m = 0; m < flight; ++m) pred *= ratio;
+            return pred > 2.0 * o->tol;
+        };
         if (o->outer == AMGG_OUTER_STATIONARY) {
-            for (;;) {
-                double* res = nullptr;
-                R.ok(vec_copy<double>(n, x, L0.u64, st));
-                R.ok(vcycle_level<double>(c, 0, bb, L0.u64, L0.t64, first, o->nu1, o->nu2, st, &res));
-                R.ok(vec_copy<double>(n, res, x, st));
-                int cnt = 0;
-                R.ok(csr_resid_norm(A, L0.val, x, bb, cur, c->partial, &cnt, st));
-                R.ok(fcg_finish_rr(c->partial, cnt, s, st));
+            // As below, an iteration is a graph launch with an asynchronous copy of the scalars, and up
+            // to kPipeline - 1 are in flight behind the one the host inspects. An iteration also
+            // saves its iterate in one of kSavedIterates vectors in turn, so that the one the
+            // inspection stops at (by any criterion) is at hand whatever ran after it.
+            static_assert(kSavedIterates >= kPipeline, "in-flight iterations leave the inspected iterate alone");
+            const SavedIterates saved{{c->rb, c->z, c->p, c->q}};
+            double* r = L0.r64;  // free between cycles
+            R.ok(vec_zero_bytes(cur, sizeof(double) * n, st));
+            int launched = 0;
+            auto launch = [&]() -> hipError_t {
+                const bool zero = first;
+                hipError_t e = run_body(c, use_graph, graph_key(c, zero ? "st0" : "st", 64, o->nu1, o->nu2, bb, cur, r),
+                                        st, R, [&](hipStream_t qs) {
+                                            double* res = nullptr;
+                                            int cnt = 0;
+                                            R.ok(vec_copy<double>(n, cur, L0.u64, qs));
+                                            R.ok(vcycle_level<double>(c, 0, bb, L0.u64, L0.t64, zero, o->nu1, o->nu2, qs,
+                                                                      &res));
+                                            R.ok(stationary_store(n, res, cur, saved, s, qs));
+                                            R.ok(csr_resid_norm(A, L0.val, cur, bb, r, c->partial, &cnt, qs));
+                                            R.ok(stationary_finish(c->partial, cnt, s, qs));
+                                        });
                 first = false;
-                ++vcycles;
+                if (e != hipSuccess) return e;
+                const int slot = launched % kPipeline;
+                if ((e = hipMemcpyAsync(hs + (1 + slot) * kSlots, s, sizeof(double) * kSlots, hipMemcpyDeviceToHost,
+                                        st)) != hipSuccess ||
+                    (e = hipEventRecord(c->ev[slot], st)) != hipSuccess)
+                    return e;
+                ++launched;
+                return hipSuccess;
+            };
+            auto iterate = [&]() { return saved.v[(k - 1) % kSavedIterates]; };  // after k iterations
+            auto stop = [&](int status, double rel) -> int {
+                R.ok(vec_copy<double>(n, iterate(), x, st));
+                R.ok(hipStreamSynchronize(st));
+                return R.e != hipSuccess ? hip_fail(R.e, "amgg_solve") : finish(status, rel, k);
+            };
+            for (;;) {
+                hipError_t e = hipSuccess;
+                while (e == hipSuccess && launched - k < kPipeline && launched < o->maxit &&
+                       (launched == k || ahead(static_cast<size_t>(launched - k))))
+                    e = launch();
+                if (e == hipSuccess) e = hipEventSynchronize(c->ev[k % kPipeline]);
+                if (e != hipSuccess) return hip_fail(e, "amgg_solve");
+                const double rel = std::sqrt(hs[(1 + k % kPipeline) * kSlots + kRR]) / nb;
                 ++k;
-                if (!R.read_scalars(st)) return hip_fail(R.e, "amgg_solve");
-                const double rel = std::sqrt(hs[kRR]) / nb;
+                ++vcycles;
                 hist.push_back(rel);
-                if (rel <= o->tol && std::isfinite(rel)) return finish(0, rel, k);
+                if (rel <= o->tol && std::isfinite(rel)) return stop(0, rel);
                 int outcome = 0;
                 if (!std::isfinite(rel) || rel > div_factor)
                     outcome = AMGG_DIVERGED;
@@ -277,17 +323,24 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
                          rel > stag_ratio * hist[hist.size() - 1 - stag_window])
                     outcome = AMGG_STAGNATED;
                 if (outcome == 0) {
-                    if (k >= o->maxit) return finish(AMGG_MAXIT, rel, k);
+                    if (k >= o->maxit) return stop(AMGG_MAXIT, rel);
                     continue;
                 }
                 bool learned = false;
                 for (int l = 0; l + 1 < c->nlevels; ++l) learned |= !c->lv[l].baseline;
-                if (!o->fallback || inf.fell_back || !learned || k >= o->maxit) return finish(outcome, rel, k);
-                // Jacobi fallback from the current x (from zero if it is not finite)
+                if (!o->fallback || inf.fell_back || !learned || k >= o->maxit) return stop(outcome, rel);
+                // Jacobi fallback from the current iterate (from zero if it is not finite); what is in
+                // flight is dropped
+                R.ok(hipStreamSynchronize(st));
                 inf.fell_back = 1;
                 set_all_jacobi(c, st);
                 first = !std::isfinite(rel);
-                if (first) R.ok(vec_zero_bytes(x, sizeof(double) * n, st));
+                if (first)
+                    R.ok(vec_zero_bytes(cur, sizeof(double) * n, st));
+                else
+                    R.ok(vec_copy<double>(n, iterate(), cur, st));
+                R.ok(stationary_set_iter(s, k, st));
+                launched = k;
                 stag_base = hist.size() - 1;
                 if (R.e != hipSuccess) return hip_fail(R.e, "amgg_solve");
             }
@@ -336,22 +389,11 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
             R.ok(hipStreamSynchronize(st));
             return R.e == hipSuccess;
         };
-        // Enqueue ahead only while the in-flight iterations are not expected to converge (the
-        // residual after the last of them, predicted from the last ratio, stays above twice the
-        // tolerance): an iteration enqueued after the converging one would run its whole cycle for
-        // nothing.
-        auto ahead = [&]() {
-            if (hist.size() < 3) return true;
-            const double last = hist[hist.size() - 1], ratio = std::min(1.0, last / hist[hist.size() - 2]);
-            double pred = last;
-            for (size_t m = 0; m < q.size(); ++m) pred *= ratio;
-            return pred > 2.0 * o->tol;
-        };
         for (;;) {
             hipError_t e = hipSuccess;
             if (q.empty()) e = launch();
             while (e == hipSuccess && more && q.size() < static_cast<size_t>(kPipeline) && launched < o->maxit &&
-                   ahead())
+                   ahead(q.size()))
                 e = launch();
             if (e != hipSuccess) return hip_fail(e, "amgg_solve");
             const int slot = k % kPipeline;
@@ -459,7 +501,7 @@ int probe_smoother(amgg_ctx* c, const amgg_solve_opts* o, int iters, const doubl
     p.fallback = 0;
     std::vector<double> hist(static_cast<size_t>(iters) + 1, 1.0);
     amgg_solve_info info{};
-    if (p.graphs && p.outer != AMGG_OUTER_STATIONARY) {
+    if (p.graphs) {
         p.maxit = std::min(2, iters);
         const int rc = amgg_solve(c, &p, b, x, &info, nullptr, 0, st);
         if (rc < 0) return rc;

@@ -3,16 +3,22 @@
 // interpolation from a given C/F split (the split itself, a sequential greedy, stays on the
 // host) and the Galerkin product A_c = R (A P) with R = P^T.
 //
-// Each sparse product C = L * M is formed in two phases:
+// A sparse product C = L * M is formed row by row in LDS: a group of 8 to 256 threads holds row i of C in
+// a hash table (one kernel counts the entries of each row, a second fills them), takes the entries L_ij
+// in ascending column order and adds L_ij M_jk for all k of row j at once, every entry starting
+// from 0.0, with product and sum rounded separately; the columns are then ranked. That is the row-by-row
+// accumulation of the host product, so the values are the host's bit for bit. Rows are served by the
+// table size their product count needs, each class by a launch of its own.
+// Rows of more than kHashMax products (a hub row), more than 2^31 - 1 products in all, or a bound on the
+// expansion asked for by the caller take the expanding form:
 //   symbolic  every product L_ij M_jk is expanded to a key (row i, column k); one radix sort
 //             of the keys and a unique pass give C's pattern (rows in order, columns
 //             ascending) without any floating point;
 //   numeric   one thread per entry c_ik walks row i of L in ascending column order and adds
-//             L_ij M_jk for every j whose row of M holds column k (binary search), starting
-//             from 0.0, with product and sum rounded separately.
-// The numeric order is exactly the row-by-row accumulation of the host product, so the
-// result does not depend on how the symbolic phase orders or batches its work. The
-// expansion is processed in row chunks that bound the temporary memory.
+//             L_ij M_jk for every j whose row of M holds column k (binary search).
+// Its numeric order is the same, so the result does not depend on the form, nor on how the symbolic
+// phase orders or batches its work (row chunks that bound the temporary memory).
+// Finest product of 623k tetrahedral cells (A 3.1M entries, P 1.5M): 2.05 ms expanding, 0.61 row-wise.
 // This file is compiled with -ffp-contract=off: no product may be fused into its sum.
 #include <hip/hip_runtime.h>
 
@@ -416,6 +422,293 @@ DevCsr spgemm(Pool& pool, const ConstCsr& L, const ConstCsr& M, int64_t budget, 
     return C;
 }
 
+template <typename T>
+void exclusive_scan_i32(Pool& pool, const T* in, int32_t* out, int64_t count, hipStream_t st) {
+    size_t tb = 0;
+    check(rocprim::exclusive_scan(nullptr, tb, in, out, int32_t{0}, static_cast<size_t>(count),
+                                  rocprim::plus<int32_t>(), st),
+          "scan size");
+    void* tmp = pool.get<unsigned char>(static_cast<int64_t>(tb));
+    check(rocprim::exclusive_scan(tmp, tb, in, out, int32_t{0}, static_cast<size_t>(count), rocprim::plus<int32_t>(),
+                                  st),
+          "scan");
+}
+
+// ---------------------------------------------------------------------------------------
+// Row-wise product in LDS hash tables
+// ---------------------------------------------------------------------------------------
+// Classes of rows by their products (at most the table's slots, so that a table never overflows):
+// threads per row and slots.
+constexpr int kClasses = 4;
+constexpr int kClassThreads[kClasses] = {8, 16, 64, 256};
+constexpr int kClassSlots[kClasses] = {32, 128, 1024, 8192};
+constexpr int kHashMax = kClassSlots[kClasses - 1];
+
+// nprod[i] = products of row i; per class the number of its rows; [kClasses]: rows beyond the classes,
+// [kClasses + 1]: all products.
+__global__ __launch_bounds__(kThreads) void row_products_kernel(int32_t n, const int32_t* __restrict__ lptr,
+                                                               const int32_t* __restrict__ lcol,
+                                                               const int32_t* __restrict__ mptr,
+                                                               int32_t* __restrict__ nprod,
+                                                               unsigned long long* __restrict__ stats) {
+    __shared__ unsigned long long sums[kClasses + 2];
+    if (threadIdx.x < kClasses + 2) sums[threadIdx.x] = 0;
+    __syncthreads();
+    const int32_t i = blockIdx.x * kThreads + threadIdx.x;
+    int64_t c = 0;
+    if (i < n) {
+        for (int32_t p = lptr[i]; p < lptr[i + 1]; ++p) {
+            const int32_t j = lcol[p];
+            c += mptr[j + 1] - mptr[j];
+        }
+        nprod[i] = static_cast<int32_t>(c < INT32_MAX ? c : INT32_MAX);
+    }
+    int cls = 0;
+    while (cls < kClasses && c > kClassSlots[cls]) ++cls;
+    // one LDS update per wavefront and value (64 lanes on one address take turns)
+    const bool first = (threadIdx.x & 63) == 0;
+#pragma unroll
+    for (int k = 0; k <= kClasses; ++k) {
+        const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0 && cls == k);
+        if (first && m) atomicAdd(&sums[k], static_cast<unsigned long long>(__popcll(m)));
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+    if (first && c) atomicAdd(&sums[kClasses + 1], static_cast<unsigned long long>(c));
+    __syncthreads();
+    if (threadIdx.x < kClasses + 2 && sums[threadIdx.x]) atomicAdd(stats + threadIdx.x, sums[threadIdx.x]);
+}
+
+// The rows of each class (their order within it decides nothing); a row without products has no entries.
+struct ClassLists {
+    int32_t* rows[kClasses];
+};
+__global__ __launch_bounds__(kThreads) void classify_rows_kernel(int32_t n, const int32_t* __restrict__ nprod,
+                                                                ClassLists lists, int32_t* __restrict__ used,
+                                                                int32_t* __restrict__ cnt) {
+    __shared__ int32_t have[kClasses], at[kClasses];
+    if (threadIdx.x < kClasses) have[threadIdx.x] = 0;
+    __syncthreads();
+    const int32_t i = blockIdx.x * kThreads + threadIdx.x;
+    int cls = kClasses, pos = 0;
+    if (i < n) {
+        const int32_t c = nprod[i];
+        if (c == 0) cnt[i] = 0;
+        cls = c == 0 ? kClasses : 0;
+        while (cls < kClasses && c > kClassSlots[cls]) ++cls;
+        if (cls < kClasses) pos = atomicAdd(&have[cls], 1);
+    }
+    __syncthreads();
+    if (threadIdx.x < kClasses && have[threadIdx.x]) at[threadIdx.x] = atomicAdd(used + threadIdx.x, have[threadIdx.x]);
+    __syncthreads();
+    if (cls < kClasses) lists.rows[cls][at[cls] + pos] = i;
+}
+
+// Orders the LDS accesses of a group: a barrier where the group is a workgroup, else the group lies within
+// a wavefront, whose LDS accesses are in order.
+template <int G>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (G > 64) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// Row i of C = L M (i one of the `count` listed rows, or of the first `count`) by G threads in a table of S slots. FILL: writes the
+// row's columns and values at cptr[i]; else its entry count. zeros: set to 1 if an exact zero is
+// written off the diagonal.
+// Bound by latency: an entry of L costs its row bounds of M, its row and the table. The row bounds of G
+// entries of L are loaded together and an entry's row of M while the one before it is added.
+template <int G, int S, bool FILL>
+__global__ __launch_bounds__(kThreads) void row_hash_kernel(
+    int32_t count, const int32_t* __restrict__ rows, const int32_t* __restrict__ lptr,
+    const int32_t* __restrict__ lcol, const double* __restrict__ lval, const int32_t* __restrict__ mptr,
+    const int32_t* __restrict__ mcol, const double* __restrict__ mval, int32_t* __restrict__ cnt,
+    const int32_t* __restrict__ cptr, int32_t* __restrict__ ccol, double* __restrict__ cval,
+    int32_t* __restrict__ zeros) {
+    constexpr int kRows = kThreads / G;
+    constexpr int kVals = FILL ? S : 1;
+    __shared__ int32_t keys[kRows][S];
+    __shared__ double vals[kRows][kVals];
+    __shared__ uint16_t list[FILL ? kRows : 1][FILL ? S : 1];
+    __shared__ int32_t tl[G > 64 ? 3 : 1][G > 64 ? G : 1];  // a workgroup-wide group's exchange
+    __shared__ double tv[G > 64 ? G : 1];
+    const int g = threadIdx.x / G, t = threadIdx.x % G;
+    const bool mine = static_cast<int32_t>(blockIdx.x) * kRows + g < count;  // uniform over the group
+    const int32_t at = static_cast<int32_t>(blockIdx.x) * kRows + g;
+    const int32_t i = !mine ? 0 : rows ? rows[at] : at;
+    int32_t* const key = keys[g];
+    double* const val = FILL ? vals[g] : nullptr;
+    for (int k = t; k < S; k += G) {
+        key[k] = -1;
+        if constexpr (FILL) val[k] = 0.0;
+    }
+    group_sync<G>();
+    const int32_t pb = mine ? lptr[i] : 0, pe = mine ? lptr[i + 1] : 0;
+    for (int32_t p0 = pb; p0 < pe; p0 += G) {
+        // the next G entries of L, one per thread
+        const int32_t p = min(p0 + t, pe - 1);
+        const int32_t j = lcol[p];
+        const int32_t mb0 = mptr[j], me0 = mptr[j + 1];
+        const double lv0 = FILL ? lval[p] : 0.0;
+        if constexpr (G > 64) {
+            __syncthreads();
+            tl[0][t] = mb0;
+            tl[1][t] = me0;
+            tv[t] = lv0;
+            __syncthreads();
+        }
+        auto bounds = [&](int e, int32_t& b, int32_t& x, double& v) {
+            if constexpr (G > 64) {
+                b = tl[0][e];
+                x = tl[1][e];
+                v = tv[e];
+            } else {
+                b = __shfl(mb0, e, G);
+                x = __shfl(me0, e, G);
+                v = FILL ? __shfl(lv0, e, G) : 0.0;
+            }
+        };
+        const int32_t ne = min(pe - p0, G);
+        int32_t b, x, kn = 0;
+        double lv, vn = 0.0;
+        bounds(0, b, x, lv);
+        if (b + t < x) {
+            kn = mcol[b + t];
+            if constexpr (FILL) vn = mval[b + t];
+        }
+        for (int e = 0; e < ne; ++e) {
+            const int32_t bc = b, xc = x;
+            const double lc = lv;
+            int32_t k = kn;
+            double m = vn;
+            if (e + 1 < ne) {
+                bounds(e + 1, b, x, lv);
+                if (b + t < x) {
+                    kn = mcol[b + t];
+                    if constexpr (FILL) vn = mval[b + t];
+                }
+            }
+            for (int32_t q = bc + t; q < xc; q += G) {
+                if (q != bc + t) {
+                    k = mcol[q];
+                    if constexpr (FILL) m = mval[q];
+                }
+                unsigned int s = static_cast<unsigned int>(k) * 2654435769u >> (32 - __builtin_ctz(S));
+                for (;;) {  // ends: the table has a slot for every product
+                    const int32_t old = atomicCAS(&key[s], -1, k);
+                    if (old == -1 || old == k) break;
+                    s = (s + 1) & (S - 1);
+                }
+                if constexpr (FILL) val[s] = val[s] + lc * m;  // no other thread has column k in this step
+            }
+            group_sync<G>();
+        }
+    }
+    // entries of the row
+    int32_t u = 0;
+    if constexpr (G > 64) {
+        for (int k0 = 0; k0 < S; k0 += G) {
+            const bool in = key[k0 + t] >= 0;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+            if ((t & 63) == 0) tl[2][t / 64] = __popcll(m);
+            __syncthreads();
+            int32_t before = u;
+            for (int w = 0; w < t / 64; ++w) before += tl[2][w];
+            if constexpr (FILL)
+                if (in) list[g][before + __popcll(m & ((1ull << (t & 63)) - 1))] = static_cast<uint16_t>(k0 + t);
+            for (int w = 0; w < G / 64; ++w) u += tl[2][w];
+            __syncthreads();
+        }
+    } else {
+        const int sh = threadIdx.x & 63 & ~(G - 1);
+        const uint64_t gm = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
+        for (int k0 = 0; k0 < S; k0 += G) {
+            const bool in = key[k0 + t] >= 0;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in) >> sh & gm;
+            if constexpr (FILL)
+                if (in) list[g][u + __popcll(m & ((1ull << t) - 1))] = static_cast<uint16_t>(k0 + t);
+            u += __popcll(m);
+        }
+    }
+    if constexpr (!FILL) {
+        if (t == 0 && mine) cnt[i] = u;
+    } else {
+        group_sync<G>();
+        if (!mine) return;
+        const int32_t base = cptr[i];
+        bool zero = false;
+        for (int32_t r = t; r < u; r += G) {
+            const int s = list[g][r];
+            const int32_t k = key[s];
+            int32_t rank = 0;
+            for (int32_t q = 0; q < u; ++q) rank += key[list[g][q]] < k ? 1 : 0;
+            const double v = val[s];
+            ccol[base + rank] = k;
+            cval[base + rank] = v;
+            zero = zero || (v == 0.0 && k != i);
+        }
+        if (zero && zeros) *zeros = 1;
+    }
+}
+
+template <bool FILL, typename... Args>
+void launch_row_hash(const unsigned long long* rows, const ClassLists& lists, hipStream_t st, Args... args) {
+    auto go = [&](auto kernel, int cls) {
+        if (rows[cls] == 0) return;
+        const unsigned per = kThreads / kClassThreads[cls];
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rows[cls] + per - 1) / per)), dim3(kThreads), 0, st,
+                           static_cast<int32_t>(rows[cls]), static_cast<const int32_t*>(lists.rows[cls]), args...);
+    };
+    go(row_hash_kernel<kClassThreads[0], kClassSlots[0], FILL>, 0);
+    go(row_hash_kernel<kClassThreads[1], kClassSlots[1], FILL>, 1);
+    go(row_hash_kernel<kClassThreads[2], kClassSlots[2], FILL>, 2);
+    go(row_hash_kernel<kClassThreads[3], kClassSlots[3], FILL>, 3);
+    check(hipGetLastError(), "row products");
+}
+
+// C = L * M with the pattern of every structurally generated entry; false where the expanding form is
+// needed. zeros (device, set to 1 if an exact zero was written off the diagonal; null: not wanted).
+bool spgemm_rows(Pool& pool, const ConstCsr& L, const ConstCsr& M, int32_t* zeros, DevCsr& C, hipStream_t st) {
+    const int32_t n = L.nrows;
+    int32_t* nprod = pool.get<int32_t>(n);
+    auto* stats = pool.get<unsigned long long>(2 * kClasses + 2);
+    auto* used = reinterpret_cast<int32_t*>(stats + kClasses + 2);
+    check(vec_zero_bytes(stats, sizeof(unsigned long long) * (2 * kClasses + 2), st), "row products");
+    launch(row_products_kernel, n, st, n, L.ptr, L.col, M.ptr, nprod, stats);
+    check(hipGetLastError(), "row products");
+    unsigned long long rows[kClasses + 2];
+    check(hipMemcpyAsync(rows, stats, sizeof(rows), hipMemcpyDeviceToHost, st), "copy");
+    check(hipStreamSynchronize(st), "hipStreamSynchronize");
+    if (rows[kClasses] || rows[kClasses + 1] > INT32_MAX) return false;
+    C.nrows = n;
+    C.ncols = M.ncols;
+    C.ptr = pool.get<int32_t>(static_cast<int64_t>(n) + 1);
+    int32_t* cnt = pool.get<int32_t>(static_cast<int64_t>(n) + 1);
+    hipLaunchKernelGGL(set_int_kernel, dim3(1), dim3(1), 0, st, cnt + n, 0);
+    ClassLists lists;
+    bool listed = true;  // false: every row is of one class
+    for (int c = 0; c < kClasses; ++c) listed = listed && rows[c] != static_cast<unsigned long long>(n);
+    for (int c = 0; c < kClasses; ++c) lists.rows[c] = pool.get<int32_t>(listed ? static_cast<int64_t>(rows[c]) : 1);
+    if (listed)
+        launch(classify_rows_kernel, n, st, n, nprod, lists, used, cnt);
+    else
+        lists = ClassLists{};
+    launch_row_hash<false>(rows, lists, st, L.ptr, L.col, L.val, M.ptr, M.col, M.val, cnt,
+                           static_cast<const int32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+                           static_cast<double*>(nullptr), static_cast<int32_t*>(nullptr));
+    exclusive_scan_i32(pool, cnt, C.ptr, static_cast<int64_t>(n) + 1, st);
+    C.nnz = read_back(C.ptr + n, st);
+    C.col = pool.get<int32_t>(C.nnz);
+    C.val = pool.get<double>(C.nnz);
+    launch_row_hash<true>(rows, lists, st, L.ptr, L.col, L.val, M.ptr, M.col, M.val, static_cast<int32_t*>(nullptr),
+                          static_cast<const int32_t*>(C.ptr), C.col, C.val, zeros);
+    return true;
+}
+
 // Drops exact zeros off the diagonal; the result's arrays replace C's.
 DevCsr drop_zeros(Pool& pool, const DevCsr& C, hipStream_t st) {
     int32_t* crow = pool.get<int32_t>(C.nnz);
@@ -555,19 +848,6 @@ void validate_square(Pool& pool, int32_t n, int32_t nnz, const int32_t* ptr, con
     pool.put(bad);
 }
 
-template <typename T>
-void exclusive_scan_i32(Pool& pool, const T* in, int32_t* out, int64_t count, hipStream_t st) {
-    size_t tb = 0;
-    check(rocprim::exclusive_scan(nullptr, tb, in, out, int32_t{0}, static_cast<size_t>(count),
-                                  rocprim::plus<int32_t>(), st),
-          "scan size");
-    void* tmp = pool.get<unsigned char>(static_cast<int64_t>(tb));
-    check(rocprim::exclusive_scan(tmp, tb, in, out, int32_t{0}, static_cast<size_t>(count), rocprim::plus<int32_t>(),
-                                  st),
-          "scan");
-    pool.put(tmp);
-}
-
 }  // namespace
 
 extern "C" int amgg_strength_device(int device, int32_t n, const int32_t* rowptr, const int32_t* col,
@@ -669,7 +949,6 @@ extern "C" int amgg_galerkin_device(int device, int32_t n, int32_t nc, const int
             if (flags[0] || flags[1])
                 throw Failure{AMGG_EINVAL, std::string("amgg_galerkin_device: ") + (flags[0] ? "A" : "P") +
                                                " is not a CSR pattern of the stated size with ascending columns"};
-            pool.put(bad);
             // R = P^T, the exact transpose (rows in ascending fine index)
             DevCsr R;
             R.nrows = nc;
@@ -682,18 +961,20 @@ extern "C" int amgg_galerkin_device(int device, int32_t n, int32_t nc, const int
             check(transpose_csr(n, nc, p_nnz, p_rowptr, p_col, p_val, R.ptr, R.col, R.val, cursor, st), "transpose");
             const ConstCsr A{n, n, a_nnz, a_rowptr, a_col, a_val};
             const ConstCsr P{n, nc, p_nnz, p_rowptr, p_col, p_val};
-            DevCsr AP = spgemm(pool, A, P, budget, st);
-            pool.put(cursor);
+            const bool expand = chunk_products > 0;  // the caller bounds the expansion
+            int32_t* zeros = bad;                     // 0 again after the checks
+            DevCsr AP, G;
+            if (expand || !spgemm_rows(pool, A, P, nullptr, AP, st)) AP = spgemm(pool, A, P, budget, st);
             const ConstCsr Rc{R.nrows, R.ncols, R.nnz, R.ptr, R.col, R.val};
             const ConstCsr APc{AP.nrows, AP.ncols, AP.nnz, AP.ptr, AP.col, AP.val};
-            DevCsr G = spgemm(pool, Rc, APc, budget, st);
-            pool.put(AP.ptr);
-            pool.put(AP.col);
-            pool.put(AP.val);
-            pool.put(R.ptr);
-            pool.put(R.col);
-            pool.put(R.val);
-            DevCsr Ac = drop_zeros(pool, G, st);
+            DevCsr Ac;
+            if (!expand && spgemm_rows(pool, Rc, APc, zeros, G, st)) {
+                // an exact zero off the diagonal is rare: the pass that drops them runs only if there is one
+                Ac = read_back(zeros, st) ? drop_zeros(pool, G, st) : G;
+            } else {
+                G = spgemm(pool, Rc, APc, budget, st);
+                Ac = drop_zeros(pool, G, st);
+            }
             pool.keep(Ac.ptr);
             pool.keep(Ac.col);
             pool.keep(Ac.val);

@@ -46,15 +46,43 @@ __device__ __forceinline__ double block_sum(double v) {
     return s;
 }
 
-// Row i of t = Q ubar, and its terms of the coefficient gradient:
+// The sums of ncoef values per thread over the workgroup, out[m * stride] = sum of g[m], each as block_sum
+// forms it; the exchanges of all of them are in flight together (one after the other they took
+// longer than the rows of a small level).
+__device__ __forceinline__ void block_sums(const double (&g)[kMaxC], int ncoef, double* out, int64_t stride) {
+    __shared__ double red[kMaxC][kBlock / 64];
+    double v[kMaxC];
+#pragma unroll
+    for (int m = 0; m < kMaxC; ++m) v[m] = g[m];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+        for (int m = 0; m < kMaxC; ++m)
+            if (m < ncoef) v[m] += __shfl_xor(v[m], off, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+        for (int m = 0; m < kMaxC; ++m) red[m][threadIdx.x / 64] = v[m];
+    __syncthreads();
+    if (static_cast<int>(threadIdx.x) < ncoef) {
+        const double* r = red[threadIdx.x];
+        double s = r[0];
+        for (int k = 1; k < kBlock / 64; ++k) s += r[k];
+        out[threadIdx.x * stride] = s;
+    }
+}
+
+// Row i of t = Q ubar, added to fbar (or, with `first`, the start of it), and its terms of the coefficient
+// gradient:
 //   g[m]       += ubar_i r_i x_ii^m / a_ii                  m = 0..deg      (diagonal part)
 //   g[deg+m]   += ubar_i r_j x_ij^m / (a_ii + a_jj)   j != i, m = 1..deg      (off-diagonal part)
-template <typename T>
+template <typename T, int DEG>
 __device__ __forceinline__ void adj_smooth_row(int32_t i, const int32_t* __restrict__ ptr,
                                                const int32_t* __restrict__ col, const double* __restrict__ val,
                                                const double* __restrict__ diag, double s, const T* __restrict__ q,
                                                const T* __restrict__ ubar, const T* __restrict__ r,
-                                               T* __restrict__ t, int deg, double* g) {
+                                               T* __restrict__ t, T* __restrict__ fbar, bool first,
+                                               double (&g)[kMaxC]) {
+    const T fb = first ? T(0) : fbar[i];
     const double ui = static_cast<double>(ubar[i]);
     const double aii = diag[i];
     const int32_t pb = ptr[i], pe = ptr[i + 1];
@@ -88,41 +116,42 @@ __device__ __forceinline__ void adj_smooth_row(int32_t i, const int32_t* __restr
             const double x = av[e] / s;
             if (j == i) {
                 double w = ui * static_cast<double>(rj[e]) / aii;
-                for (int m = 0; m <= deg; ++m) {
+#pragma unroll
+                for (int m = 0; m <= DEG; ++m) {
                     g[m] += w;
                     w *= x;
                 }
             } else {
                 double w = ui * static_cast<double>(rj[e]) / (aii + dj[e]) * x;
-                for (int m = 1; m <= deg; ++m) {
-                    g[deg + m] += w;
+#pragma unroll
+                for (int m = 1; m <= DEG; ++m) {
+                    g[DEG + m] += w;
                     w *= x;
                 }
             }
         }
     }
     t[i] = acc;
+    fbar[i] = fb + acc;
 }
 
 // t = Q ubar and per-workgroup partial sums of the coefficient gradient (grid-stride rows).
-template <typename T>
+template <typename T, int DEG>
 __global__ __launch_bounds__(kBlock) void adj_smooth_kernel(int32_t n, const int32_t* __restrict__ ptr,
                                                            const int32_t* __restrict__ col,
                                                            const double* __restrict__ val,
                                                            const double* __restrict__ diag,
                                                            const double* __restrict__ scale,
                                                            const T* __restrict__ q, const T* __restrict__ ubar,
-                                                           const T* __restrict__ r, T* __restrict__ t, int deg,
+                                                           const T* __restrict__ r, T* __restrict__ t,
+                                                           T* __restrict__ fbar, bool first,
                                                            double* __restrict__ partial) {
     double g[kMaxC];
     for (int m = 0; m < kMaxC; ++m) g[m] = 0.0;
     const double s = scale[0];
     for (int32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += kReduceBlocks * kBlock)
-        adj_smooth_row<T>(i, ptr, col, val, diag, s, q, ubar, r, t, deg, g);
-    for (int m = 0; m <= 2 * deg; ++m) {
-        const double v = block_sum(g[m]);
-        if (threadIdx.x == 0) partial[m * kReduceBlocks + blockIdx.x] = v;
-    }
+        adj_smooth_row<T, DEG>(i, ptr, col, val, diag, s, q, ubar, r, t, fbar, first, g);
+    block_sums(g, 2 * DEG + 1, partial + blockIdx.x, kReduceBlocks);
 }
 
 __device__ __forceinline__ int32_t block_of_row(int32_t i, int32_t nblk, const int32_t* __restrict__ off) {
@@ -139,42 +168,39 @@ __device__ __forceinline__ int32_t block_of_row(int32_t i, int32_t nblk, const i
 
 // Block-diagonal level: workgroup c takes the rows of chunk c (all in one block, whose scale
 // it uses) and writes its partial sums to partial[m * nchunk + c].
-template <typename T>
+template <typename T, int DEG>
 __global__ __launch_bounds__(kBlock) void adj_smooth_blocks_kernel(
     int32_t nchunk, const int32_t* __restrict__ chunk_row, int32_t nblk, const int32_t* __restrict__ off,
     const double* __restrict__ scale, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
     const double* __restrict__ val, const double* __restrict__ diag, const T* __restrict__ q,
-    const T* __restrict__ ubar, const T* __restrict__ r, T* __restrict__ t, int deg, double* __restrict__ partial) {
+    const T* __restrict__ ubar, const T* __restrict__ r, T* __restrict__ t, T* __restrict__ fbar, bool first,
+    double* __restrict__ partial) {
     double g[kMaxC];
     for (int m = 0; m < kMaxC; ++m) g[m] = 0.0;
     const int32_t c = blockIdx.x;
     const int32_t r0 = chunk_row[c], r1 = chunk_row[c + 1];
     const double s = scale[block_of_row(r0, nblk, off)];
-    for (int32_t i = r0 + threadIdx.x; i < r1; i += kBlock) adj_smooth_row<T>(i, ptr, col, val, diag, s, q, ubar, r, t, deg, g);
-    for (int m = 0; m <= 2 * deg; ++m) {
-        const double v = block_sum(g[m]);
-        if (threadIdx.x == 0) partial[m * nchunk + c] = v;
-    }
+    for (int32_t i = r0 + threadIdx.x; i < r1; i += kBlock)
+        adj_smooth_row<T, DEG>(i, ptr, col, val, diag, s, q, ubar, r, t, fbar, first, g);
+    block_sums(g, 2 * DEG + 1, partial + c, nchunk);
 }
 
-// cbar[crow[b]][m] += sum of block b's chunk partials (in chunk order), one workgroup per block.
+// cbar[crow[b]][m] += sum of block b's chunk partials (in chunk order), one workgroup per block and m.
 // The first nkeep of each row's ncoef gradients are accumulated (the diagonal form of Eq. 5 keeps
 // d0..d_deg only: its off-diagonal coefficients are no parameters and keep a zero gradient).
 __global__ __launch_bounds__(kBlock) void adj_coeff_reduce_blocks_kernel(const double* __restrict__ partial,
-                                                                        int32_t nchunk, int ncoef, int nkeep,
+                                                                        int32_t nchunk, int ncoef,
                                                                         const int32_t* __restrict__ blk_chunk,
                                                                         const int32_t* __restrict__ crow,
                                                                         double* __restrict__ cbar) {
     const int32_t b = blockIdx.x;
     const int32_t row = crow[b];
     if (row < 0) return;  // uniform over the workgroup
-    const int32_t c0 = blk_chunk[b], c1 = blk_chunk[b + 1];
-    for (int m = 0; m < nkeep; ++m) {
-        double v = 0.0;
-        for (int32_t k = c0 + threadIdx.x; k < c1; k += kBlock) v += partial[m * nchunk + k];
-        v = block_sum(v);
-        if (threadIdx.x == 0) cbar[static_cast<int64_t>(row) * ncoef + m] += v;
-    }
+    const int32_t c0 = blk_chunk[b], c1 = blk_chunk[b + 1], m = blockIdx.y;
+    double v = 0.0;
+    for (int32_t k = c0 + threadIdx.x; k < c1; k += kBlock) v += partial[m * nchunk + k];
+    v = block_sum(v);
+    if (threadIdx.x == 0) cbar[static_cast<int64_t>(row) * ncoef + m] += v;
 }
 
 // Per-block dot products of a level's vectors: chunk partials, then one sum per block.
@@ -216,21 +242,19 @@ __global__ void scale_blocks_kernel(int32_t n, T* __restrict__ y, int32_t nblk, 
     if (i < n) y[i] = static_cast<T>(static_cast<double>(y[i]) * s[block_of_row(i, nblk, off)]);
 }
 
-__global__ __launch_bounds__(kBlock) void adj_coeff_reduce_kernel(const double* __restrict__ partial, int nkeep,
+__global__ __launch_bounds__(kBlock) void adj_coeff_reduce_kernel(const double* __restrict__ partial,
                                                                  double* __restrict__ cbar) {
     __shared__ double red[kBlock];
-    for (int m = 0; m < nkeep; ++m) {
-        double v = 0.0;
-        for (int k = threadIdx.x; k < kReduceBlocks; k += kBlock) v += partial[m * kReduceBlocks + k];
-        red[threadIdx.x] = v;
-        __syncthreads();
-        for (int w = kBlock / 2; w > 0; w >>= 1) {
-            if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) cbar[m] += red[0];
+    const int m = blockIdx.x;
+    double v = 0.0;
+    for (int k = threadIdx.x; k < kReduceBlocks; k += kBlock) v += partial[m * kReduceBlocks + k];
+    red[threadIdx.x] = v;
+    __syncthreads();
+    for (int w = kBlock / 2; w > 0; w >>= 1) {
+        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
+    if (threadIdx.x == 0) cbar[m] += red[0];
 }
 
 template <typename T>
@@ -309,36 +333,48 @@ struct Adj {
         return cur;
     }
 
-    // Reverse one smoothing step u' = u + Q (f - A u) whose input iterate is w (nullptr = 0).
+    // Reverse one smoothing step u' = u + Q (f - A u) whose input iterate is w (nullptr = 0). `first`: the
+    // level's fbar starts here.
+    template <typename T, int DEG>
+    void step_back_deg(Level& L, const T* r, bool first) {
+        T* ub = L.adj<T>(kAdjUbar);
+        T* tq = L.t<T>();
+        T* fb = L.adj<T>(kAdjFbar);
+        if (blocked) {
+            const int32_t nch = L.nchunk();
+            adj_smooth_blocks_kernel<T, DEG><<<nch, kBlock, 0, st>>>(nch, L.chunk_row, L.nblk, L.blk_off, L.blk_scale,
+                                                                     L.ptr, L.col, L.val, L.diag, L.qval<T>(), ub, r, tq,
+                                                                     fb, first, c->blk_partial);
+        } else {
+            adj_smooth_kernel<T, DEG><<<kReduceBlocks, kBlock, 0, st>>>(L.n, L.ptr, L.col, L.val, L.diag, L.scale,
+                                                                        L.qval<T>(), ub, r, tq, fb, first,
+                                                                        c->adj_partial);
+        }
+        ok(hipGetLastError());
+    }
     template <typename T>
-    void step_back(int l, const T* f, const T* w) {
+    void step_back(int l, const T* f, const T* w, bool first) {
         Level& L = c->lv[l];
         const T* r = f;
         if (w) {
             ok(csr_apply<T>(L.A(), L.aval<T>(), w, L.adj<T>(kAdjR), f, nullptr, nullptr, Epi::Resid, st));
             r = L.adj<T>(kAdjR);
         }
-        T* ub = L.adj<T>(kAdjUbar);
-        T* tq = L.t<T>();
-        if (blocked) {
-            const int32_t nch = L.nchunk();
-            adj_smooth_blocks_kernel<T><<<nch, kBlock, 0, st>>>(nch, L.chunk_row, L.nblk, L.blk_off, L.blk_scale, L.ptr,
-                                                                L.col, L.val, L.diag, L.qval<T>(), ub, r, tq, deg,
-                                                                c->blk_partial);
-            ok(hipGetLastError());
-            adj_coeff_reduce_blocks_kernel<<<L.nblk, kBlock, 0, st>>>(c->blk_partial, nch, 2 * deg + 1,
-                                                                      L.diag_form ? deg + 1 : 2 * deg + 1,
-                                                                      L.blk_chunk, L.blk_crow, cbar);
-        } else {
-            adj_smooth_kernel<T><<<kReduceBlocks, kBlock, 0, st>>>(L.n, L.ptr, L.col, L.val, L.diag, L.scale,
-                                                                    L.qval<T>(), ub, r, tq, deg, c->adj_partial);
-            ok(hipGetLastError());
-            adj_coeff_reduce_kernel<<<1, kBlock, 0, st>>>(c->adj_partial, L.diag_form ? deg + 1 : 2 * deg + 1,
-                                                          cbar + l * (2 * deg + 1));
+        static_assert(AMGG_MAX_DEGREE == 4, "one instance per degree");
+        switch (deg) {
+            case 1: step_back_deg<T, 1>(L, r, first); break;
+            case 2: step_back_deg<T, 2>(L, r, first); break;
+            case 3: step_back_deg<T, 3>(L, r, first); break;
+            default: step_back_deg<T, 4>(L, r, first); break;
         }
+        const unsigned keep = L.diag_form ? deg + 1 : 2 * deg + 1;
+        if (blocked)
+            adj_coeff_reduce_blocks_kernel<<<dim3(L.nblk, keep), kBlock, 0, st>>>(c->blk_partial, L.nchunk(), 2 * deg + 1,
+                                                                                  L.blk_chunk, L.blk_crow, cbar);
+        else
+            adj_coeff_reduce_kernel<<<keep, kBlock, 0, st>>>(c->adj_partial, cbar + l * (2 * deg + 1));
         ok(hipGetLastError());
-        axpy<T>(L.n, tq, L.adj<T>(kAdjFbar));
-        ok(csr_apply<T>(L.A(), L.aval<T>(), tq, ub, nullptr, nullptr, nullptr, Epi::Sub, st));
+        ok(csr_apply<T>(L.A(), L.aval<T>(), L.t<T>(), L.adj<T>(kAdjUbar), nullptr, nullptr, nullptr, Epi::Sub, st));
     }
 
     // Given ubar of level l's output (in adj(kAdjUbar)), leave ubar of its input there and the
@@ -352,8 +388,8 @@ struct Adj {
             ok(coarse_solve<T>(L, ub, fb, st));
             return;
         }
-        ok(vec_zero_bytes(fb, sizeof(T) * L.n, st));
-        for (int k = nu2; k >= 1; --k) step_back<T>(l, f, recompute<T>(L, f, L.adj<T>(kAdjUmid), k));
+        if (nu2 == 0) ok(vec_zero_bytes(fb, sizeof(T) * L.n, st));
+        for (int k = nu2; k >= 1; --k) step_back<T>(l, f, recompute<T>(L, f, L.adj<T>(kAdjUmid), k), k == nu2);
         Level& C = c->lv[l + 1];
         ok(csr_apply<T>(L.R(), L.rv<T>(), ub, C.adj<T>(kAdjUbar), nullptr, nullptr, nullptr, Epi::Store, st));
         level_back<T>(l + 1, C.f<T>(), nullptr);
@@ -361,24 +397,23 @@ struct Adj {
                         st));
         ok(csr_apply<T>(L.A(), L.aval<T>(), L.adj<T>(kAdjR), ub, nullptr, nullptr, nullptr, Epi::Sub, st));
         axpy<T>(L.n, L.adj<T>(kAdjR), fb);
-        for (int k = nu1; k >= 1; --k) step_back<T>(l, f, recompute<T>(L, f, entry, k));
+        for (int k = nu1; k >= 1; --k) step_back<T>(l, f, recompute<T>(L, f, entry, k), false);
     }
 
     // u_m from u_0 by m cycles; the level vectors of the m-th cycle are kept for the sweep.
-    // On return adj(kAdjUin) of level 0 holds u_{m-1}.
+    // On return adj(kAdjUin) of level 0 holds u_{m-1}, unless that is zero (m = 1 without u0): a cycle
+    // from zero takes its first step without a pass over A, and so does the sweep back through it.
     template <typename T>
     T* forward_to(int m, const T* f0, const T* u0) {
         Level& L0 = c->lv[0];
         T* uin = L0.adj<T>(kAdjUin);
-        if (u0)
-            ok(vec_copy<T>(L0.n, u0, uin, st));
-        else
-            ok(vec_zero_bytes(uin, sizeof(T) * L0.n, st));
+        if (u0) ok(vec_copy<T>(L0.n, u0, uin, st));
         T* res = nullptr;
         for (int i = 1; i <= m; ++i) {
+            const bool zero = i == 1 && !u0;
             if (i > 1) ok(vec_copy<T>(L0.n, res, uin, st));
-            ok(vec_copy<T>(L0.n, uin, L0.u<T>(), st));
-            ok(vcycle_level<T>(c, 0, f0, L0.u<T>(), L0.t<T>(), false, nu1, nu2, st, &res, i == m));
+            if (!zero) ok(vec_copy<T>(L0.n, uin, L0.u<T>(), st));
+            ok(vcycle_level<T>(c, 0, f0, L0.u<T>(), L0.t<T>(), zero, nu1, nu2, st, &res, i == m));
         }
         return res;
     }
@@ -419,7 +454,7 @@ struct Adj {
             // recompute cycle m (a later cycle overwrote its level vectors); the forward pass
             // does not touch ubar
             if (m < nvc) forward_to<T>(m, f0, u0);
-            level_back<T>(0, f0, L0.adj<T>(kAdjUin));
+            level_back<T>(0, f0, m == 1 && !u0 ? nullptr : L0.adj<T>(kAdjUin));
         }
     }
 };

@@ -42,7 +42,7 @@ HIP_SOURCES = {
     "gcin.hip": [],
     "galerkin.hip": ["-ffp-contract=off"],  # same rounding as the host Galerkin product
 }
-HOST_SOURCES = ["rs_setup.cpp", "errors.cpp", "halo.cpp"]
+HOST_SOURCES = ["rs_setup.cpp", "errors.cpp"]
 
 
 def _run(cmd):

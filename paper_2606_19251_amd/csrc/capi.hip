@@ -14,7 +14,6 @@
 #include "amggnn.h"
 #include "ctx.hpp"
 #include "errors.hpp"
-#include "halo.hpp"
 #include "kernels.hpp"
 
 using namespace amgg;
@@ -154,7 +153,7 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
     c->flags = b.take<int32_t>(8);
     c->cursor = b.take<int32_t>(max_nc + 1);
     c->pack_parts = b.take<int32_t>(kScanPartsMax + 1);
-    c->blkmax = b.take<int32_t>(6 * AMGG_MAX_LEVELS);
+    c->setup_out = b.take<int32_t>(kSetupOut);
     c->ra = b.take<double>(n0);
     c->rb = b.take<double>(n0);
     c->z = b.take<double>(n0);
@@ -441,45 +440,6 @@ extern "C" int amgg_workspace_bytes(const amgg_ctx* c, size_t* bytes) {
     });
 }
 
-// Halo lists of every smoothing level for the fused kernels, built on the host from a copy of
-// the level's pattern (setup only).
-static hipError_t build_halos(amgg_ctx* c, hipStream_t st) {
-    hipError_t e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
-    std::vector<int32_t> ptr, col;
-    HaloLists h;
-    auto up = [&](void* dst, const void* src, size_t bytes) {
-        if (e == hipSuccess && bytes > 0) e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
-    };
-    for (int l = 0; l + 1 < c->nlevels; ++l) {
-        Level& L = c->lv[l];
-        L.hrows = 0;
-        const int rows = L.n <= kFuseMaxRows ? stream_rows_for(L.n, L.nnz) : 0;
-        if (rows == 0 || L.hoff == nullptr) continue;
-        ptr.resize(static_cast<size_t>(L.n) + 1);
-        col.resize(static_cast<size_t>(L.nnz));
-        if ((e = hipMemcpy(ptr.data(), L.ptr, sizeof(int32_t) * ptr.size(), hipMemcpyDeviceToHost)) != hipSuccess ||
-            (e = hipMemcpy(col.data(), L.col, sizeof(int32_t) * col.size(), hipMemcpyDeviceToHost)) != hipSuccess)
-            return e;
-        if (!build_halo(L.n, ptr.data(), col.data(), rows, kHaloCap, kHaloEntCap, static_cast<size_t>(L.nnz), h))
-            continue;
-        up(L.hoff, h.hoff.data(), sizeof(int32_t) * h.hoff.size());
-        up(L.halo, h.halo.data(), sizeof(int32_t) * h.halo.size());
-        up(L.hend, h.hend.data(), sizeof(uint16_t) * h.hend.size());
-        up(L.heoff, h.heoff.data(), sizeof(int32_t) * h.heoff.size());
-        up(L.hent, h.hent.data(), sizeof(int32_t) * h.hent.size());
-        std::vector<int32_t> hc(h.hent.size());
-        for (size_t k = 0; k < hc.size(); ++k) hc[k] = col[h.hent[k]];
-        up(L.hcol, hc.data(), sizeof(int32_t) * hc.size());
-        up(L.hloc, h.loc.data(), sizeof(uint16_t) * h.loc.size());
-        if (e != hipSuccess) return e;
-        L.nhent = static_cast<int32_t>(h.hent.size());
-        if ((e = gather_values(L.nhent, L.hent, L.val, L.val32, L.ha64, L.ha32, st)) != hipSuccess) return e;
-        L.hrows = rows;
-    }
-    return hipSuccess;
-}
-
 extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t ws_bytes, void* stream) {
     return guarded([&]() -> int {
         if (!c) return fail(AMGG_EINVAL, "amgg_finalize: null context");
@@ -547,55 +507,69 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
             ok(dense_lu_inverse(Lc.n, Lc.dense, Lc.piv, Lc.inv, c->flags + 1, st));
         }
         if (e != hipSuccess) return hip_fail(e, "amgg_finalize (launch)");
-        // packed columns of every CSR-stream matrix (each call synchronises to read its far count)
+        ok(vec_zero_bytes(c->setup_out, sizeof(int32_t) * kSetupOut, st));
+        struct Stream {  // a CSR-stream matrix of a level
+            int32_t n, nz;
+            const int32_t *ptr, *col;
+            Level::Pack* pack;
+        };
+        auto streams = [](Level& L, bool coarsest) {
+            std::vector<Stream> s{{L.n, L.nnz, L.ptr, L.col, &L.pa}};
+            if (!coarsest) {
+                s.push_back({L.n, L.pnnz, L.pptr, L.pcol, &L.pp});
+                s.push_back({L.nc, L.pnnz, L.rptr, L.rcol, &L.pr});
+            }
+            return s;
+        };
+        auto halo_rows = [&](const Level& L, int l) {
+            return l + 1 < c->nlevels && L.n <= kFuseMaxRows ? stream_rows_for(L.n, L.nnz) : 0;
+        };
         for (int l = 0; l < c->nlevels && e == hipSuccess; ++l) {
             Level& L = c->lv[l];
-            auto pack = [&](Level::Pack& pk, int32_t rows_m, int32_t nz, const int32_t* ptr, const int32_t* col) {
-                if (pk.rows > 0 && e == hipSuccess)
-                    ok(pack_columns(rows_m, nz, ptr, col, pk.rows, pk.off, pk.base, pk.foff, pk.fslot, pk.fcol, pk.cap,
-                                    c->pack_parts, &pk.nfar, st));
-            };
-            pack(L.pa, L.n, L.nnz, L.ptr, L.col);
-            if (l + 1 < c->nlevels) {
-                pack(L.pp, L.n, L.pnnz, L.pptr, L.pcol);
-                pack(L.pr, L.nc, L.pnnz, L.rptr, L.rcol);
+            const bool pads = L.pad_a.cap > 0 && L.pad_p.cap > 0 && L.pad_r.cap > 0;
+            int k = 0;
+            for (const Stream& m : streams(L, l + 1 == c->nlevels)) {
+                int32_t* out = c->setup_out + 3 * l + k++;
+                if (m.pack->rows > 0)
+                    ok(pack_columns(m.n, m.nz, m.ptr, m.col, m.pack->rows, m.pack->off, m.pack->base, m.pack->foff,
+                                    m.pack->fslot, m.pack->fcol, m.pack->cap, c->pack_parts, out + kSetupFar, st));
+                // largest row block: sizes the kernels' LDS product buffers
+                ok(block_max_entries(m.n, m.ptr, stream_rows_for(m.n, m.nz), out, st));
+                if (pads) ok(block_max_entries(m.n, m.ptr, 1, out + kSetupLongest, st));
             }
+            L.hrows = 0;
+            if (halo_rows(L, l))
+                ok(halo_lists(L.n, L.nnz, L.ptr, L.col, L.val, L.val32, halo_rows(L, l),
+                              {L.hoff, L.halo, L.hend, L.heoff, L.hent, L.hcol, L.ha64, L.ha32, L.hloc},
+                              c->setup_out + kSetupHalo + 2 * l, st));
         }
-        if (e != hipSuccess) return hip_fail(e, "amgg_finalize (column packing)");
-        // largest row block of every CSR-stream matrix: sizes the kernels' LDS product buffers
-        ok(vec_zero_bytes(c->blkmax, sizeof(int32_t) * 6 * AMGG_MAX_LEVELS, st));
-        for (int l = 0; l < c->nlevels && e == hipSuccess; ++l) {
-            Level& L = c->lv[l];
-            int32_t* m = c->blkmax + 3 * l;
-            ok(block_max_entries(L.n, L.ptr, stream_rows_for(L.n, L.nnz), m, st));
-            if (l + 1 < c->nlevels) {
-                ok(block_max_entries(L.n, L.pptr, stream_rows_for(L.n, L.pnnz), m + 1, st));
-                ok(block_max_entries(L.nc, L.rptr, stream_rows_for(L.nc, L.pnnz), m + 2, st));
-            }
-            if (L.pad_a.cap > 0 && L.pad_p.cap > 0 && L.pad_r.cap > 0) {  // longest rows
-                int32_t* w = c->blkmax + 3 * (AMGG_MAX_LEVELS + l);
-                ok(block_max_entries(L.n, L.ptr, 1, w, st));
-                ok(block_max_entries(L.n, L.pptr, 1, w + 1, st));
-                ok(block_max_entries(L.nc, L.rptr, 1, w + 2, st));
-            }
-        }
-        if (e != hipSuccess) return hip_fail(e, "amgg_finalize (row blocks)");
-        if ((e = build_halos(c, st)) != hipSuccess) return hip_fail(e, "amgg_finalize (halo lists)");
+        if (e != hipSuccess) return hip_fail(e, "amgg_finalize (row blocks and lists)");
         int32_t flags[3] = {0, 0, 0};
-        std::vector<int32_t> bmax(6 * AMGG_MAX_LEVELS, 0);
+        std::vector<int32_t> got(kSetupOut, 0);
         if ((e = hipMemcpyAsync(flags, c->flags, sizeof(flags), hipMemcpyDeviceToHost, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(bmax.data(), c->blkmax, sizeof(int32_t) * bmax.size(), hipMemcpyDeviceToHost, st)) !=
+            (e = hipMemcpyAsync(got.data(), c->setup_out, sizeof(int32_t) * kSetupOut, hipMemcpyDeviceToHost, st)) !=
                 hipSuccess ||
             (e = hipStreamSynchronize(st)) != hipSuccess)
             return hip_fail(e, "amgg_finalize (sync)");
         for (int l = 0; l < c->nlevels; ++l) {
-            c->lv[l].acap = stream_cap_for(bmax[3 * l]);
-            c->lv[l].pcap = stream_cap_for(bmax[3 * l + 1]);
-            c->lv[l].rcap = stream_cap_for(bmax[3 * l + 2]);
+            Level& L = c->lv[l];
+            L.acap = stream_cap_for(got[3 * l]);
+            L.pcap = stream_cap_for(got[3 * l + 1]);
+            L.rcap = stream_cap_for(got[3 * l + 2]);
+            int k = 0;
+            for (const Stream& m : streams(L, l + 1 == c->nlevels)) {
+                const int32_t far = got[kSetupFar + 3 * l + k++];
+                m.pack->nfar = m.pack->rows > 0 && m.n > 0 && m.nz > 0 ? far : -1;
+            }
+            const int32_t* halo = got.data() + kSetupHalo + 2 * l;
+            if (halo_rows(L, l) && halo[0] == 0 && halo[1] <= L.nnz) {
+                L.hrows = halo_rows(L, l);
+                L.nhent = halo[1];
+            }
         }
         for (int l = 0; l + 1 < c->nlevels; ++l) {
             Level& L = c->lv[l];
-            const int32_t* longest = bmax.data() + 3 * (AMGG_MAX_LEVELS + l);
+            const int32_t* longest = got.data() + kSetupLongest + 3 * l;
             Level::Pad* pads[3] = {&L.pad_a, &L.pad_p, &L.pad_r};
             int w[3];
             bool fit = true;

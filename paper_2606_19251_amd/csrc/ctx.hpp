@@ -159,6 +159,13 @@ enum AdjVec : int {
     kAdjVecs = 7
 };
 
+// Places in setup_out, 3 values per level (A, P, R): largest row block (first), longest row and far entries of
+// the packing; then the two results of halo_lists per level.
+constexpr int kSetupLongest = 3 * AMGG_MAX_LEVELS;
+constexpr int kSetupFar = 6 * AMGG_MAX_LEVELS;
+constexpr int kSetupHalo = 9 * AMGG_MAX_LEVELS;
+constexpr int kSetupOut = 11 * AMGG_MAX_LEVELS;
+
 }  // namespace amgg
 
 struct amgg_ctx {
@@ -184,7 +191,7 @@ struct amgg_ctx {
     int32_t* flags = nullptr;
     int32_t* cursor = nullptr;
     int32_t* pack_parts = nullptr;  // scan scratch of the column packing
-    int32_t* blkmax = nullptr;      // largest row block of A, P and R per level (3 x AMGG_MAX_LEVELS)
+    int32_t* setup_out = nullptr;  // what finalize reads back (see kSetupOut)
     double *ra = nullptr, *rb = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *bproj = nullptr;
     double* adj_partial = nullptr;
     double* adj_scal = nullptr;

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kScanBlock) void scan_apply_kernel(int32_t m, int32
     __shared__ int32_t lds[kScanBlock / 64];
     const int64_t lo = 1 + static_cast<int64_t>(blockIdx.x) * piece;
     const int64_t hi = min(lo + piece, static_cast<int64_t>(m) + 1);
-    int32_t carry = parts[blockIdx.x];
+    int32_t carry = parts ? parts[blockIdx.x] : 0;
     for (int64_t base = lo; base < hi; base += kScanBlock) {
         const int64_t k = base + threadIdx.x;
         const int32_t v = k < hi ? a[k] : 0;
@@ -382,6 +382,176 @@ __global__ __launch_bounds__(kBlock) void block_dense_gemv_kernel(int32_t n, int
     if (row < n && lane == 0) y[row] = static_cast<T>(s);
 }
 
+// a[1..m] becomes its inclusive scan; parts: scratch of at least min(m, kScanParts) ints. A few thousand
+// values are one workgroup's work: three launches cost more than its few rounds.
+void inclusive_scan(int32_t m, int32_t* a, int32_t* parts, hipStream_t stream) {
+    if (m <= 4 * kScanBlock) {
+        scan_apply_kernel<<<1, kScanBlock, 0, stream>>>(m, m, a, nullptr);
+        return;
+    }
+    const int32_t nparts = static_cast<int32_t>(
+        std::min<int64_t>(kScanParts, (static_cast<int64_t>(m) + kScanBlock - 1) / kScanBlock));
+    const int32_t piece = static_cast<int32_t>((static_cast<int64_t>(m) + nparts - 1) / nparts);
+    scan_reduce_kernel<<<nparts, kScanBlock, 0, stream>>>(m, piece, a, parts);
+    scan_parts_kernel<<<1, kScanBlock, 0, stream>>>(nparts, parts);
+    scan_apply_kernel<<<nparts, kScanBlock, 0, stream>>>(m, piece, a, parts);
+}
+
+// --- halo lists of the fused smoothing kernels -------------------------------------------
+// One workgroup per block of `rows` rows. Its distinct outside columns go through a hash table in LDS and
+// are sorted there; then every entry finds its slot by bisection and groups of 8 lanes copy the halo
+// rows' entries. Without FILL: the block's halo rows and halo entries into hoff[b + 1] and heoff[b + 1], and
+// out[0] is set if it has more than kHaloCap rows or kHaloEntCap entries; with FILL the lists
+// themselves at the scanned offsets. Forming the list twice is cheaper than keeping it: both passes of
+// a level read its pattern from cache. (101k-row triangulation, its levels of 37k rows and less:
+// 6.15 ms with copies to the host, sorting there and copies back, 0.15 ms here.)
+constexpr int kHaloSlots = 2 * kHaloCap;  // at most kHaloCap + kBlock columns enter the table
+static_assert(kHaloCap + kBlock <= kHaloSlots, "an insertion always finds a free slot");
+
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void halo_kernel(int32_t n, int32_t nnz, int rows, const int32_t* __restrict__ ptr,
+                                                     const int32_t* __restrict__ col, const double* __restrict__ val,
+                                                     const float* __restrict__ val32, HaloOut h,
+                                                     int32_t* __restrict__ out) {
+    __shared__ int32_t table[kHaloSlots], list[kHaloCap], end[kHaloCap], wsum[kBlock / 64], count, bad;
+    const int32_t b = blockIdx.x, tid = threadIdx.x;
+    const int32_t r0 = b * rows, r1 = min(r0 + rows, n);
+    const int32_t e0 = ptr[r0], e1 = ptr[r1];
+    if (FILL && (out[0] != 0 || out[1] > nnz)) return;  // the level has no lists
+    for (int i = tid; i < kHaloSlots; i += kBlock) table[i] = -1;
+    for (int i = tid; i < kHaloCap; i += kBlock) list[i] = INT32_MAX;
+    if (tid == 0) count = bad = 0;
+    __syncthreads();
+    for (int32_t k = e0 + tid; k < e1; k += kBlock) {
+        const int32_t j = col[k];
+        if (j >= r0 && j < r1) continue;
+        if (j < 0 || j >= n) {
+            bad = 1;
+            continue;
+        }
+        if (__hip_atomic_load(&count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > kHaloCap) break;
+        for (uint32_t s = static_cast<uint32_t>(j) * 2654435761u >> 8;; ++s) {
+            const int32_t was = atomicCAS(&table[s % kHaloSlots], -1, j);
+            if (was == j) break;
+            if (was == -1) {
+                const int32_t at = atomicAdd(&count, 1);
+                if (at < kHaloCap) list[at] = j;
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    const int32_t m = count;
+    if (m > kHaloCap || bad) {
+        if (tid == 0) {
+            out[0] = 1;
+            if (!FILL) h.hoff[b + 1] = h.heoff[b + 1] = 0;
+        }
+        return;
+    }
+    int32_t span = 2;
+    while (span < m) span *= 2;
+    for (int32_t size = 2; size <= span; size *= 2)  // bitonic
+        for (int32_t step = size / 2; step > 0; step /= 2) {
+            for (int32_t i = tid; i < span / 2; i += kBlock) {
+                const int32_t lo = 2 * i - (i & (step - 1)), hi = lo + step;
+                const int32_t x = list[lo], y = list[hi];
+                if ((x > y) == ((lo & size) == 0)) {
+                    list[lo] = y;
+                    list[hi] = x;
+                }
+            }
+            __syncthreads();
+        }
+    // ends of the halo rows' entries: every thread its four rows, the threads by a scan
+    constexpr int kPer = kHaloCap / kBlock;
+    int32_t len[kPer], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int32_t i = tid * kPer + q;
+        len[q] = i < m ? ptr[list[i] + 1] - ptr[list[i]] : 0;
+        sum += len[q];
+    }
+    int32_t incl = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t t = __shfl_up(incl, o, 64);
+        if ((tid & 63) >= o) incl += t;
+    }
+    if ((tid & 63) == 63) wsum[tid / 64] = incl;
+    __syncthreads();
+    for (int w = 0; w < tid / 64; ++w) incl += wsum[w];
+    int32_t at = incl - sum;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        at += len[q];
+        end[tid * kPer + q] = at;
+    }
+    __syncthreads();
+    const int32_t ents = end[kHaloCap - 1];
+    if constexpr (!FILL) {
+        if (tid == 0) {
+            if (ents > kHaloEntCap) out[0] = 1;
+            h.hoff[b + 1] = m;
+            h.heoff[b + 1] = ents > kHaloEntCap ? 0 : ents;
+            if (b == 0) h.hoff[0] = h.heoff[0] = 0;
+        }
+    } else {
+        const int32_t o = h.hoff[b], eo = h.heoff[b];
+        for (int32_t i = tid; i < m; i += kBlock) {
+            h.halo[o + i] = list[i];
+            h.hend[o + i] = static_cast<uint16_t>(end[i]);
+        }
+        for (int32_t k = e0 + tid; k < e1; k += kBlock) {
+            const int32_t j = col[k];
+            int32_t slot = j - r0;
+            if (j < r0 || j >= r1) {
+                int32_t lo = 0, hi = m;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) / 2;
+                    if (list[mid] < j)
+                        lo = mid + 1;
+                    else
+                        hi = mid;
+                }
+                slot = rows + lo;
+            }
+            h.hloc[k] = static_cast<uint16_t>(slot);
+        }
+        for (int32_t i = tid / 8; i < m; i += kBlock / 8) {
+            const int32_t first = ptr[list[i]], dst = eo + (i > 0 ? end[i - 1] : 0), cnt = ptr[list[i] + 1] - first;
+            for (int32_t q = tid % 8; q < cnt; q += 8) {
+                h.hent[dst + q] = first + q;
+                h.hcol[dst + q] = col[first + q];
+                h.ha64[dst + q] = val[first + q];
+                h.ha32[dst + q] = val32[first + q];
+            }
+        }
+    }
+}
+
+// Inclusive scans of hoff[1..nb] and heoff[1..nb]; *total receives the latter's last value. (65536 rows
+// of at most kHaloEntCap entries each stay below 2^31.)
+static_assert(static_cast<int64_t>(kFuseMaxRows) * kHaloEntCap < INT32_MAX, "the totals fit");
+__global__ __launch_bounds__(kScanBlock) void halo_scan_kernel(int32_t nb, int32_t* __restrict__ hoff,
+                                                              int32_t* __restrict__ heoff,
+                                                              int32_t* __restrict__ total) {
+    __shared__ int32_t lds[kScanBlock / 64];
+    int32_t c0 = 0, c1 = 0;
+    for (int32_t base = 1; base <= nb; base += kScanBlock) {
+        const int32_t k = base + threadIdx.x;
+        int32_t t0, t1;
+        const int32_t s0 = block_inclusive_scan(k <= nb ? hoff[k] : 0, lds, &t0);
+        const int32_t s1 = block_inclusive_scan(k <= nb ? heoff[k] : 0, lds, &t1);
+        if (k <= nb) {
+            hoff[k] = c0 + s0;
+            heoff[k] = c1 + s1;
+        }
+        c0 += t0;
+        c1 += t1;
+    }
+    if (threadIdx.x == 0) *total = c1;
+}
+
 }  // namespace
 
 hipError_t extract_diag(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* diag,
@@ -429,18 +599,23 @@ __global__ __launch_bounds__(kBlock) void pack_count_kernel(int32_t nrows, int r
     if (threadIdx.x == 0) {
         base[b] = bs;
         cnt[b + 1] = ne <= kStreamCap ? nfar : 0;
+        if (b == 0) cnt[0] = 0;
     }
 }
 
-// Far entries of each block at foff[b]..: entry index within the block and full column. Their
-// order within a block is immaterial (each one is written to its own product slot).
+// Far entries of each block at foff[b]..: entry index within the block and full column, unless there are
+// more than cap of them (total receives their number). Their order within a block is immaterial (each
+// one is written to its own product slot).
 __global__ __launch_bounds__(kBlock) void pack_far_kernel(int32_t nrows, int rows, const int32_t* __restrict__ ptr,
                                                          const int32_t* __restrict__ col,
                                                          const uint16_t* __restrict__ off,
                                                          const int32_t* __restrict__ foff,
-                                                         uint16_t* __restrict__ fslot, int32_t* __restrict__ fcol) {
+                                                         uint16_t* __restrict__ fslot, int32_t* __restrict__ fcol,
+                                                         int64_t cap, int32_t* __restrict__ total) {
     __shared__ int32_t pos;
     const int32_t b = blockIdx.x;
+    if (b == 0 && threadIdx.x == 0) *total = foff[gridDim.x];
+    if (foff[gridDim.x] > cap) return;
     const int32_t r0 = b * rows, r1 = min(r0 + rows, nrows);
     const int32_t e0 = ptr[r0], ne = ptr[r1] - e0;
     if (ne > kStreamCap || foff[b + 1] == foff[b]) return;  // uniform over the workgroup
@@ -457,28 +632,22 @@ __global__ __launch_bounds__(kBlock) void pack_far_kernel(int32_t nrows, int row
 
 hipError_t pack_columns(int32_t nrows, int32_t nnz, const int32_t* ptr, const int32_t* col, int rows, uint16_t* off,
                         int32_t* base, int32_t* foff, uint16_t* fslot, int32_t* fcol, int64_t cap, int32_t* parts,
-                        int64_t* nfar, hipStream_t stream) {
-    *nfar = -1;
+                        int32_t* nfar, hipStream_t stream) {
     if (nrows <= 0 || nnz <= 0 || rows <= 0) return hipSuccess;
     const int32_t nb = (nrows + rows - 1) / rows;
-    hipError_t e = vec_zero_bytes(foff, sizeof(int32_t), stream);
-    if (e != hipSuccess) return e;
     pack_count_kernel<<<nb, kBlock, 0, stream>>>(nrows, rows, ptr, col, off, base, foff);
-    // in-place inclusive scan of the counts foff[1..nb]: foff[b] = far entries before block b
-    const int32_t nparts = static_cast<int32_t>(
-        std::min<int64_t>(kScanParts, (static_cast<int64_t>(nb) + kScanBlock - 1) / kScanBlock));
-    const int32_t piece = static_cast<int32_t>((static_cast<int64_t>(nb) + nparts - 1) / nparts);
-    scan_reduce_kernel<<<nparts, kScanBlock, 0, stream>>>(nb, piece, foff, parts);
-    scan_parts_kernel<<<1, kScanBlock, 0, stream>>>(nparts, parts);
-    scan_apply_kernel<<<nparts, kScanBlock, 0, stream>>>(nb, piece, foff, parts);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    int32_t total = 0;
-    if ((e = hipMemcpyAsync(&total, foff + nb, sizeof(int32_t), hipMemcpyDeviceToHost, stream)) != hipSuccess ||
-        (e = hipStreamSynchronize(stream)) != hipSuccess)
-        return e;
-    *nfar = total;
-    if (total > cap || total == 0) return hipSuccess;  // over capacity: the plain columns stay in use
-    pack_far_kernel<<<nb, kBlock, 0, stream>>>(nrows, rows, ptr, col, off, foff, fslot, fcol);
+    inclusive_scan(nb, foff, parts, stream);  // foff[b] = far entries before block b
+    pack_far_kernel<<<nb, kBlock, 0, stream>>>(nrows, rows, ptr, col, off, foff, fslot, fcol, cap, nfar);
+    return hipGetLastError();
+}
+
+hipError_t halo_lists(int32_t n, int32_t nnz, const int32_t* ptr, const int32_t* col, const double* val,
+                      const float* val32, int rows, const HaloOut& h, int32_t* out, hipStream_t stream) {
+    if (n <= 0 || rows <= 0) return hipErrorInvalidValue;
+    const int32_t nb = (n + rows - 1) / rows;
+    halo_kernel<false><<<nb, kBlock, 0, stream>>>(n, nnz, rows, ptr, col, val, val32, h, out);
+    halo_scan_kernel<<<1, kScanBlock, 0, stream>>>(nb, h.hoff, h.heoff, out + 1);
+    halo_kernel<true><<<nb, kBlock, 0, stream>>>(n, nnz, rows, ptr, col, val, val32, h, out);
     return hipGetLastError();
 }
 
@@ -488,12 +657,7 @@ hipError_t transpose_csr(int32_t nf, int32_t nc, int32_t nnz, const int32_t* p_p
     hipError_t e = vec_zero_bytes(r_ptr, sizeof(int32_t) * (nc + 1), stream);
     if (e != hipSuccess) return e;
     if (nnz > 0) count_cols_kernel<<<grid_for(nnz), kBlock, 0, stream>>>(nnz, p_col, r_ptr);
-    // piece sums live in `cursor`, which is free until the scatter below
-    const int32_t nparts = static_cast<int32_t>(std::min<int64_t>(kScanParts, (static_cast<int64_t>(nc) + kScanBlock - 1) / kScanBlock));
-    const int32_t piece = static_cast<int32_t>((static_cast<int64_t>(nc) + nparts - 1) / nparts);
-    scan_reduce_kernel<<<nparts, kScanBlock, 0, stream>>>(nc, piece, r_ptr, cursor);
-    scan_parts_kernel<<<1, kScanBlock, 0, stream>>>(nparts, cursor);
-    scan_apply_kernel<<<nparts, kScanBlock, 0, stream>>>(nc, piece, r_ptr, cursor);
+    inclusive_scan(nc, r_ptr, cursor, stream);  // piece sums live in `cursor`, which is free until the scatter below
     if ((e = vec_copy<int32_t>(nc, r_ptr, cursor, stream)) != hipSuccess) return e;
     scatter_transpose_kernel<<<grid_for(nf), kBlock, 0, stream>>>(nf, p_ptr, p_col, p_val, cursor, r_col, r_val);
     sort_rows_kernel<<<grid_for(nc), kBlock, 0, stream>>>(nc, r_ptr, r_col, r_val);

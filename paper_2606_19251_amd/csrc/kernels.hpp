@@ -117,13 +117,13 @@ hipError_t block_max_entries(int32_t nrows, const int32_t* ptr, int rows, int32_
 
 // Pack the columns of an nrows-row CSR matrix for row blocks of `rows` rows (a value of
 // stream_rows_for): off [nnz], base [blocks], foff [blocks + 1], and at most `cap` far entries
-// in fslot / fcol. `parts` is scratch of at least kScanParts + 1 ints. Synchronises the stream;
-// *nfar receives the number of far entries (the packing is unusable when it exceeds cap).
+// in fslot / fcol. `parts` is scratch of at least kScanParts + 1 ints. *nfar (on the device) receives the
+// number of far entries (the packing is unusable when it exceeds cap).
 // Blocks whose entries exceed the stream kernels' product buffer record no far entries (their
 // rows are summed from the plain columns).
 hipError_t pack_columns(int32_t nrows, int32_t nnz, const int32_t* ptr, const int32_t* col, int rows, uint16_t* off,
                         int32_t* base, int32_t* foff, uint16_t* fslot, int32_t* fcol, int64_t cap, int32_t* parts,
-                        int64_t* nfar, hipStream_t stream);
+                        int32_t* nfar, hipStream_t stream);
 constexpr int64_t kScanPartsMax = 1024;  // scratch of pack_columns: kScanPartsMax + 1 ints
 // Which matrices read packed columns by default. Those of at least 2^24 entries (128 MB of FP32 values and
 // plain columns) stream from HBM: there the packing pays however many far entries it has (8M-cell
@@ -148,12 +148,33 @@ int stream_rows_for(int32_t nrows, int32_t nnz);
 
 // Fused smoothing steps on a level (Q values on A's pattern). Rows are grouped in blocks of
 // h.rows consecutive rows (= stream_rows_for(A)); each block has at most kHaloCap halo rows
-// with at most kHaloEntCap stored entries between them (lists built on the host, halo.hpp).
+// with at most kHaloEntCap stored entries between them (halo_lists).
 // Levels with more rows than this stay with separate passes: there the halo rows' extra
 // traffic (about 0.4-0.9 of the block's own entries) costs more than the saved launch.
 constexpr int32_t kFuseMaxRows = 65536;
 constexpr int kHaloCap = 1024;
 constexpr int kHaloEntCap = 3072;  // <= the kernels' LDS product buffer (4096)
+// The lists, over blocks of `rows` consecutive rows:
+//   hoff[b]..hoff[b+1]   the block's halo rows in `halo` (distinct columns outside the block,
+//                        ascending);
+//   hloc[k]              block-local slot of col[k] (own row j -> j - r0, halo row i -> rows + i);
+//   heoff[b]..heoff[b+1] the block's halo entries: the stored entries of its halo rows, row after
+//                        row, as entry index (hent), column (hcol) and values (ha64, ha32);
+//   hend[i]              end of halo row i's entries, relative to heoff[b] (its start is the
+//                        previous row's end, 0 for the block's first halo row).
+struct HaloOut {
+    int32_t *hoff, *halo;
+    uint16_t* hend;
+    int32_t *heoff, *hent, *hcol;
+    double* ha64;
+    float* ha32;
+    uint16_t* hloc;
+};
+// Builds them: halo, hend and the entry arrays hold nnz items each. out[0] (0 before) becomes nonzero where a
+// block has more than kHaloCap halo rows or kHaloEntCap halo entries, out[1] the halo entries of
+// all blocks; there are no lists if out[0] is set or out[1] exceeds nnz.
+hipError_t halo_lists(int32_t n, int32_t nnz, const int32_t* ptr, const int32_t* col, const double* val,
+                      const float* val32, int rows, const HaloOut& h, int32_t* out, hipStream_t stream);
 struct HaloView {
     int rows;
     const int32_t* hoff;   // [blocks + 1] into halo / hend

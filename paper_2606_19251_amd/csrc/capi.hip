@@ -126,12 +126,12 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
             const size_t dz = static_cast<size_t>(L.dense_off_h.back());
             L.dense = b.take<double>(dz);
             L.inv = b.take<double>(dz);
-            L.piv = b.take<int32_t>(n);
+            L.piv = b.take<int32_t>(2 * n);
             L.dense_off = b.take<int64_t>(L.nblk + 1);
         } else {
             L.dense = b.take<double>(n * n);
             L.inv = b.take<double>(n * n);
-            L.piv = b.take<int32_t>(n);
+            L.piv = b.take<int32_t>(2 * n);
         }
         if (L.nblk > 0) {
             L.blk_off = b.take<int32_t>(L.nblk + 1);
@@ -500,7 +500,7 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
                 const int32_t o = Lc.blk_off_h[b], nb = Lc.blk_off_h[b + 1] - o;
                 double* M = Lc.dense + Lc.dense_off_h[b];
                 ok(dense_from_csr(nb, Lc.ptr + o, Lc.col, Lc.val, M, Lc.blk_sing_h[b], st, o));
-                ok(dense_lu_inverse(nb, M, Lc.piv + o, Lc.inv + Lc.dense_off_h[b], c->flags + 1, st));
+                ok(dense_lu_inverse(nb, M, Lc.piv + 2 * o, Lc.inv + Lc.dense_off_h[b], c->flags + 1, st));
             }
         } else {
             ok(dense_from_csr(Lc.n, Lc.ptr, Lc.col, Lc.val, Lc.dense, c->singular, st));

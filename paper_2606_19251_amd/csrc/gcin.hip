@@ -94,93 +94,6 @@ __device__ __forceinline__ float normrelu(float y, float mu, float rs, float ga,
     return fmaxf((y - mu) * rs * ga + be, 0.0f);
 }
 
-// Aggregation over the stored entries of a lane group's rows [r0, r1) of the batched graph (W
-// lanes, one per channel, share the row index; r1 - r0 < W). The group's row bounds are loaded
-// once, one per lane, and read across lanes at each row change, so that the walk over the rows
-// has no dependent global load. Entries are visited in stored order, a batch at a time: the
-// batch's column indices and weights are spread over the group's lanes (lane l holds entry l),
-// its gathers load(j) are issued together while the next batch's indices load, and use(w, v)
-// is then applied in entry order, each entry's index and weight read across lanes; done(row) is
-// called once per row after its last entry (rows without entries included). A 64-lane group
-// owns its wavefront, so the indices it reads are uniform (scalar registers) and it takes 32
-// entries per batch; a 32-lane group (two per wavefront, on different rows) takes kAggBatch.
-constexpr int kAggBatch = 16;
-
-template <int W, typename V, class Load, class Use, class Done>
-__device__ __forceinline__ void visit_rows(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
-                                           const float* __restrict__ w, int32_t r0, int32_t r1, Load load, Use use,
-                                           Done done) {
-    static_assert(W == 64 || W == 32, "lane groups of 64 or 32");
-    const int32_t rp = ptr[r0 + min(static_cast<int32_t>(threadIdx.x % W), r1 - r0)];
-    auto bound = [&](int32_t i) {  // ptr[r0 + i], i <= r1 - r0
-        const int32_t v = __shfl(rp, i, W);
-        if constexpr (W == 64) return __builtin_amdgcn_readfirstlane(v);
-        return v;
-    };
-    const int32_t kend = bound(r1 - r0);
-    int32_t r = r0;
-    int32_t rnext = bound(1);
-    const int32_t kbeg = bound(0);
-    auto walk = [&](int32_t k, int q, float wq, const V& v) {
-        if (k + q < kend) {
-            while (k + q >= rnext) {
-                done(r);
-                ++r;
-                rnext = bound(r + 1 - r0);
-            }
-            use(wq, v);
-        }
-    };
-    if constexpr (W == 64) {
-        constexpr int B = 2 * kAggBatch;  // 32 gathers in flight per wavefront
-        const int32_t l = static_cast<int32_t>(threadIdx.x % 64) % B;
-        int32_t cl = 0;
-        float wl = 0.0f;
-        if (kbeg < kend) {
-            const int32_t kk = min(kbeg + l, kend - 1);
-            cl = col[kk];
-            wl = w[kk];
-        }
-        for (int32_t k = kbeg; k < kend; k += B) {
-            V vj[B];
-#pragma unroll
-            for (int q = 0; q < B; ++q) vj[q] = load(__builtin_amdgcn_readlane(cl, q));
-            const float wcur = wl;
-            if (k + B < kend) {
-                const int32_t kk = min(k + B + l, kend - 1);
-                cl = col[kk];
-                wl = w[kk];
-            }
-#pragma unroll
-            for (int q = 0; q < B; ++q)
-                walk(k, q, __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wcur), q)), vj[q]);
-        }
-    } else {
-        const int32_t l = static_cast<int32_t>(threadIdx.x % W) % kAggBatch;
-        int32_t cl = 0;
-        float wl = 0.0f;
-        if (kbeg < kend) {
-            const int32_t kk = min(kbeg + l, kend - 1);
-            cl = col[kk];
-            wl = w[kk];
-        }
-        for (int32_t k = kbeg; k < kend; k += kAggBatch) {
-            V vj[kAggBatch];
-#pragma unroll
-            for (int q = 0; q < kAggBatch; ++q) vj[q] = load(__shfl(cl, q, W));
-            const float wcur = wl;
-            if (k + kAggBatch < kend) {
-                const int32_t kk = min(k + kAggBatch + l, kend - 1);
-                cl = col[kk];
-                wl = w[kk];
-            }
-#pragma unroll
-            for (int q = 0; q < kAggBatch; ++q) walk(k, q, __shfl(wcur, q, W), vj[q]);
-        }
-    }
-    for (; r < r1; ++r) done(r);
-}
-
 // f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>): an unrolled loop whose index is a
 // constant expression (the DPP controls below have to be).
 template <int... I, class F>
@@ -281,10 +194,10 @@ __device__ __forceinline__ float group_bcast(float v) {
     return __builtin_bit_cast(float, group_bcast<Q, G>(__builtin_bit_cast(int, v)));
 }
 
-// The same walk with 16-byte gathers: group q of G = HD / 4 lanes (of the HD lanes that own rows
+// Aggregation over the stored entries of rows of the batched graph with 16-byte gathers: group q of G = HD / 4 lanes (of the HD lanes that own rows
 // [r0, r0 + 16)) owns the rows [r0 + 4 q, r0 + 4 q + 4) and lane p of the group holds channels
 // 4 p .. 4 p + 3, so that one load instruction brings 64 / G neighbour rows. Each row's entries are
-// visited in stored order, so every channel's sum is the one visit_rows forms. A group's lanes hold
+// visited in stored order. A group's lanes hold
 // its next G entries (column, weight, row); eight gathers are in flight at a time, and the next
 // entries load meanwhile. What is bound here is instructions and latency, not bytes, so the steps are
 // straight-line code: entries are broadcast by DPP, a slot past the group's end has weight 0 and ends
@@ -653,26 +566,6 @@ __device__ __forceinline__ void stage_bf16(const float* __restrict__ M, bool tra
             Bt[c][k] = f2bf(M[e]);
         else
             Bt[k][c] = f2bf(M[e]);
-    }
-}
-
-// y of rows r0 .. r0 + 15 in channel c (0 past the graph's end): read from Y, or formed from H0
-// for layer 0; the 16 loads are issued together.
-template <int HD, bool Y0>
-__device__ __forceinline__ void load_rows(float (&yv)[16], int32_t r0, int32_t end, int c, const float* __restrict__ Y,
-                                          const float* __restrict__ H0, const float* __restrict__ W0,
-                                          const float* __restrict__ b0) {
-    if constexpr (Y0) {
-        const float w0 = W0[c], w1 = W0[HD + c], bb = b0[c];
-        float2 hv[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            hv[r] = r0 + r < end ? reinterpret_cast<const float2*>(H0)[r0 + r] : make_float2(0.0f, 0.0f);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? y0_of(hv[r], w0, w1, bb) : 0.0f;
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? Y[static_cast<int64_t>(r0 + r) * HD + c] : 0.0f;
     }
 }
 
@@ -1045,7 +938,9 @@ __global__ __launch_bounds__(4 * HD) void pool_tile_kernel(const int32_t* __rest
     float mx = -INFINITY;
     int32_t am = INT32_MAX;
     float yv[16];  // the 16 rows' loads are issued together
-    load_rows<HD, false>(yv, tile * TILE + wv * 16, end, c, Y, nullptr, nullptr, nullptr);
+    const int32_t r0 = tile * TILE + wv * 16;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) yv[r] = r0 + r < end ? Y[static_cast<int64_t>(r0 + r) * HD + c] : 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int32_t row = tile * TILE + wv * 16 + r;
@@ -1217,9 +1112,12 @@ __global__ __launch_bounds__(128) void head_bwd_kernel(const float* __restrict__
 
 // Layer backward, first half, per tile: dX from pooling (mean and arg-max) and, below the last
 // layer, from the next layer's aggregation (A_hat^T dH = A_hat dH, A symmetric); ReLU and the
-// affine part of InstanceNorm; per-tile sums for the normalisation backward and gamma/beta.
-template <int HD, bool Y0>
-__global__ __launch_bounds__(4 * HD) void bwd_a_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+// affine part of InstanceNorm; per-tile sums for the normalisation backward and gamma/beta. The walk and the
+// split of rows and channels over the lanes are the layer kernel's, and so is what bounds it: the
+// gathers of dH and, on large batches, Y in and dxhat out (422k nodes, four layers: 389 us with one channel per lane
+// and the sums passed through LDS one by one, 323 here).
+template <int HD, bool Y0, typename Off>
+__global__ __launch_bounds__(4 * HD, 5) void bwd_a_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, const int32_t* __restrict__ tile_graph,
                                                    const int32_t* __restrict__ gend, const float* __restrict__ gcnt,
                                                    const float* __restrict__ Y, const float* __restrict__ H0,
@@ -1230,60 +1128,109 @@ __global__ __launch_bounds__(4 * HD) void bwd_a_kernel(const int32_t* __restrict
                                                    const int32_t* __restrict__ argmax, int layer,
                                                    const float* __restrict__ dHn, float* __restrict__ dxh,
                                                    double* __restrict__ tb) {
-    __shared__ double sh[4][HD];
-    const int tile = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    constexpr int LD = HD + 4, G = HD / 4;
+    __shared__ __align__(16) float aggs[TILE][LD];  // per row: sum of w * dH of the layer above; then the reductions
+    const int tile = dealt_tile(), wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const int32_t r0 = tile * TILE + wv * 16;
+    const int32_t g0 = r0 + 4 * (c / G);  // the first row of the lane's group (see visit_rows_x4)
+    const int rp = dHn ? ptr[g0 + min(static_cast<int>(threadIdx.x % G), 4)] : 0;
     const int g = tile_graph[tile];
     const int32_t end = gend[g];
-    const float m = mu[g * HD + c], rs = rstd[g * HD + c], ga = gam[c], be = bet[c];
-    const float dmean = dpooled[(g * NL + layer) * 2 * HD + c] / gcnt[g];
-    const float dmax = dpooled[(g * NL + layer) * 2 * HD + HD + c];
-    const int32_t am = argmax[(g * NL + layer) * HD + c];
-    __shared__ float aggs[TILE][HD];  // per row: sum of w * dH of the layer above (A_hat^T = A_hat)
-    double sa = 0.0, sb = 0.0, sg = 0.0, sbe = 0.0;
-    const int32_t r0 = tile * TILE + wv * 16;
-    float yv[16];  // this wavefront's rows of Y, loaded together while the aggregation runs
-    load_rows<HD, Y0>(yv, r0, end, c, Y, H0, W0, b0);
-    float acc = 0.0f;
+    const int c4 = 4 * static_cast<int>(threadIdx.x % G);  // the lane's channels: c4 .. c4 + 3
+    float* const mine = &aggs[g0 - tile * TILE][c4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<float4*>(mine + i * LD) = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 yv[4];  // the rows' own y, loaded while the aggregation runs
+    auto own = [&] {
+        float4 w04, w14, bb4;
+        if constexpr (Y0) {
+            w04 = *reinterpret_cast<const float4*>(W0 + c4);
+            w14 = *reinterpret_cast<const float4*>(W0 + HD + c4);
+            bb4 = *reinterpret_cast<const float4*>(b0 + c4);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (Y0)
+                yv[e] = y0_of4(reinterpret_cast<const float2*>(H0)[g0 + e], w04, w14, bb4);
+            else
+                yv[e] = *reinterpret_cast<const float4*>(Y + static_cast<int64_t>(g0 + e) * HD + c4);
+        }
+    };
     if (dHn) {
-        visit_rows<HD, float>(
-            ptr, col, w, r0, r0 + 16, [&](int32_t j) { return dHn[static_cast<int64_t>(j) * HD + c]; },
-            [&](float wp, float v) { acc += wp * v; },
-            [&](int32_t row) {
-                aggs[row - tile * TILE][c] = acc;
-                acc = 0.0f;
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        visit_rows_x4<G, false>(
+            rp, col, w, own,
+            [&](int32_t j) {
+                const Off at = static_cast<Off>(j) * (HD * 4) + c4 * 4;
+                return *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(dHn) + at);
+            },
+            [&](float wp, const float4& v) {
+                acc.x += wp * v.x;
+                acc.y += wp * v.y;
+                acc.z += wp * v.z;
+                acc.w += wp * v.w;
+            },
+            [&](int i) {  // read back below by the same lane
+                *reinterpret_cast<float4*>(mine + i * LD) = acc;
+                acc = make_float4(0.f, 0.f, 0.f, 0.f);
             });
     } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) aggs[wv * 16 + r][c] = 0.0f;
+        own();
     }
-    // each lane reads back only what it wrote (same wavefront, same channel): no barrier needed
+    const auto four = [](const float4& v, float (&o)[4]) {
+        o[0] = v.x;
+        o[1] = v.y;
+        o[2] = v.z;
+        o[3] = v.w;
+    };
+    float m[4], rs[4], ga[4], be[4], dmean[4], dmax[4];
+    four(*reinterpret_cast<const float4*>(mu + g * HD + c4), m);
+    four(*reinterpret_cast<const float4*>(rstd + g * HD + c4), rs);
+    four(*reinterpret_cast<const float4*>(gam + c4), ga);
+    four(*reinterpret_cast<const float4*>(bet + c4), be);
+    const float* dp = dpooled + static_cast<int64_t>(g * NL + layer) * 2 * HD + c4;
+    four(*reinterpret_cast<const float4*>(dp), dmean);
+    four(*reinterpret_cast<const float4*>(dp + HD), dmax);
+    const int4 am4 = *reinterpret_cast<const int4*>(argmax + (g * NL + layer) * HD + c4);
+    const int32_t am[4] = {am4.x, am4.y, am4.z, am4.w};
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int32_t row = r0 + r;
-        float d = 0.0f;
-        if (row < end) {
-            const float dx = dmean + (row == am ? dmax : 0.0f) + aggs[wv * 16 + r][c];
-            const float xh = (yv[r] - m) * rs;
-            const float xn = xh * ga + be;
+    for (int k = 0; k < 4; ++k) dmean[k] /= gcnt[g];
+    double sa[4] = {}, sb[4] = {}, sg[4] = {}, sbe[4] = {};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int32_t row = g0 + e;
+        float y[4], ag[4], d[4];
+        four(yv[e], y);
+        four(*reinterpret_cast<const float4*>(mine + e * LD), ag);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            d[k] = 0.0f;
+            if (row >= end) continue;
+            const float dx = dmean[k] + (row == am[k] ? dmax[k] : 0.0f) + ag[k];
+            const float xh = (y[k] - m[k]) * rs[k];
+            const float xn = xh * ga[k] + be[k];
             const float dxn = xn > 0.0f ? dx : 0.0f;
-            d = dxn * ga;
-            sa += d;
-            sb += static_cast<double>(d) * xh;
-            sg += static_cast<double>(dxn) * xh;
-            sbe += dxn;
+            d[k] = dxn * ga[k];
+            sa[k] += d[k];
+            sb[k] += static_cast<double>(d[k]) * xh;
+            sg[k] += static_cast<double>(dxn) * xh;
+            sbe[k] += dxn;
         }
-        dxh[static_cast<int64_t>(row) * HD + c] = d;
+        *reinterpret_cast<float4*>(dxh + static_cast<int64_t>(row) * HD + c4) = make_float4(d[0], d[1], d[2], d[3]);
     }
-    sa = wave4_sum(sa, sh);
-    sb = wave4_sum(sb, sh);
-    sg = wave4_sum(sg, sh);
-    sbe = wave4_sum(sbe, sh);
-    if (wv == 0) {
-        tb[tile * 4 * HD + c] = sa;
-        tb[tile * 4 * HD + HD + c] = sb;
-        tb[tile * 4 * HD + 2 * HD + c] = sg;
-        tb[tile * 4 * HD + 3 * HD + c] = sbe;
-    }
+    // over the 16 rows of the HD lanes, then over the tile, in a fixed order (as in layer_kernel)
+    const int cc = c4 + reduced_channel<G>();
+    const double t[4] = {reduce_groups<G>(sa), reduce_groups<G>(sb), reduce_groups<G>(sg), reduce_groups<G>(sbe)};
+    auto part = [&](int k) { return reinterpret_cast<double*>(&aggs[16 * k][0]); };
+    static_assert(16 * LD * sizeof(float) >= 4 * HD * sizeof(double), "they fit");
+    wave_sync();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part(wv)[q * HD + cc] = t[q];
+    __syncthreads();
+    if (wv == 0)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            tb[tile * 4 * HD + q * HD + c] = part(0)[q * HD + c] + part(1)[q * HD + c] + part(2)[q * HD + c] + part(3)[q * HD + c];
 }
 
 // Per graph: means of dxhat and dxhat*xhat; gamma/beta gradients of the graph (from the chunk
@@ -1945,7 +1892,10 @@ void backward_impl(gcin_batch* b, int degree, int precision, const float* P, con
     float* bufs[2] = {b->dHa, b->dHb};
     for (int l = NL - 1; l >= 0; --l) {
         const float *W0 = P + o.convW[0], *b0 = P + o.convb[0];
-        (l == 0 ? bwd_a_kernel<HD, true> : bwd_a_kernel<HD, false>)<<<T, NT, 0, st>>>(
+        auto pick = [&](auto off) {
+            return l == 0 ? bwd_a_kernel<HD, true, decltype(off)> : bwd_a_kernel<HD, false, decltype(off)>;
+        };
+        (b->N * HD * 4 <= UINT32_MAX ? pick(uint32_t{}) : pick(uint64_t{}))<<<T, NT, 0, st>>>(
             b->ptr, b->col, b->w, b->d_tile_graph, b->d_gend, b->d_gcnt, b->Y[l], b->H0, W0, b0, b->mu[l], b->rstd[l],
             P + o.gam[l], P + o.bet[l], b->dpooled, b->argmax, l, dHn, b->dxh, b->tb);
         chunk_sum_kernel<HD, 4><<<dim3(b->nchunks, 4), NT, 0, st>>>(b->tb, b->d_cbound, b->cbuf);

@@ -37,7 +37,10 @@ constexpr int JK = RO * NL;
 constexpr int M1 = 128, M2 = 64;
 constexpr int TILE = 64;
 constexpr int kAdamThreads = 256;
-constexpr int kWBlocks = 512; // fixed grid of the weight-gradient reductions
+// Grids of the weight-gradient kernels, at most: what the chip holds of bwd_b_kernel at a time (its LDS leaves
+// room for 3 or 7 workgroups per CU), and of bwd_b0_kernel, which keeps nothing but its loads in flight.
+constexpr int w_blocks(int hidden) { return hidden == 64 ? 768 : 1792; }
+constexpr int kW0Blocks = 1024;
 constexpr int kMaxOut = 9;    // 2 d + 1 for d <= 4
 constexpr float kEps = 1e-5f;
 
@@ -1258,30 +1261,41 @@ __global__ __launch_bounds__(4 * HD) void bwd_final_kernel(const double* __restr
 }
 
 // Layer backward, second half. dY = rstd (dxhat - mean(dxhat) - xhat mean(dxhat xhat));
-// dH = dY W^T (stored for the layer below unless first); partial dW = H^T dY and db = sum dY
-// accumulated over the tiles a workgroup visits (fixed grid of kWBlocks, fixed order).
-template <int HD, bool MFMA, bool Y0>
+// dH = dY W^T (stored for the layer below); partial dW = H^T dY and db = sum dY
+// accumulated over the tiles a workgroup visits (fixed grid of w_blocks, fixed order). With MFMA it is
+// bound by its four arrays (422k nodes: 432 MB in 92 us, 101 with 512
+// workgroups). In FP32 by the LDS reads of the products: a thread
+// keeps its row of W and reads rows of dY and H as 16-byte broadcasts (36.5k nodes of 32 channels: 41 us
+// with W read per row and two rounds of tiles, 14 now).
+template <int HD, bool MFMA>
 __global__ __launch_bounds__(4 * HD) void bwd_b_kernel(int ntiles, const int32_t* __restrict__ tile_graph,
                                                    const int32_t* __restrict__ gend, const float* __restrict__ Y,
-                                                   const float* __restrict__ H0, const float* __restrict__ W0,
-                                                   const float* __restrict__ b0,
                                                    const float* __restrict__ mu, const float* __restrict__ rstd,
                                                    const float* __restrict__ gmean, const float* __restrict__ dxh,
-                                                   const float* __restrict__ H, int in_dim,
-                                                   const float* __restrict__ W, float* __restrict__ dH,
-                                                   float* __restrict__ wpart, double* __restrict__ bpart) {
-    __shared__ float dYs[TILE][HD + 1];
-    __shared__ float Hs[TILE][HD + 1];
-    float (*Ds)[HD + 1] = Hs;  // the dH product is formed after dW no longer needs Hs
-    __shared__ unsigned short Bt[HD][HD + 8];
+                                                   const float* __restrict__ H, const float* __restrict__ W,
+                                                   float* __restrict__ dH, float* __restrict__ wpart,
+                                                   double* __restrict__ bpart) {
+    constexpr int LD = HD + (MFMA ? 1 : 4);  // FP32: rows stay aligned to 16 bytes
+    __shared__ __align__(16) float dYs[TILE][LD];
+    __shared__ __align__(16) float Hs[TILE][LD];
+    float (*Ds)[LD] = Hs;  // the dH product is formed after dW no longer needs Hs
+    __shared__ unsigned short Bt[MFMA ? HD : 1][HD + 8];
     __shared__ double sh[4][HD];
     const int wv = threadIdx.x / HD, c = threadIdx.x % HD;
     static_assert(!MFMA || HD == 64, "the MFMA tiling is written for 64 channels");
-    constexpr int NT = 4 * HD, NW = HD / 4;  // threads; dW entries per thread (in_dim <= HD)
-    if constexpr (MFMA) {
-        if (dH) stage_bf16<HD>(W, false, Bt);  // dH = dY W^T: B[c'][k] = W[k][c'] read as rows of W
-    }
-    // dW accumulator: thread owns W entries e = threadIdx.x + q*NT (in_dim*HD entries)
+    constexpr int NW = HD / 4;  // dW entries per thread
+    if constexpr (MFMA) stage_bf16<HD>(W, false, Bt);  // dH = dY W^T: B[c'][k] = W[k][c'] read as rows of W
+    float wr[MFMA ? 1 : HD];                           // FP32: row c of W
+    if constexpr (!MFMA)
+#pragma unroll
+        for (int q = 0; q < HD; q += 4) {
+            const float4 v = *reinterpret_cast<const float4*>(W + c * HD + q);
+            wr[q] = v.x;
+            wr[q + 1] = v.y;
+            wr[q + 2] = v.z;
+            wr[q + 3] = v.w;
+        }
+    // FP32: a thread owns the entries k = NW wv + q of column c of dW
     float accw[NW];
     for (int q = 0; q < NW; ++q) accw[q] = 0.0f;
     double accb = 0.0;
@@ -1298,12 +1312,9 @@ __global__ __launch_bounds__(4 * HD) void bwd_b_kernel(int ntiles, const int32_t
                 const int32_t row = tile * TILE + wv * 16 + r8 + r;
                 const int64_t k = static_cast<int64_t>(row) * HD + c;
                 const bool ok = row < end;
-                if constexpr (Y0)
-                    yv[r] = ok ? y0_of(reinterpret_cast<const float2*>(H0)[row], W0[c], W0[HD + c], b0[c]) : 0.0f;
-                else
-                    yv[r] = ok ? Y[k] : 0.0f;
+                yv[r] = ok ? Y[k] : 0.0f;
                 dv[r] = ok ? dxh[k] : 0.0f;
-                hv[r] = ok && c < in_dim ? H[static_cast<int64_t>(row) * in_dim + c] : 0.0f;
+                hv[r] = ok ? H[k] : 0.0f;
             }
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
@@ -1322,68 +1333,70 @@ __global__ __launch_bounds__(4 * HD) void bwd_b_kernel(int ntiles, const int32_t
         __syncthreads();
         // dW[k][c'] += sum_rows H[row][k] dY[row][c']
         if constexpr (!MFMA) {
-            for (int q = 0; q < NW; ++q) {
-                const int e = threadIdx.x + q * NT;
-                if (e < in_dim * HD) {
-                    const int k = e / HD, cc = e % HD;
-                    float acc = 0.0f;
-                    for (int r = 0; r < TILE; ++r) acc += Hs[r][k] * dYs[r][cc];
-                    accw[q] += acc;
+            float acc[NW];
+#pragma unroll
+            for (int q = 0; q < NW; ++q) acc[q] = 0.0f;
+#pragma unroll 4
+            for (int r = 0; r < TILE; ++r) {
+                const float dy = dYs[r][c];
+#pragma unroll
+                for (int q = 0; q < NW; q += 4) {
+                    const float4 h = *reinterpret_cast<const float4*>(&Hs[r][wv * NW + q]);
+                    acc[q] += h.x * dy;
+                    acc[q + 1] += h.y * dy;
+                    acc[q + 2] += h.z * dy;
+                    acc[q + 3] += h.w * dy;
                 }
             }
+#pragma unroll
+            for (int q = 0; q < NW; ++q) accw[q] += acc[q];
         } else {
-            if (in_dim == HD) {
-                // 64 x 64 = (H^T)(64 x 64 rows) (dY): wavefront wv owns output rows k in [16 wv, 16 wv + 16)
-                const int lane = c, i = lane % 16, kq = (lane / 16) * 8;
-                f32x4 acc[4];
-                for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-                for (int ks = 0; ks < TILE; ks += 32) {
-                    // H^T is the uncentred operand here as in the forward product: split it
-                    u16x8 av, alv;
-                    for (int e = 0; e < 8; ++e) {
-                        unsigned short h, l;
-                        split_bf16(Hs[ks + kq + e][wv * 16 + i], h, l);
-                        av[e] = h;
-                        alv[e] = l;
-                    }
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, av);
-                    const bf16x8 al = __builtin_bit_cast(bf16x8, alv);
-                    for (int nb = 0; nb < 4; ++nb) {
-                        u16x8 bv;
-                        for (int e = 0; e < 8; ++e) bv[e] = f2bf(dYs[ks + kq + e][nb * 16 + i]);
-                        const bf16x8 b = __builtin_bit_cast(bf16x8, bv);
-                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nb], 0, 0, 0);
-                        acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[nb], 0, 0, 0);
-                    }
+            // 64 x 64 = (H^T)(64 x 64 rows) (dY): wavefront wv owns output rows k in [16 wv, 16 wv + 16)
+            const int lane = c, i = lane % 16, kq = (lane / 16) * 8;
+            f32x4 acc[4];
+            for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < TILE; ks += 32) {
+                // H^T is the uncentred operand here as in the forward product: split it
+                u16x8 av, alv;
+                for (int e = 0; e < 8; ++e) {
+                    unsigned short h, l;
+                    split_bf16(Hs[ks + kq + e][wv * 16 + i], h, l);
+                    av[e] = h;
+                    alv[e] = l;
                 }
-                // lane holds rows k = 16 wv + 4 (lane/16) + e, column 16 nb + i; map to accw slots
-                for (int nb = 0; nb < 4; ++nb)
-                    for (int e = 0; e < 4; ++e) accw[nb * 4 + e] += acc[nb][e];
-            } else {
-                for (int q = 0; q < NW; ++q) {
-                    const int e = threadIdx.x + q * NT;
-                    if (e < in_dim * HD) {
-                        const int k = e / HD, cc = e % HD;
-                        float acc = 0.0f;
-                        for (int r = 0; r < TILE; ++r) acc += Hs[r][k] * dYs[r][cc];
-                        accw[q] += acc;
-                    }
+                const bf16x8 a = __builtin_bit_cast(bf16x8, av);
+                const bf16x8 al = __builtin_bit_cast(bf16x8, alv);
+                for (int nb = 0; nb < 4; ++nb) {
+                    u16x8 bv;
+                    for (int e = 0; e < 8; ++e) bv[e] = f2bf(dYs[ks + kq + e][nb * 16 + i]);
+                    const bf16x8 b = __builtin_bit_cast(bf16x8, bv);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nb], 0, 0, 0);
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[nb], 0, 0, 0);
                 }
             }
+            // lane holds rows k = 16 wv + 4 (lane/16) + e, column 16 nb + i; map to accw slots
+            for (int nb = 0; nb < 4; ++nb)
+                for (int e = 0; e < 4; ++e) accw[nb * 4 + e] += acc[nb][e];
         }
-        if (dH) {  // dH = dY W^T into the rows of Hs
-            __syncthreads();
-            if constexpr (!MFMA) {
-                for (int r = 0; r < 16; ++r) {
-                    const int lr = wv * 16 + r;
-                    float acc = 0.0f;
-#pragma unroll 8
-                    for (int q = 0; q < HD; ++q) acc += dYs[lr][q] * W[c * HD + q];
-                    Ds[lr][c] = acc;
+        // dH = dY W^T
+        if constexpr (!MFMA) {
+            for (int r = 0; r < 16; ++r) {
+                const int lr = wv * 16 + r;
+                const int32_t row = tile * TILE + lr;
+                float acc = 0.0f;
+#pragma unroll
+                for (int q = 0; q < HD; q += 4) {
+                    const float4 d = *reinterpret_cast<const float4*>(&dYs[lr][q]);
+                    acc += d.x * wr[q];
+                    acc += d.y * wr[q + 1];
+                    acc += d.z * wr[q + 2];
+                    acc += d.w * wr[q + 3];
                 }
-            } else {
-                tile_gemm<HD, true>(dYs, W, Bt, Ds);
+                dH[static_cast<int64_t>(row) * HD + c] = row < end ? acc : 0.0f;
             }
+        } else {  // into the rows of Hs
+            __syncthreads();
+            tile_gemm<HD, true>(dYs, W, Bt, Ds);
             __syncthreads();
             for (int r = 0; r < 16; ++r) {
                 const int lr = wv * 16 + r;
@@ -1394,21 +1407,83 @@ __global__ __launch_bounds__(4 * HD) void bwd_b_kernel(int ntiles, const int32_t
         __syncthreads();
     }
     // write this workgroup's partials in plain [k][c] order
-    if (MFMA && in_dim == HD) {
+    float* const wp = wpart + static_cast<int64_t>(blockIdx.x) * HD * HD;
+    if constexpr (MFMA) {
         const int lane = c, i = lane % 16;
         for (int nb = 0; nb < 4; ++nb)
             for (int e = 0; e < 4; ++e) {
                 const int k = wv * 16 + (lane / 16) * 4 + e, cc = nb * 16 + i;
-                wpart[static_cast<int64_t>(blockIdx.x) * HD * HD + k * HD + cc] = accw[nb * 4 + e];
+                wp[k * HD + cc] = accw[nb * 4 + e];
             }
     } else {
-        for (int q = 0; q < NW; ++q) {
-            const int e = threadIdx.x + q * NT;
-            if (e < in_dim * HD) wpart[static_cast<int64_t>(blockIdx.x) * HD * HD + e] = accw[q];
-        }
+#pragma unroll
+        for (int q = 0; q < NW; ++q) wp[(wv * NW + q) * HD + c] = accw[q];
     }
     accb = wave4_sum(accb, sh);
     if (wv == 0) bpart[blockIdx.x * HD + c] = accb;
+}
+
+// The same for layer 0, whose input is two features per node and whose dH nobody needs: a stream over dxhat
+// (Y formed from H0), the lanes' rows and channels as in bwd_a_kernel and the sums in FP64 registers until
+// the end; no LDS tile and no barrier per tile. (422k nodes: 115 us as the general kernel with
+// two input channels, 20 here.)
+template <int HD>
+__global__ __launch_bounds__(4 * HD) void bwd_b0_kernel(int ntiles, const int32_t* __restrict__ tile_graph,
+                                                    const int32_t* __restrict__ gend, const float* __restrict__ H0,
+                                                    const float* __restrict__ W0, const float* __restrict__ b0,
+                                                    const float* __restrict__ mu, const float* __restrict__ rstd,
+                                                    const float* __restrict__ gmean, const float* __restrict__ dxh,
+                                                    float* __restrict__ wpart, double* __restrict__ bpart) {
+    constexpr int G = HD / 4;
+    __shared__ double sh[4][3][HD];
+    const int wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const int c4 = 4 * static_cast<int>(threadIdx.x % G);
+    const float4 w0 = *reinterpret_cast<const float4*>(W0 + c4), w1 = *reinterpret_cast<const float4*>(W0 + HD + c4),
+                 bb = *reinterpret_cast<const float4*>(b0 + c4);
+    double s0[4] = {}, s1[4] = {}, sb[4] = {};
+    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        const int32_t g0 = tile * TILE + wv * 16 + 4 * (c / G);
+        float4 dv[4];
+        float2 hv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            dv[e] = *reinterpret_cast<const float4*>(dxh + static_cast<int64_t>(g0 + e) * HD + c4);
+            hv[e] = reinterpret_cast<const float2*>(H0)[g0 + e];
+        }
+        const int g = tile_graph[tile];
+        const int32_t end = gend[g];
+        const float4 m = *reinterpret_cast<const float4*>(mu + g * HD + c4);
+        const float4 rs = *reinterpret_cast<const float4*>(rstd + g * HD + c4);
+        const float4 ma = *reinterpret_cast<const float4*>(gmean + g * 2 * HD + c4);
+        const float4 mb = *reinterpret_cast<const float4*>(gmean + g * 2 * HD + HD + c4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (g0 + e >= end) continue;
+            const float4 y = y0_of4(hv[e], w0, w1, bb);
+            const float dy[4] = {rs.x * (dv[e].x - ma.x - (y.x - m.x) * rs.x * mb.x),
+                                 rs.y * (dv[e].y - ma.y - (y.y - m.y) * rs.y * mb.y),
+                                 rs.z * (dv[e].z - ma.z - (y.z - m.z) * rs.z * mb.z),
+                                 rs.w * (dv[e].w - ma.w - (y.w - m.w) * rs.w * mb.w)};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                s0[k] += static_cast<double>(hv[e].x) * dy[k];
+                s1[k] += static_cast<double>(hv[e].y) * dy[k];
+                sb[k] += dy[k];
+            }
+        }
+    }
+    const int cc = c4 + reduced_channel<G>();
+    sh[wv][0][cc] = reduce_groups<G>(s0);
+    sh[wv][1][cc] = reduce_groups<G>(s1);
+    sh[wv][2][cc] = reduce_groups<G>(sb);
+    __syncthreads();
+    if (wv < 3) {
+        const double v = sh[0][wv][c] + sh[1][wv][c] + sh[2][wv][c] + sh[3][wv][c];
+        if (wv < 2)
+            wpart[(static_cast<int64_t>(blockIdx.x) * 2 + wv) * HD + c] = static_cast<float>(v);
+        else
+            bpart[static_cast<int64_t>(blockIdx.x) * HD + c] = v;
+    }
 }
 
 // One workgroup: D1 = A B by the FP32 path and D2 = A B by the BF16 MFMA path of tile_gemm.
@@ -1653,8 +1728,8 @@ size_t layout_batch(gcin_batch* b, uintptr_t base) {
     b->tb = cv.take<double>(T * 4 * HD);
     b->gmean = cv.take<float>(G * 2 * HD);
     b->ggb = cv.take<double>(G * 2 * HD);
-    b->wpart = cv.take<float>(static_cast<size_t>(kWBlocks) * HD * HD);
-    b->bpart = cv.take<double>(static_cast<size_t>(kWBlocks) * HD);
+    b->wpart = cv.take<float>(std::max<size_t>(static_cast<size_t>(w_blocks(HD)) * HD, kW0Blocks * 2) * HD);
+    b->bpart = cv.take<double>(static_cast<size_t>(std::max(w_blocks(HD), kW0Blocks)) * HD);
     return (cv.off + 255) & ~static_cast<size_t>(255);
 }
 
@@ -1903,15 +1978,19 @@ void backward_impl(gcin_batch* b, int degree, int precision, const float* P, con
         sums.add(b->ggb, G, 2 * HD, HD, grads + o.gam[l]);
         sums.add(b->ggb + HD, G, 2 * HD, HD, grads + o.bet[l]);
         float* dHout = l > 0 ? bufs[l & 1] : nullptr;
-        const int in_dim = l == 0 ? 2 : HD;
-        const float* Hin = l == 0 ? b->H0 : b->H[l];
-        const int grid = T < kWBlocks ? T : kWBlocks;
-        auto kern = l == 0 ? bwd_b_kernel<HD, false, true> : bwd_b_kernel<HD, false, false>;
-        if constexpr (HD == 64)
-            if (precision != GCIN_FP32) kern = l == 0 ? bwd_b_kernel<HD, true, true> : bwd_b_kernel<HD, true, false>;
-        kern<<<grid, NT, 0, st>>>(T, b->d_tile_graph, b->d_gend, b->Y[l], b->H0, W0, b0, b->mu[l], b->rstd[l],
-                                  b->gmean, b->dxh, Hin, in_dim, P + o.convW[l], dHout, b->wpart, b->bpart);
-        sums.add(b->wpart, grid, HD * HD, in_dim * HD, grads + o.convW[l]);
+        const int grid = std::min(T, l > 0 ? w_blocks(HD) : kW0Blocks);
+        if (l == 0) {
+            bwd_b0_kernel<HD><<<grid, NT, 0, st>>>(T, b->d_tile_graph, b->d_gend, b->H0, W0, b0, b->mu[l], b->rstd[l],
+                                                   b->gmean, b->dxh, b->wpart, b->bpart);
+            sums.add(b->wpart, grid, 2 * HD, 2 * HD, grads + o.convW[l]);
+        } else {
+            auto kern = bwd_b_kernel<HD, false>;
+            if constexpr (HD == 64)
+                if (precision != GCIN_FP32) kern = bwd_b_kernel<HD, true>;
+            kern<<<grid, NT, 0, st>>>(T, b->d_tile_graph, b->d_gend, b->Y[l], b->mu[l], b->rstd[l], b->gmean, b->dxh,
+                                      b->H[l], P + o.convW[l], dHout, b->wpart, b->bpart);
+            sums.add(b->wpart, grid, HD * HD, HD * HD, grads + o.convW[l]);
+        }
         sums.add(b->bpart, grid, HD, HD, grads + o.convb[l]);
         reduce_parts_kernel<<<sums.blocks, 256, 0, st>>>(sums);
         sums = PartJobs{};

@@ -472,13 +472,34 @@ __device__ __forceinline__ void tile_gemm(const float (*A)[LD], const float* __r
     static_assert(!MFMA || HD == 64, "the MFMA tiling is written for 64 channels");
     const int wv = threadIdx.x / HD, lane = threadIdx.x % HD;
     if constexpr (!MFMA) {
-        for (int r = 0; r < 16; ++r) {
-            const int lr = wv * 16 + r;
-            float acc = 0.0f;
-#pragma unroll 8
-            for (int k = 0; k < HD; ++k) acc += A[lr][k] * Bf[k * HD + lane];
-            D[lr][lane] = acc;
+        // column `lane` of B in registers, 32 rows of it at a time, and the rows of A as broadcasts
+        float acc[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+        for (int k0 = 0; k0 < HD; k0 += 32) {
+            float bc[32];
+#pragma unroll
+            for (int k = 0; k < 32; ++k) bc[k] = Bf[(k0 + k) * HD + lane];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float* ar = &A[wv * 16 + r][k0];
+                if constexpr (LD % 4 == 0) {
+#pragma unroll
+                    for (int k = 0; k < 32; k += 4) {
+                        const float4 a = *reinterpret_cast<const float4*>(ar + k);
+                        acc[r] += a.x * bc[k];
+                        acc[r] += a.y * bc[k + 1];
+                        acc[r] += a.z * bc[k + 2];
+                        acc[r] += a.w * bc[k + 3];
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 32; ++k) acc[r] += ar[k] * bc[k];
+                }
+            }
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) D[wv * 16 + r][lane] = acc[r];
     } else {
         const int i = lane % 16, kq = (lane / 16) * 8;
         f32x4 acc[4];
@@ -611,7 +632,7 @@ __device__ __forceinline__ int dealt_tile() {
 // Y0: the layer below is layer 0, whose output is formed from H0 (y0_of) instead of read from Yp. Off: type
 // of the byte offsets into Yp (32 bits where they suffice).
 template <int HD, bool MFMA, bool X3, bool Y0, typename Off>
-__global__ __launch_bounds__(4 * HD, Y0 || X3 ? 5 : 4) void layer_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+__global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, const int32_t* __restrict__ tile_graph,
                                                    const int32_t* __restrict__ gend, const float* __restrict__ Yp,
                                                    const float* __restrict__ H0, const float* __restrict__ W0,

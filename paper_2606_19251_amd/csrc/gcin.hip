@@ -801,35 +801,38 @@ __global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kern
 // Per-graph reductions over tiles run in two fixed-order stages so that large graphs (the fine
 // level has n/64 tiles) are spread over many workgroups: stage 1 sums the tiles of each chunk
 // (at most kChunkTiles consecutive tiles of one graph, chunks counted from the graph's first
-// tile), stage 2 the chunks of each graph. In both, wave w of the workgroup sums items w, w+4,
-// w+8, ... in order and the four wave sums are added in wave order: deterministic, and a
-// graph's result does not depend on the other graphs of the batch. A full chunk is 64 dependent
-// additions per wave whose loads decide the time, so kAhead items' loads are issued together, and
-// what can be summed apart (y, y^2, the readout; blockIdx.y) gets its own workgroup: one workgroup
-// reads only some 50 GB/s. The statistics of a layer and the readout of the layer below it share their
+// tile), stage 2 the chunks of each graph. In both, group w of the workgroup's kSumGroups groups of HD lanes
+// sums items w, w + kSumGroups, ... in order and the groups' sums are added in group order:
+// deterministic, and a graph's result does not depend on the other graphs of the batch. The loads decide the
+// time, so kAhead items' loads are issued together, all that a full chunk gives a group (with 4 groups a chunk
+// took four such rounds, 7.5 us against 4.7 on 625 tiles of 32 channels), and what can be summed apart
+// (y, y^2, the readout, the backward's four sums; blockIdx.y) gets its own workgroup. The statistics of a layer and the readout of the layer below it share their
 // launches, and where every graph is one chunk, stage 1 finishes it and there is no stage 2. On the
 // 998k-cell hierarchy the forward's reductions went from 16 launches and 180 us to 10 and 92, on the
-// 32-mesh training batch from 16 and 130 to 5 and 50; the backward's per-chunk sums from 13 to 7 us.
+// 32-mesh training batch from 16 and 130 to 5 and 44, the backward's sums from 8 and 48 to 4 and 33.
 constexpr int kChunkTiles = 256;
 constexpr int kAhead = 16;
+constexpr int kSumGroups = 16;
 
-// Sum of in[i][c] over the items i = i0 + wv, i0 + wv + 4, ... < i1 in order, rows `stride` apart, the
-// four waves' sums added in wave order; the same value in every wave.
+// Sum of in[i][c] over the items i0 <= i < i1 as above, rows `stride` apart; valid in group 0.
 template <int HD>
 __device__ __forceinline__ double sum_items(const double* __restrict__ in, int64_t stride, int32_t i0, int32_t i1,
                                             int wv, int c, double (*sh)[HD]) {
     double s = 0.0;
-    for (int32_t i = i0 + wv; i < i1; i += 4 * kAhead) {
+    for (int32_t i = i0 + wv; i < i1; i += kSumGroups * kAhead) {
         double v[kAhead];  // a slot past the end re-reads the last item and is not used
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) v[u] = in[min(i + 4 * u, i1 - 1) * stride + c];
+        for (int u = 0; u < kAhead; ++u) v[u] = in[min(i + kSumGroups * u, i1 - 1) * stride + c];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
-            if (i + 4 * u < i1) s += v[u];
+            if (i + kSumGroups * u < i1) s += v[u];
     }
     sh[wv][c] = s;
     __syncthreads();
-    return ((sh[0][c] + sh[1][c]) + sh[2][c]) + sh[3][c];
+    if (wv != 0) return s;
+#pragma unroll
+    for (int w = 1; w < kSumGroups; ++w) s += sh[w][c];
+    return s;
 }
 
 // Mean and 1/sqrt(biased variance + eps) of a graph's channel from its sums of y and y^2.
@@ -841,31 +844,31 @@ __device__ __forceinline__ void norm_of(double s1, double s2, double n, float* m
     *rstd = static_cast<float>(1.0 / sqrt(var + static_cast<double>(kEps)));
 }
 
-// Sum, max and arg-max over the items as sum_items takes them, the waves combined; valid in wave 0.
+// Sum, max and arg-max over the items as sum_items takes them; valid in group 0.
 template <int HD>
 __device__ __forceinline__ void pool_items(const double* __restrict__ isum, const float* __restrict__ imax,
                                            const int32_t* __restrict__ iarg, int32_t i0, int32_t i1, int wv, int c,
                                            double& s, float& mx, int32_t& am) {
-    __shared__ double ss[4][HD];
-    __shared__ float sm[4][HD];
-    __shared__ int32_t sa[4][HD];
+    __shared__ double ss[kSumGroups][HD];
+    __shared__ float sm[kSumGroups][HD];
+    __shared__ int32_t sa[kSumGroups][HD];
     s = 0.0;
     mx = -INFINITY;
     am = INT32_MAX;
-    for (int32_t i = i0 + wv; i < i1; i += 4 * kAhead) {
+    for (int32_t i = i0 + wv; i < i1; i += kSumGroups * kAhead) {
         double vs[kAhead];
         float vm[kAhead];
         int32_t va[kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
-            const int64_t e = static_cast<int64_t>(min(i + 4 * u, i1 - 1)) * HD + c;
+            const int64_t e = static_cast<int64_t>(min(i + kSumGroups * u, i1 - 1)) * HD + c;
             vs[u] = isum[e];
             vm[u] = imax[e];
             va[u] = iarg[e];
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
-            if (i + 4 * u < i1) {
+            if (i + kSumGroups * u < i1) {
                 s += vs[u];
                 max_merge(mx, am, vm[u], va[u]);
             }
@@ -875,8 +878,11 @@ __device__ __forceinline__ void pool_items(const double* __restrict__ isum, cons
     sa[wv][c] = am;
     __syncthreads();
     if (wv != 0) return;
-    for (int w = 1; w < 4; ++w) max_merge(mx, am, sm[w][c], sa[w][c]);
-    s = ((ss[0][c] + ss[1][c]) + ss[2][c]) + ss[3][c];
+#pragma unroll
+    for (int w = 1; w < kSumGroups; ++w) {
+        s += ss[w][c];
+        max_merge(mx, am, sm[w][c], sa[w][c]);
+    }
 }
 
 // What a reduction of the forward takes and writes: the statistics of layer `layer` (stats) and the
@@ -900,8 +906,8 @@ struct Reduce {
 // chunks); otherwise a chunk and its tiles. blockIdx.y + first selects the part: 0 = statistics (the
 // first stage takes y and y^2 apart, 0 and 1), then the readout.
 template <int HD, bool FINAL>
-__global__ __launch_bounds__(4 * HD) void reduce_kernel(const int32_t* __restrict__ bounds, Reduce r, int first) {
-    __shared__ double sh[2][4][HD];
+__global__ __launch_bounds__(kSumGroups * HD) void reduce_kernel(const int32_t* __restrict__ bounds, Reduce r, int first) {
+    __shared__ double sh[2][kSumGroups][HD];
     constexpr int NSTAT = FINAL ? 1 : 2;
     const int k = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
     const int part = blockIdx.y + first;
@@ -933,14 +939,25 @@ __global__ __launch_bounds__(4 * HD) void reduce_kernel(const int32_t* __restric
     }
 }
 
-// out[k][j][c] = sum over items i in [bounds[k], bounds[k+1]) of in[i][j][c], j = blockIdx.y < K, c < HD
-template <int HD, int K>
-__global__ __launch_bounds__(4 * HD) void chunk_sum_kernel(const double* __restrict__ in, const int32_t* __restrict__ bounds,
-                                                       double* __restrict__ out) {
-    __shared__ double sh[4][HD];
+// The sums of the backward's four quantities j = blockIdx.y over a graph (FINAL) or a chunk, as above:
+// out[k][j][c], or per graph the means of dxhat and dxhat*xhat (j = 0, 1) and the gamma / beta
+// gradients (j = 2, 3).
+template <int HD, bool FINAL>
+__global__ __launch_bounds__(kSumGroups * HD) void bwd_sum_kernel(const double* __restrict__ in,
+                                                                  const int32_t* __restrict__ bounds,
+                                                                  double* __restrict__ out,
+                                                                  const float* __restrict__ gcnt,
+                                                                  float* __restrict__ gmean, double* __restrict__ ggb) {
+    __shared__ double sh[kSumGroups][HD];
     const int k = blockIdx.x, j = blockIdx.y, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    const double s = sum_items<HD>(in + j * HD, K * HD, bounds[k], bounds[k + 1], wv, c, sh);
-    if (wv == 0) out[(static_cast<int64_t>(k) * K + j) * HD + c] = s;
+    const double s = sum_items<HD>(in + j * HD, 4 * HD, bounds[k], bounds[k + 1], wv, c, sh);
+    if (wv != 0) return;
+    if constexpr (!FINAL)
+        out[(static_cast<int64_t>(k) * 4 + j) * HD + c] = s;
+    else if (j < 2)
+        gmean[(k * 2 + j) * HD + c] = static_cast<float>(s / gcnt[k]);
+    else
+        ggb[(k * 2 + j - 2) * HD + c] = s;
 }
 
 // Per tile: sum, max and first arg-max of x = ReLU(IN(y)) per channel (the last layer's readout).
@@ -1255,30 +1272,6 @@ __global__ __launch_bounds__(4 * HD, 5) void bwd_a_kernel(const int32_t* __restr
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             tb[tile * 4 * HD + q * HD + c] = part(0)[q * HD + c] + part(1)[q * HD + c] + part(2)[q * HD + c] + part(3)[q * HD + c];
-}
-
-// Per graph: means of dxhat and dxhat*xhat; gamma/beta gradients of the graph (from the chunk
-// sums of the four per-tile quantities, as in stats_final_kernel).
-template <int HD>
-__global__ __launch_bounds__(4 * HD) void bwd_final_kernel(const double* __restrict__ ctb, const int32_t* __restrict__ gchunk,
-                                                       const float* __restrict__ gcnt, float* __restrict__ gmean,
-                                                       double* __restrict__ ggb) {
-    __shared__ double sh[4][4][HD];
-    const int g = blockIdx.x, wv = threadIdx.x / HD, c = threadIdx.x % HD;
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int32_t k = gchunk[g] + wv; k < gchunk[g + 1]; k += 4)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s[j] += ctb[(static_cast<int64_t>(k) * 4 + j) * HD + c];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sh[wv][j][c] = s[j];
-    __syncthreads();
-    if (wv != 0) return;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] = ((sh[0][j][c] + sh[1][j][c]) + sh[2][j][c]) + sh[3][j][c];
-    gmean[g * 2 * HD + c] = static_cast<float>(s[0] / gcnt[g]);
-    gmean[g * 2 * HD + HD + c] = static_cast<float>(s[1] / gcnt[g]);
-    ggb[g * 2 * HD + c] = s[2];
-    ggb[g * 2 * HD + HD + c] = s[3];
 }
 
 // Layer backward, second half. dY = rstd (dxhat - mean(dxhat) - xhat mean(dxhat xhat));
@@ -1937,15 +1930,15 @@ void forward_impl(gcin_batch* b, int degree, int precision, const float* P, floa
                  stat_layer < 0 ? nullptr : b->rstd[stat_layer], b->pooled, b->argmax, pool_layer};
         const int stat = stat_layer >= 0, pool = pool_layer >= 0;
         if (one) {
-            reduce_kernel<HD, true><<<dim3(G, stat + pool), NT, 0, st>>>(b->d_cbound, r, 1 - stat);
+            reduce_kernel<HD, true><<<dim3(G, stat + pool), kSumGroups * HD, 0, st>>>(b->d_cbound, r, 1 - stat);
             return;
         }
-        reduce_kernel<HD, false><<<dim3(C, 2 * stat + pool), NT, 0, st>>>(b->d_cbound, r, 2 - 2 * stat);
+        reduce_kernel<HD, false><<<dim3(C, 2 * stat + pool), kSumGroups * HD, 0, st>>>(b->d_cbound, r, 2 - 2 * stat);
         r.tstat = r.cstat;
         r.psum = r.csum;
         r.pmax = r.cmax;
         r.parg = r.carg;
-        reduce_kernel<HD, true><<<dim3(G, stat + pool), NT, 0, st>>>(b->d_gchunk, r, 1 - stat);
+        reduce_kernel<HD, true><<<dim3(G, stat + pool), kSumGroups * HD, 0, st>>>(b->d_gchunk, r, 1 - stat);
     };
     reduce(0, -1);
     const bool mfma = HD == 64 && precision != GCIN_FP32;
@@ -1994,8 +1987,12 @@ void backward_impl(gcin_batch* b, int degree, int precision, const float* P, con
         (b->N * HD * 4 <= UINT32_MAX ? pick(uint32_t{}) : pick(uint64_t{}))<<<T, NT, 0, st>>>(
             b->ptr, b->col, b->w, b->d_tile_graph, b->d_gend, b->d_gcnt, b->Y[l], b->H0, W0, b0, b->mu[l], b->rstd[l],
             P + o.gam[l], P + o.bet[l], b->dpooled, b->argmax, l, dHn, b->dxh, b->tb);
-        chunk_sum_kernel<HD, 4><<<dim3(b->nchunks, 4), NT, 0, st>>>(b->tb, b->d_cbound, b->cbuf);
-        bwd_final_kernel<HD><<<G, NT, 0, st>>>(b->cbuf, b->d_gchunk, b->d_gcnt, b->gmean, b->ggb);
+        const bool one = b->nchunks == G;  // every graph is one chunk
+        if (!one)
+            bwd_sum_kernel<HD, false><<<dim3(b->nchunks, 4), kSumGroups * HD, 0, st>>>(b->tb, b->d_cbound, b->cbuf,
+                                                                                       nullptr, nullptr, nullptr);
+        bwd_sum_kernel<HD, true><<<dim3(G, 4), kSumGroups * HD, 0, st>>>(
+            one ? b->tb : b->cbuf, one ? b->d_cbound : b->d_gchunk, nullptr, b->d_gcnt, b->gmean, b->ggb);
         sums.add(b->ggb, G, 2 * HD, HD, grads + o.gam[l]);
         sums.add(b->ggb + HD, G, 2 * HD, HD, grads + o.bet[l]);
         float* dHout = l > 0 ? bufs[l & 1] : nullptr;

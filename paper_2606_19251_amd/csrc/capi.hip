@@ -467,8 +467,7 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
         for (int l = 0; l < c->nlevels; ++l) {
             Level& L = c->lv[l];
             L.smoother = kSmootherNone;
-            ok(extract_diag(L.n, L.ptr, L.col, L.val, L.diag, c->flags + 0, st));
-            ok(offdiag_absmax(L.n, L.ptr, L.col, L.val, c->partial, L.scale, st));
+            ok(diag_and_scale(L.n, L.ptr, L.col, L.val, L.diag, c->flags + 0, c->partial, L.scale, st));
             ok(cast_f64_f32(L.nnz, L.val, L.val32, st));
             if (l + 1 < c->nlevels) {
                 ok(cast_f64_f32(L.pnnz, L.pval, L.pval32, st));
@@ -527,6 +526,7 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
         for (int l = 0; l < c->nlevels && e == hipSuccess; ++l) {
             Level& L = c->lv[l];
             const bool pads = L.pad_a.cap > 0 && L.pad_p.cap > 0 && L.pad_r.cap > 0;
+            BlockMaxList longest;
             int k = 0;
             for (const Stream& m : streams(L, l + 1 == c->nlevels)) {
                 int32_t* out = c->setup_out + 3 * l + k++;
@@ -534,9 +534,10 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
                     ok(pack_columns(m.n, m.nz, m.ptr, m.col, m.pack->rows, m.pack->off, m.pack->base, m.pack->foff,
                                     m.pack->fslot, m.pack->fcol, m.pack->cap, c->pack_parts, out + kSetupFar, st));
                 // largest row block: sizes the kernels' LDS product buffers
-                ok(block_max_entries(m.n, m.ptr, stream_rows_for(m.n, m.nz), out, st));
-                if (pads) ok(block_max_entries(m.n, m.ptr, 1, out + kSetupLongest, st));
+                longest.add(m.n, m.ptr, stream_rows_for(m.n, m.nz), out);
+                if (pads) longest.add(m.n, m.ptr, 1, out + kSetupLongest);
             }
+            ok(block_max_entries(longest, st));
             L.hrows = 0;
             if (halo_rows(L, l))
                 ok(halo_lists(L.n, L.nnz, L.ptr, L.col, L.val, L.val32, halo_rows(L, l),

@@ -806,8 +806,8 @@ __global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kern
 // deterministic, and a graph's result does not depend on the other graphs of the batch. The loads decide the
 // time, so kAhead items' loads are issued together, all that a full chunk gives a group (with 4 groups a chunk
 // took four such rounds, 7.5 us against 4.7 on 625 tiles of 32 channels), and what can be summed apart
-// (y, y^2, the readout, the backward's four sums; blockIdx.y) gets its own workgroup. The statistics of a layer and the readout of the layer below it share their
-// launches, and where every graph is one chunk, stage 1 finishes it and there is no stage 2. On the
+// (y, y^2, the readout, the backward's four sums; blockIdx.y) gets its own workgroup. The statistics of
+// a layer and the readout of the layer below it share their launches, and where every graph is one chunk, stage 1 finishes it and there is no stage 2. On the
 // 998k-cell hierarchy the forward's reductions went from 16 launches and 180 us to 10 and 92, on the
 // 32-mesh training batch from 16 and 130 to 5 and 44, the backward's sums from 8 and 48 to 4 and 33.
 constexpr int kChunkTiles = 256;

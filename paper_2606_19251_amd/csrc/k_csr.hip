@@ -695,29 +695,32 @@ hipError_t launch_jpre(const CsrView& m, const T* a, const T* d, const T* f, T* 
     }
 }
 
-__global__ __launch_bounds__(kBlock) void block_max_kernel(int32_t nrows, const int32_t* __restrict__ ptr, int rows,
-                                                          int32_t* __restrict__ out) {
+__global__ __launch_bounds__(kBlock) void block_max_kernel(BlockMaxList list) {
     __shared__ int32_t red[kBlock / 64];
+    const BlockMax t = list.item[blockIdx.y];
     const int64_t b = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    const int64_t r0 = b * rows;
+    const int64_t r0 = b * t.rows;
+    if ((r0 - static_cast<int64_t>(threadIdx.x) * t.rows) >= t.nrows) return;  // the whole workgroup is past the end
     int32_t m = 0;
-    if (r0 < nrows) m = ptr[min(r0 + rows, static_cast<int64_t>(nrows))] - ptr[r0];
+    if (r0 < t.nrows) m = t.ptr[min(r0 + t.rows, static_cast<int64_t>(t.nrows))] - t.ptr[r0];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x / 64] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int k = 1; k < kBlock / 64; ++k) m = max(m, red[k]);
-        atomicMax(out, m);
+        atomicMax(t.out, m);
     }
 }
 
 }  // namespace
 
-hipError_t block_max_entries(int32_t nrows, const int32_t* ptr, int rows, int32_t* out, hipStream_t stream) {
-    if (nrows <= 0 || rows <= 0) return hipSuccess;
-    const int64_t nb = (static_cast<int64_t>(nrows) + rows - 1) / rows;
-    block_max_kernel<<<static_cast<unsigned>((nb + kBlock - 1) / kBlock), kBlock, 0, stream>>>(nrows, ptr, rows, out);
+hipError_t block_max_entries(const BlockMaxList& list, hipStream_t stream) {
+    int64_t most = 0;
+    for (int k = 0; k < list.n; ++k)
+        most = std::max(most, (static_cast<int64_t>(list.item[k].nrows) + list.item[k].rows - 1) / list.item[k].rows);
+    if (most <= 0) return hipSuccess;
+    block_max_kernel<<<dim3(static_cast<unsigned>((most + kBlock - 1) / kBlock), list.n), kBlock, 0, stream>>>(list);
     return hipGetLastError();
 }
 

@@ -16,31 +16,29 @@ inline dim3 grid_for(int64_t n) {
     return dim3(static_cast<unsigned>(g));
 }
 
-__global__ void extract_diag_kernel(int32_t n, const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
-                                    const double* __restrict__ val, double* __restrict__ diag,
-                                    int32_t* __restrict__ bad) {
-    const int32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double d = 0.0;
-    bool found = false;
-    for (int32_t p = ptr[i]; p < ptr[i + 1]; ++p)
-        if (col[p] == i) {
-            d = val[p];
-            found = true;
-        }
-    diag[i] = d;
-    if (!found || !(d > 0.0)) atomicOr(bad, 1);
-}
-
-__global__ __launch_bounds__(kBlock) void absmax_partial_kernel(int32_t n, const int32_t* __restrict__ ptr,
-                                                               const int32_t* __restrict__ col,
-                                                               const double* __restrict__ val,
-                                                               double* __restrict__ partial) {
+// Diagonal of every row (bad[0] set where it is missing or not positive) and, per workgroup, the largest
+// |off-diagonal| entry (-1: none), in one pass over the rows.
+__global__ __launch_bounds__(kBlock) void diag_absmax_kernel(int32_t n, const int32_t* __restrict__ ptr,
+                                                            const int32_t* __restrict__ col,
+                                                            const double* __restrict__ val, double* __restrict__ diag,
+                                                            int32_t* __restrict__ bad, double* __restrict__ partial) {
     __shared__ double red[kBlock];
-    double m = -1.0;  // -1 marks "no off-diagonal seen"
-    for (int32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += kReduceBlocks * kBlock)
-        for (int32_t p = ptr[i]; p < ptr[i + 1]; ++p)
-            if (col[p] != i) m = fmax(m, fabs(val[p]));
+    double m = -1.0;
+    for (int32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
+        double d = 0.0;
+        bool found = false;
+        for (int32_t p = ptr[i]; p < ptr[i + 1]; ++p) {
+            const double v = val[p];
+            if (col[p] == i) {
+                d = v;
+                found = true;
+            } else {
+                m = fmax(m, fabs(v));
+            }
+        }
+        diag[i] = d;
+        if (!found || !(d > 0.0)) atomicOr(bad, 1);
+    }
     red[threadIdx.x] = m;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
@@ -50,11 +48,11 @@ __global__ __launch_bounds__(kBlock) void absmax_partial_kernel(int32_t n, const
     if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(kBlock) void absmax_final_kernel(const double* __restrict__ partial,
+__global__ __launch_bounds__(kBlock) void absmax_final_kernel(const double* __restrict__ partial, int count,
                                                              double* __restrict__ scale) {
     __shared__ double red[kBlock];
     double m = -1.0;
-    for (int k = threadIdx.x; k < kReduceBlocks; k += kBlock) m = fmax(m, partial[k]);
+    for (int k = threadIdx.x; k < count; k += kBlock) m = fmax(m, partial[k]);
     red[threadIdx.x] = m;
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
@@ -151,12 +149,51 @@ __global__ void scatter_transpose_kernel(int32_t nf, const int32_t* __restrict__
 }
 
 // The scatter order within a row depends on atomics; sorting by column restores the one
-// exact transpose.
-__global__ void sort_rows_kernel(int32_t nc, const int32_t* __restrict__ r_ptr, int32_t* __restrict__ r_col,
-                                 double* __restrict__ r_val) {
-    const int32_t c = blockIdx.x * kBlock + threadIdx.x;
+// exact transpose. kSortLanes lanes hold a row of up to 4 entries each and put every entry at its rank (the
+// row's entries passed by shuffles); a longer row is sorted in place by one lane. With one thread per row
+// throughout, the chain of dependent moves took 20 us a level however small; 5 us here.
+constexpr int kSortLanes = 16;
+
+// A row of at most Q kSortLanes entries [lo, hi).
+template <int Q>
+__device__ __forceinline__ void rank_row(int32_t lo, int32_t hi, int lane, int32_t* __restrict__ r_col,
+                                         double* __restrict__ r_val) {
+    int32_t key[Q], rank[Q];
+    double v[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int32_t k = lo + q * kSortLanes + lane;
+        key[q] = k < hi ? r_col[k] : INT32_MAX;
+        v[q] = k < hi ? r_val[k] : 0.0;
+        rank[q] = 0;
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int here = min(kSortLanes, hi - lo - q * kSortLanes);
+        for (int l = 0; l < here; ++l) {
+            const int32_t other = __shfl(key[q], l, kSortLanes);
+#pragma unroll
+            for (int t = 0; t < Q; ++t)  // equal columns keep their order
+                rank[t] += other < key[t] || (other == key[t] && q * kSortLanes + l < t * kSortLanes + lane) ? 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+        if (lo + q * kSortLanes + lane < hi) {
+            r_col[lo + rank[q]] = key[q];
+            r_val[lo + rank[q]] = v[q];
+        }
+}
+
+__global__ __launch_bounds__(kBlock) void sort_rows_kernel(int32_t nc, const int32_t* __restrict__ r_ptr,
+                                                          int32_t* __restrict__ r_col, double* __restrict__ r_val) {
+    const int32_t c = blockIdx.x * (kBlock / kSortLanes) + threadIdx.x / kSortLanes;
     if (c >= nc) return;
+    const int lane = threadIdx.x % kSortLanes;
     const int32_t lo = r_ptr[c], hi = r_ptr[c + 1];
+    if (hi - lo <= kSortLanes) return rank_row<1>(lo, hi, lane, r_col, r_val);
+    if (hi - lo <= 4 * kSortLanes) return rank_row<4>(lo, hi, lane, r_col, r_val);
+    if (lane != 0) return;
     for (int32_t a = lo + 1; a < hi; ++a) {
         const int32_t key = r_col[a];
         const double v = r_val[a];
@@ -770,17 +807,11 @@ __global__ __launch_bounds__(kScanBlock) void halo_scan_kernel(int32_t nb, int32
 
 }  // namespace
 
-hipError_t extract_diag(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* diag,
-                        int32_t* bad, hipStream_t stream) {
-    if (n <= 0) return hipSuccess;
-    extract_diag_kernel<<<grid_for(n), kBlock, 0, stream>>>(n, ptr, col, val, diag, bad);
-    return hipGetLastError();
-}
-
-hipError_t offdiag_absmax(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* partial,
-                          double* scale, hipStream_t stream) {
-    absmax_partial_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, ptr, col, val, partial);
-    absmax_final_kernel<<<1, kBlock, 0, stream>>>(partial, scale);
+hipError_t diag_and_scale(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* diag,
+                          int32_t* bad, double* partial, double* scale, hipStream_t stream) {
+    const int blocks = n <= 0 ? 0 : std::min<int>(kReduceBlocks, (n + kBlock - 1) / kBlock);
+    if (blocks > 0) diag_absmax_kernel<<<blocks, kBlock, 0, stream>>>(n, ptr, col, val, diag, bad, partial);
+    absmax_final_kernel<<<1, kBlock, 0, stream>>>(partial, blocks, scale);
     return hipGetLastError();
 }
 
@@ -876,7 +907,8 @@ hipError_t transpose_csr(int32_t nf, int32_t nc, int32_t nnz, const int32_t* p_p
     inclusive_scan(nc, r_ptr, cursor, stream);  // piece sums live in `cursor`, which is free until the scatter below
     if ((e = vec_copy<int32_t>(nc, r_ptr, cursor, stream)) != hipSuccess) return e;
     scatter_transpose_kernel<<<grid_for(nf), kBlock, 0, stream>>>(nf, p_ptr, p_col, p_val, cursor, r_col, r_val);
-    sort_rows_kernel<<<grid_for(nc), kBlock, 0, stream>>>(nc, r_ptr, r_col, r_val);
+    const int rows = kBlock / kSortLanes;
+    if (nc > 0) sort_rows_kernel<<<(nc + rows - 1) / rows, kBlock, 0, stream>>>(nc, r_ptr, r_col, r_val);
     return hipGetLastError();
 }
 

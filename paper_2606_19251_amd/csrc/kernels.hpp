@@ -112,8 +112,22 @@ inline int32_t stream_cap_for(int32_t maxblk) {
     const int32_t c = (maxblk + kStreamRound - 1) / kStreamRound * kStreamRound;
     return c < kStreamRound ? kStreamRound : (c > kStreamCap ? kStreamCap : c);
 }
-// out[0] = max over row blocks of `rows` rows of the block's entries (out[0] must start at 0).
-hipError_t block_max_entries(int32_t nrows, const int32_t* ptr, int rows, int32_t* out, hipStream_t stream);
+// *out = max over row blocks of `rows` rows of the block's entries (*out must start at 0), for several
+// matrices in one launch: on most levels it takes less than the launch.
+struct BlockMax {
+    int32_t nrows;
+    int rows;
+    const int32_t* ptr;
+    int32_t* out;
+};
+struct BlockMaxList {
+    BlockMax item[6];
+    int n = 0;
+    void add(int32_t nrows, const int32_t* ptr, int rows, int32_t* out) {
+        if (nrows > 0 && rows > 0) item[n++] = {nrows, rows, ptr, out};
+    }
+};
+hipError_t block_max_entries(const BlockMaxList& list, hipStream_t stream);
 
 // Pack the columns of an nrows-row CSR matrix for row blocks of `rows` rows (a value of
 // stream_rows_for): off [nnz], base [blocks], foff [blocks + 1], and at most `cap` far entries
@@ -343,12 +357,10 @@ hipError_t stationary_finish(const double* partial, int count, double* s, hipStr
 // ---------------------------------------------------------------------------------------
 // Setup kernels
 // ---------------------------------------------------------------------------------------
-// diag[i] = a_ii; bad[0] set to 1 when a row has no positive stored diagonal
-hipError_t extract_diag(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* diag,
-                        int32_t* bad, hipStream_t stream);
-// scale[0] = max |a_ij| over off-diagonal entries, or 1 when there are none
-hipError_t offdiag_absmax(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* partial,
-                          double* scale, hipStream_t stream);
+// diag[i] = a_ii; bad[0] set to 1 when a row has no positive stored diagonal; scale[0] = max |a_ij| over
+// off-diagonal entries, or 1 when there are none. partial: kReduceBlocks values of scratch.
+hipError_t diag_and_scale(int32_t n, const int32_t* ptr, const int32_t* col, const double* val, double* diag,
+                          int32_t* bad, double* partial, double* scale, hipStream_t stream);
 // R = P^T (rows in ascending fine index): counts, scan, scatter, per-row sort; r_ptr has
 // n_c + 1 entries, cursor n_c + 1 entries of scratch
 hipError_t transpose_csr(int32_t nf, int32_t nc, int32_t nnz, const int32_t* p_ptr, const int32_t* p_col,

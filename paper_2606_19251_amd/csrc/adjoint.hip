@@ -315,9 +315,9 @@ struct Adj {
             ok(hipGetLastError());
             return out;
         }
-        dot_partial_kernel<T><<<kReduceBlocks, kBlock, 0, st>>>(n, a, b, c->adj_partial);
+        dot_partial_kernel<T><<<reduce_blocks(n), kBlock, 0, st>>>(n, a, b, c->adj_partial);
         ok(hipGetLastError());
-        ok(finish_sum(c->adj_partial, out, st));
+        ok(finish_sum(c->adj_partial, reduce_blocks(n), out, st));
         return out;
     }
 

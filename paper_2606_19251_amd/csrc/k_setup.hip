@@ -151,7 +151,7 @@ __global__ void scatter_transpose_kernel(int32_t nf, const int32_t* __restrict__
 // The scatter order within a row depends on atomics; sorting by column restores the one
 // exact transpose. kSortLanes lanes hold a row of up to 4 entries each and put every entry at its rank (the
 // row's entries passed by shuffles); a longer row is sorted in place by one lane. With one thread per row
-// throughout, the chain of dependent moves took 20 us a level however small; 5 us here.
+// throughout, the chain of dependent moves took 20 us a level however small; 4 to 7 us here.
 constexpr int kSortLanes = 16;
 
 // A row of at most Q kSortLanes entries [lo, hi).

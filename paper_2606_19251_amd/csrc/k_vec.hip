@@ -1,6 +1,6 @@
 // Streaming vector kernels, deterministic reductions and the scalar steps of the outer
-// FP64 loops. Reductions always use kReduceBlocks workgroups with a grid-stride loop and
-// a fixed combination tree, so every sum is bitwise reproducible from run to run.
+// FP64 loops. Reductions use reduce_blocks(n) workgroups with a grid-stride loop and a fixed
+// combination tree, so every sum is bitwise reproducible from run to run.
 #include <cmath>
 
 #include "kernels.hpp"
@@ -28,30 +28,52 @@ __device__ __forceinline__ void block_partial(double v, double* partial) {
     }
 }
 
-// Sum of `count` partials by one workgroup, in a fixed order.
-// Sum of count partials by one workgroup of kFinish threads: each thread keeps eight
-// independent accumulators (eight loads in flight) over a fixed strided subset, then a
-// fixed-order tree; the result does not depend on timing.
+// Sums of `count` partials of each of N arrays by one workgroup of kFinish threads, valid in its first thread:
+// each thread keeps eight independent accumulators (eight loads in flight) over a fixed strided subset, then
+// a fixed-order tree that halves the threads; the result does not depend on timing. The first wavefront
+// does the tree, its upper half from LDS and the rest by shuffles: one barrier instead of ten for
+// each array.
 constexpr int kFinish = 1024;
 
-__device__ __forceinline__ double sum_partials(const double* partial, int count = kReduceBlocks) {
-    __shared__ double red[kFinish];
-    double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    int k = threadIdx.x;
-    for (; k + 7 * kFinish < count; k += 8 * kFinish) {
+template <int N>
+__device__ __forceinline__ void sum_partials(const double* const (&in)[N], int count, double (&out)[N]) {
+    __shared__ double red[N][kFinish];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] += partial[k + q * kFinish];
+    for (int j = 0; j < N; ++j) {
+        const double* partial = in[j];
+        double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        int k = threadIdx.x;
+        for (; k + 7 * kFinish < count; k += 8 * kFinish) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += partial[k + q * kFinish];
+        }
+#pragma unroll
+        for (int q = 0; q < 7; ++q)
+            if (k + q * kFinish < count) v[q] += partial[k + q * kFinish];
+        red[j][threadIdx.x] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     }
-#pragma unroll
-    for (int q = 0; q < 7; ++q)
-        if (k + q * kFinish < count) v[q] += partial[k + q * kFinish];
-    red[threadIdx.x] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
     __syncthreads();
-    for (int w = kFinish / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x >= 64) return;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        constexpr int kWaves = kFinish / 64;
+        double v[kWaves];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) v[w] = red[j][threadIdx.x + 64 * w];
+#pragma unroll
+        for (int h = kWaves / 2; h > 0; h >>= 1)
+#pragma unroll
+            for (int w = 0; w < h; ++w) v[w] += v[w + h];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[0] += __shfl_down(v[0], off, 64);
+        out[j] = v[0];
     }
-    return red[0];
+}
+__device__ __forceinline__ double sum_partials(const double* partial, int count) {
+    const double* const in[1] = {partial};
+    double out[1] = {0.0};
+    sum_partials<1>(in, count, out);
+    return out[0];
 }
 
 template <typename T>
@@ -137,9 +159,9 @@ __global__ __launch_bounds__(kBlock) void partial_sum_kernel(int32_t n, const do
     block_partial(v, partial);
 }
 
-__global__ __launch_bounds__(kFinish) void finish_sum_kernel(const double* __restrict__ partial,
+__global__ __launch_bounds__(kFinish) void finish_sum_kernel(const double* __restrict__ partial, int count,
                                                            double* __restrict__ out) {
-    const double s = sum_partials(partial);
+    const double s = sum_partials(partial, count);
     if (threadIdx.x == 0) out[0] = s;
 }
 
@@ -239,12 +261,13 @@ __global__ __launch_bounds__(kBlock) void fcg_dots64_kernel(int32_t n, const dou
     block_partial(b, partial2 + kReduceBlocks);
 }
 
-__global__ __launch_bounds__(kFinish) void fcg_finish_beta_kernel(const double* __restrict__ partial2,
+__global__ __launch_bounds__(kFinish) void fcg_finish_beta_kernel(const double* __restrict__ partial2, int count,
                                                                 double* __restrict__ s, int first) {
-    const double zr = sum_partials(partial2);
-    __syncthreads();
-    const double zro = sum_partials(partial2 + kReduceBlocks);
+    const double* const in[2] = {partial2, partial2 + kReduceBlocks};
+    double sums[2] = {0.0, 0.0};
+    sum_partials<2>(in, count, sums);
     if (threadIdx.x == 0) {
+        const double zr = sums[0], zro = sums[1];
         s[kZR] = zr;
         s[kZRold] = zro;
         if (!(zr > 0.0)) s[kFlag] = 1.0;
@@ -411,17 +434,17 @@ hipError_t sub_mean(int32_t n, const double* x, const double* sum, double* y, hi
 }
 
 hipError_t partial_dot(int32_t n, const double* a, const double* b, double* partial, hipStream_t stream) {
-    partial_dot_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, a, b, partial);
+    partial_dot_kernel<<<reduce_blocks(n), kBlock, 0, stream>>>(n, a, b, partial);
     return hipGetLastError();
 }
 
 hipError_t partial_sum(int32_t n, const double* a, double* partial, hipStream_t stream) {
-    partial_sum_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, a, partial);
+    partial_sum_kernel<<<reduce_blocks(n), kBlock, 0, stream>>>(n, a, partial);
     return hipGetLastError();
 }
 
-hipError_t finish_sum(const double* partial, double* out, hipStream_t stream) {
-    finish_sum_kernel<<<1, kFinish, 0, stream>>>(partial, out);
+hipError_t finish_sum(const double* partial, int count, double* out, hipStream_t stream) {
+    finish_sum_kernel<<<1, kFinish, 0, stream>>>(partial, count, out);
     return hipGetLastError();
 }
 
@@ -433,7 +456,7 @@ hipError_t fcg_finish_pq(const double* partial, int count, double* s, hipStream_
 hipError_t fcg_update_xr(int32_t n, double* x, const double* p, const double* r, const double* q, double* rnew,
                          const double* s, double* partial, hipStream_t stream, const Cast32& cast) {
     if ((cast.qd == nullptr) != (cast.u == nullptr)) return hipErrorInvalidValue;
-    fcg_update_xr_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, x, p, r, q, rnew, s, partial, cast);
+    fcg_update_xr_kernel<<<reduce_blocks(n), kBlock, 0, stream>>>(n, x, p, r, q, rnew, s, partial, cast);
     return hipGetLastError();
 }
 
@@ -460,18 +483,18 @@ hipError_t stationary_set_iter(double* s, int iter, hipStream_t stream) {
 
 hipError_t fcg_castback_dots(int32_t n, const float* u32, const double* s, const double* rnew, const double* rold,
                              double* z, double* partial2, hipStream_t stream) {
-    fcg_castback_dots_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, u32, s, rnew, rold, z, partial2);
+    fcg_castback_dots_kernel<<<reduce_blocks(n), kBlock, 0, stream>>>(n, u32, s, rnew, rold, z, partial2);
     return hipGetLastError();
 }
 
 hipError_t fcg_dots64(int32_t n, const double* z, const double* rnew, const double* rold, double* partial2,
                       hipStream_t stream) {
-    fcg_dots64_kernel<<<kReduceBlocks, kBlock, 0, stream>>>(n, z, rnew, rold, partial2);
+    fcg_dots64_kernel<<<reduce_blocks(n), kBlock, 0, stream>>>(n, z, rnew, rold, partial2);
     return hipGetLastError();
 }
 
-hipError_t fcg_finish_beta(const double* partial2, double* s, int first, hipStream_t stream) {
-    fcg_finish_beta_kernel<<<1, kFinish, 0, stream>>>(partial2, s, first);
+hipError_t fcg_finish_beta(const double* partial2, int count, double* s, int first, hipStream_t stream) {
+    fcg_finish_beta_kernel<<<1, kFinish, 0, stream>>>(partial2, count, s, first);
     return hipGetLastError();
 }
 

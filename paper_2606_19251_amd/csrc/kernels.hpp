@@ -51,7 +51,14 @@ inline hipError_t launch_kernel_lds(void (*kernel)(KArgs...), dim3 grid, dim3 bl
 
 constexpr int kBlock = 256;         // threads per workgroup (4 wavefronts of 64)
 constexpr int kStreamCap = 4096;    // products a CSR-stream workgroup holds in LDS
-constexpr int kReduceBlocks = 1024; // fixed partial count: reductions are deterministic
+constexpr int kReduceBlocks = 1024; // most partials of a reduction
+// Workgroups (partials) of a reduction over n values: those beyond one value per thread would only write
+// zeros, which the sums already hold (with the finishing kernels' single barrier, an 8-iteration solve of a
+// 64 x 64 grid 486 -> 476 us, 13 iterations on 304k rows 2444 -> 2416).
+inline int reduce_blocks(int32_t n) {
+    const int b = static_cast<int>((static_cast<int64_t>(n) + kBlock - 1) / kBlock);
+    return b < 1 ? 1 : b < kReduceBlocks ? b : kReduceBlocks;
+}
 
 // ---------------------------------------------------------------------------------------
 // Row-wise CSR products y = epilogue(sum_j a_ij x_j); `lanes` threads cooperate on a row.
@@ -281,11 +288,11 @@ hipError_t cast_f32_f64(int32_t n, const float* x, double* y, hipStream_t stream
 // y = x - mean, mean = sum/n from a device scalar sum
 hipError_t sub_mean(int32_t n, const double* x, const double* sum, double* y, hipStream_t stream);
 
-// Deterministic two-stage reductions into partial[kReduceBlocks]
+// Deterministic two-stage reductions into partial[reduce_blocks(n)]
 hipError_t partial_dot(int32_t n, const double* a, const double* b, double* partial, hipStream_t stream);
 hipError_t partial_sum(int32_t n, const double* a, double* partial, hipStream_t stream);
-// final: scalars[out] = sum(partial[0..kReduceBlocks))
-hipError_t finish_sum(const double* partial, double* out, hipStream_t stream);  // kReduceBlocks partials
+// final: scalars[out] = sum(partial[0..count))
+hipError_t finish_sum(const double* partial, int count, double* out, hipStream_t stream);
 
 // FCG pieces; s = device scalars (see fcg_slot)
 enum FcgSlot : int {
@@ -331,12 +338,12 @@ hipError_t fcg_finish_pq(const double* partial, int count, double* s, hipStream_
 hipError_t fcg_update_xr(int32_t n, double* x, const double* p, const double* r, const double* q, double* rnew,
                          const double* s, double* partial, hipStream_t stream, const Cast32& cast = Cast32{});
 hipError_t fcg_finish_rr(const double* partial, int count, double* s, hipStream_t stream);  // rr, norm, invnorm
-// z = (double)u32 * s[kUnscale] (stored unless z is null) and partials of z.rnew, z.rold (2 * kReduceBlocks)
+// z = (double)u32 * s[kUnscale] (stored unless z is null) and partials of z.rnew, z.rold (at 0 and at kReduceBlocks)
 hipError_t fcg_castback_dots(int32_t n, const float* u32, const double* s, const double* rnew, const double* rold,
                              double* z, double* partial2, hipStream_t stream);
 hipError_t fcg_dots64(int32_t n, const double* z, const double* rnew, const double* rold, double* partial2,
                       hipStream_t stream);
-hipError_t fcg_finish_beta(const double* partial2, double* s, int first, hipStream_t stream);
+hipError_t fcg_finish_beta(const double* partial2, int count, double* s, int first, hipStream_t stream);
 hipError_t fcg_update_p(int32_t n, const double* z, double* p, const double* s, int first, hipStream_t stream);
 // p = z (+ beta p) with z = (double)u32 * s[kUnscale] formed in place, as fcg_castback_dots forms it
 hipError_t fcg_update_p32(int32_t n, const float* u32, double* p, const double* s, int first, hipStream_t stream);

@@ -91,7 +91,7 @@ struct Runner {
         } else {
             ok(fcg_dots64(n, z, cur, first ? nullptr : prev, c->partial2, st));
         }
-        ok(fcg_finish_beta(c->partial2, s, first ? 1 : 0, st));
+        ok(fcg_finish_beta(c->partial2, reduce_blocks(n), s, first ? 1 : 0, st));
         if (prec == 32)
             ok(fcg_update_p32(n, last32, c->p, s, first ? 1 : 0, st));
         else
@@ -107,7 +107,7 @@ struct Runner {
             cs.u = ready ? L0.u32 : nullptr;
         }
         ok(fcg_update_xr(n, x, c->p, cur, c->q, prev, s, c->partial, st, cs));
-        ok(fcg_finish_rr_guarded(c->partial, kReduceBlocks, s, st));
+        ok(fcg_finish_rr_guarded(c->partial, reduce_blocks(n), s, st));
     }
 
     // Iterative refinement: x += V(0, r); r = b - A x. FP32 cycles take r scaled by a power of two
@@ -223,7 +223,7 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         const double* bb = b;
         if (c->singular) {
             R.ok(partial_sum(n, b, c->partial, st));
-            R.ok(finish_sum(c->partial, s + kSum, st));
+            R.ok(finish_sum(c->partial, reduce_blocks(n), s + kSum, st));
             R.ok(sub_mean(n, b, s + kSum, c->bproj, st));
             bb = c->bproj;
         }
@@ -231,7 +231,7 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         R.ok(vec_zero_bytes(x, sizeof(double) * n, st));
         R.ok(vec_copy<double>(n, bb, c->ra, st));
         R.ok(partial_dot(n, bb, bb, c->partial, st));
-        R.ok(fcg_finish_rr(c->partial, kReduceBlocks, s, st));
+        R.ok(fcg_finish_rr(c->partial, reduce_blocks(n), s, st));
         if (!R.read_scalars(st)) return hip_fail(R.e, "amgg_solve");
         const double nb = std::sqrt(hs[kRR]);
         std::vector<double> hist{1.0};

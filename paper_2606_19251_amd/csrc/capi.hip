@@ -45,7 +45,7 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
     Bump b{base};
     c->nblk = c->lv[0].nblk;
     int32_t max_nc = 1;
-    int32_t max_chunks = 1;
+    size_t chunks = 0;  // of all levels
     for (int l = 0; l < c->nlevels; ++l) {
         Level& L = c->lv[l];
         const size_t n = L.n, z = L.nnz;
@@ -139,7 +139,7 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
             L.blk_scale = b.take<double>(L.nblk);
             L.chunk_row = b.take<int32_t>(L.nchunk() + 1);
             L.blk_chunk = b.take<int32_t>(L.nblk + 1);
-            max_chunks = std::max(max_chunks, L.nchunk());
+            chunks += L.nchunk();
         }
         for (int k = 0; k < kAdjVecs; ++k) {
             L.adj64[k] = b.take<double>(n);
@@ -165,7 +165,7 @@ size_t layout(amgg_ctx* c, uintptr_t base) {
     c->adj_f32 = b.take<float>(n0);
     if (c->nblk > 0) {
         c->blk_scal = b.take<double>(4 * static_cast<size_t>(c->nblk));
-        c->blk_partial = b.take<double>(static_cast<size_t>(kMaxCoef) * max_chunks);
+        c->blk_partial = b.take<double>(kAdjSteps * kMaxCoef * std::max<size_t>(chunks, 1));
     }
     return (b.off + 255) & ~static_cast<size_t>(255);
 }
@@ -476,7 +476,14 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
             }
         }
         Level& Lc = c->lv[c->nlevels - 1];
+        c->crow_shared = false;
         if (c->nblk > 0) {
+            std::vector<int32_t> rows;
+            for (int l = 0; l < c->nlevels; ++l)
+                for (int32_t r : c->lv[l].blk_crow_h)
+                    if (r >= 0) rows.push_back(r);
+            std::sort(rows.begin(), rows.end());
+            c->crow_shared = std::adjacent_find(rows.begin(), rows.end()) != rows.end();
             auto up = [&](void* dst, const void* src, size_t bytes) {
                 ok(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
             };

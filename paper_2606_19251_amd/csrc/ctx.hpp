@@ -159,6 +159,10 @@ enum AdjVec : int {
     kAdjVecs = 7
 };
 
+// Smoothing steps of a level whose partial sums the adjoint of a block-diagonal hierarchy keeps until it
+// adds them up.
+constexpr int kAdjSteps = 4;
+
 // Places in setup_out, 3 values per level (A, P, R): largest row block (first), longest row and far entries of
 // the packing; then the two results of halo_lists per level.
 constexpr int kSetupLongest = 3 * AMGG_MAX_LEVELS;
@@ -199,7 +203,8 @@ struct amgg_ctx {
     // block-diagonal contexts (every level split into nblk blocks)
     int32_t nblk = 0;
     double* blk_scal = nullptr;     // per-block loss scalars, 4 x nblk
-    double* blk_partial = nullptr;  // per-chunk partial sums, kMaxCoef x (most chunks of a level)
+    double* blk_partial = nullptr;  // per-chunk partial sums, kAdjSteps x kMaxCoef x (chunks of all levels)
+    bool crow_shared = false;       // a coefficient row belongs to several blocks or levels
 };
 
 namespace amgg {

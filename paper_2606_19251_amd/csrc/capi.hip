@@ -262,7 +262,7 @@ hipError_t vcycle_level(amgg_ctx* c, int l, const T* f, T* u, T* t, bool zero, i
     Level& C = c->lv[l + 1];
     // the restriction also forms the coarse level's first smoothing step where that is diagonal
     const bool ready = takes_ready_u(c, l + 1, nu1);
-    const bool down = !still_zero && !have_r && L.pairs();
+    const bool down = !still_zero && !have_r && L.smoother == kSmootherDiagonal && L.pairs();
     const T* res = f;
     if (!still_zero && have_r) {
         res = r;
@@ -585,7 +585,9 @@ extern "C" int amgg_finalize(amgg_ctx* c, int singular, void* workspace, size_t 
                 w[k] = std::max(4, (longest[k] + 3) / 4 * 4);
                 fit = fit && w[k] <= pads[k]->cap;
             }
-            if (!fit || static_cast<int64_t>(L.n) * w[0] > kPairMaxSlots) continue;
+            if (!fit || static_cast<int64_t>(L.n) * w[0] > kPairMaxSlots ||
+                static_cast<int64_t>(L.nc) * w[2] * w[0] > kPairMaxWork)
+                continue;
             ok(pad_rows(L.n, w[0], L.ptr, L.col, L.val, L.pad_a.col, L.pad_a.v64, L.pad_a.v32, st));
             ok(pad_rows(L.n, w[1], L.pptr, L.pcol, L.pval, L.pad_p.col, L.pad_p.v64, L.pad_p.v32, st));
             ok(pad_rows(L.nc, w[2], L.rptr, L.rcol, L.rval, L.pad_r.col, L.pad_r.v64, L.pad_r.v32, st));

@@ -232,7 +232,16 @@ hipError_t jacobi_pre_step(const CsrView& m, const T* a, const T* d, const T* f,
 // Measured per V-cycle, the four separate passes of a level against the two pairs, us: 1.1k rows of 13
 // entries 12.5 / 8.1, 4.9k 14.2 / 8.6, 21k (w = 24) 14.7 / 13.4; beyond, the pairs' repeated work shows:
 // 24k rows (w = 32) 14.9 / 15.9, 11k rows with some of 60 entries (w = 64) 14.8 / 15.4, 91k 21.3 / 30.
+// A restriction forms the residual of every entry of R's padded rows, so the two widths count together: levels
+// of more than kPairMaxWork such products keep the separate passes, whose matrix is smaller and stays in
+// cache. Whole solves, us, with the pairs by kPairMaxSlots alone, with this limit, without pairs: 59k-row
+// triangulation 5730 / 5248 / 5338, 64k tetrahedral cells (levels of 1.1M products) 2249 / 2081 / 2079, 12k-row
+// triangulation (0.4M) 1457 / 1479 / 1749, 11k-cell layer mesh (0.4M) 1320 / 1319 / 1523, 64 x 64 grid (0.13M)
+// 469 / 478 / 577; with the limit at 0.25M the 12k-row one takes 1661.
+// Both pairs are for diagonal smoothing steps: around the sparse smoother's fused step the restriction's alone
+// lost (64k tetrahedral cells 2936, without 2759).
 constexpr int64_t kPairMaxSlots = 1 << 19;
+constexpr int64_t kPairMaxWork = 1 << 20;
 constexpr int32_t kPairMaxRows = 32768;
 constexpr int kPairMaxWidthA = 64;
 constexpr int kPairMaxWidthR = 32;

@@ -247,6 +247,9 @@ typedef struct {
     int32_t stream_cap[3];
 } amgg_level_view;
 int amgg_level_view_get(const amgg_ctx* ctx, int lvl, amgg_level_view* out);
+/* Number of captured solve graphs the context keeps (diagnostics and tests; see
+ * amgg_solve_opts.graphs). Errors: AMGG_EINVAL (NULL). */
+int amgg_kept_graphs(const amgg_ctx* ctx, int* count);
 /* Copy level lvl's FP64 smoother values Q^-1 (nnz entries on A_l's pattern, as assembled from
  * Eq. 5; Sec. 3.1) into the caller's device buffer q_out (nnz doubles), ordered on `stream`.
  * Errors: AMGG_EINVAL (bad level or NULL), AMGG_ESTATE (not finalized or no smoother set). */

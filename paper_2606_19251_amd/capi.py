@@ -122,6 +122,7 @@ SIGNATURES = {
     "amgg_level_apply": (_I, [_VP, _I, _I, _I, _VP, _VP, _VP, _VP]),
     "amgg_set_fusion": (_I, [_VP, _I]),
     "amgg_set_packed_columns": (_I, [_VP, _I]),
+    "amgg_kept_graphs": (_I, [_VP, C.POINTER(_I)]),
     "amgg_level_apply_timed": (_I, [_VP, _I, _I, _I, _VP, _VP, _VP, _VP, _VP, _VP]),
     "amgg_solve": (_I, [_VP, C.POINTER(amgg_solve_opts), _VP, _VP, C.POINTER(amgg_solve_info), _VP, _I, _VP]),
     "amgg_judge_smoother": (_I, [_VP, C.POINTER(amgg_solve_opts), _I, _I, _VP, _I, _VP, _VP,
@@ -444,6 +445,12 @@ def amgg_set_packed_columns(ctx, mode):
 
 def amgg_set_fusion(ctx, enable):
     return _check(lib().amgg_set_fusion(ctx, int(enable)), "amgg_set_fusion")
+
+
+def amgg_kept_graphs(ctx) -> int:
+    count = _I()
+    _check(lib().amgg_kept_graphs(ctx, C.byref(count)), "amgg_kept_graphs")
+    return count.value
 
 
 def amgg_level_apply_timed(ctx, lvl, op, precision, x, y, f, start_event, stop_event, stream):

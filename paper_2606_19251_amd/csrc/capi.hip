@@ -617,6 +617,12 @@ extern "C" int amgg_set_packed_columns(amgg_ctx* c, int mode) {
     return AMGG_OK;
 }
 
+extern "C" int amgg_kept_graphs(const amgg_ctx* c, int* count) {
+    if (!c || !count) return fail(AMGG_EINVAL, "amgg_kept_graphs: null argument");
+    *count = static_cast<int>(c->graphs.size());
+    return AMGG_OK;
+}
+
 extern "C" int amgg_level_view_get(const amgg_ctx* c, int lvl, amgg_level_view* v) {
     if (!c || !v || lvl < 0 || lvl >= c->nlevels) return fail(AMGG_EINVAL, "amgg_level_view_get: bad argument");
     if (!c->finalized) return fail(AMGG_ESTATE, "amgg_level_view_get: hierarchy not finalized");

@@ -219,12 +219,16 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         double* hs = c->host_scal;
         int vcycles = 0;
 
-        // right-hand side, projected to zero mean for a singular (all-Neumann) hierarchy
+        // right-hand side, projected to zero mean for a singular (all-Neumann) hierarchy; the stationary
+        // iteration takes a copy, so that its graphs know no address of the caller's
         const double* bb = b;
         if (c->singular) {
             R.ok(partial_sum(n, b, c->partial, st));
             R.ok(finish_sum(c->partial, reduce_blocks(n), s + kSum, st));
             R.ok(sub_mean(n, b, s + kSum, c->bproj, st));
+            bb = c->bproj;
+        } else if (o->outer == AMGG_OUTER_STATIONARY) {
+            R.ok(vec_copy<double>(n, b, c->bproj, st));
             bb = c->bproj;
         }
         R.ok(vec_zero_bytes(s, sizeof(double) * kSlots, st));

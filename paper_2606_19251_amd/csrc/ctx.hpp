@@ -20,6 +20,11 @@ constexpr int kMaxCoef = 2 * AMGG_MAX_DEGREE + 1;
 // Outer iterations of a solve enqueued at once (the one the host inspects and those behind it), so
 // that a host thread late by up to kPipeline - 1 iterations leaves no gap on the stream.
 constexpr int kPipeline = 3;
+// Captured iterations a context keeps. Those of refinement and flexible CG hold the addresses of the caller's x
+// (and b), so a program with new tensors per solve makes new ones: beyond this many the one unused for the
+// longest goes. A solve launches at most three in turn (flexible CG: the first iteration and the two
+// places of the residual), times the smoother forms and cycles a program alternates between.
+constexpr size_t kKeptGraphs = 32;
 
 struct Level {
     bool loaded = false, p_loaded = false;
@@ -186,8 +191,10 @@ struct amgg_ctx {
     struct Graph {
         std::string key;
         hipGraphExec_t exec;
+        int64_t used;  // graph_uses at its last launch
     };
-    std::vector<Graph> graphs;  // captured outer-iteration bodies
+    std::vector<Graph> graphs;  // captured outer-iteration bodies, at most kKeptGraphs
+    int64_t graph_uses = 0;
     // workspace
     double* scal = nullptr;
     double* partial = nullptr;

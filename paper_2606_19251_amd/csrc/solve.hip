@@ -165,7 +165,10 @@ hipError_t run_body(amgg_ctx* c, bool use_graph, const std::string& key, hipStre
         return R.e;
     }
     for (auto& g : c->graphs)
-        if (g.key == key) return hipGraphLaunch(g.exec, st);
+        if (g.key == key) {
+            g.used = ++c->graph_uses;
+            return hipGraphLaunch(g.exec, st);
+        }
     hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     body(c->cap_stream);
@@ -180,7 +183,18 @@ hipError_t run_body(amgg_ctx* c, bool use_graph, const std::string& key, hipStre
     e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     if (e != hipSuccess) return e;
-    c->graphs.push_back({key, exec});
+    if (c->graphs.size() >= kKeptGraphs) {
+        // its launches by earlier solves have ended with them, those of this one are on st
+        auto old = std::min_element(c->graphs.begin(), c->graphs.end(),
+                                    [](const auto& a, const auto& b) { return a.used < b.used; });
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) {
+            (void)hipGraphExecDestroy(exec);
+            return e;
+        }
+        (void)hipGraphExecDestroy(old->exec);
+        c->graphs.erase(old);
+    }
+    c->graphs.push_back({key, exec, ++c->graph_uses});
     return hipGraphLaunch(exec, st);
 }
 

@@ -769,8 +769,9 @@ __global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kern
     const int cc = c4 + reduced_channel<G>();
     const double t1 = reduce_groups<G>(s1), t2 = reduce_groups<G>(s2), tp = reduce_groups<G>(ps);
     reduce_groups_max<G>(mx, am);
-    // each group of HD lanes puts its partials where its rows of the tile were; the first adds them
-    // up in order
+    // each group of HD lanes puts its partials where its rows of the tile were, once all its lanes have read
+    // them; the first adds them up in order
+    wave_sync();
     auto part = [&](int k) { return reinterpret_cast<double*>(&Hs[16 * k][0]); };
     static_assert(16 * LD * sizeof(float) >= HD * (3 * sizeof(double) + sizeof(float) + sizeof(int32_t)), "they fit");
     {

@@ -3,13 +3,14 @@
 // interpolation from a given C/F split (the split itself, a sequential greedy, stays on the
 // host) and the Galerkin product A_c = R (A P) with R = P^T.
 //
-// A sparse product C = L * M is formed row by row in LDS: a group of 8 to 256 threads holds row i of C in
-// a hash table (one kernel counts the entries of each row, a second fills them), takes the entries L_ij
-// in ascending column order and adds L_ij M_jk for all k of row j at once, every entry starting
-// from 0.0, with product and sum rounded separately; the columns are then ranked. That is the row-by-row
-// accumulation of the host product, so the values are the host's bit for bit. Rows are served by the
-// table size their product count needs, each class by a launch of its own.
-// Rows of more than kHashMax products (a hub row), more than 2^31 - 1 products in all, or a bound on the
+// A sparse product C = L * M is formed row by row in LDS (one kernel counts the entries of each row, a second
+// fills them). A group of 8 to 64 threads holds row i of C in a hash table, takes the entries L_ij in
+// ascending column order and adds L_ij M_jk for all k of row j at once, every entry starting
+// from 0.0, with product and sum rounded separately; the columns are then ranked. A row of more than 1024
+// products is a workgroup's, which sorts the products by column and adds each column's in the same
+// order. That is the row-by-row accumulation of the host product, so the values are the host's bit for
+// bit. Rows are served by the size their product count needs, each class by a launch of its own.
+// Rows of more than kRowMax products (a hub row), more than 2^31 - 1 products in all, or a bound on the
 // expansion asked for by the caller take the expanding form:
 //   symbolic  every product L_ij M_jk is expanded to a key (row i, column k); one radix sort
 //             of the keys and a unique pass give C's pattern (rows in order, columns
@@ -435,17 +436,20 @@ void exclusive_scan_i32(Pool& pool, const T* in, int32_t* out, int64_t count, hi
 }
 
 // ---------------------------------------------------------------------------------------
-// Row-wise product in LDS hash tables
+// Row-wise product in LDS
 // ---------------------------------------------------------------------------------------
-// Classes of rows by their products (at most the table's slots, so that a table never overflows):
-// threads per row and slots.
-constexpr int kClasses = 4;
-constexpr int kClassThreads[kClasses] = {8, 16, 64, 256};
-constexpr int kClassSlots[kClasses] = {32, 128, 1024, 8192};
-constexpr int kHashMax = kClassSlots[kClasses - 1];
+// Classes of rows by their products: threads per row and most products. The first kHashClasses hold the row in
+// a hash table with a slot for every product (so that it never overflows), the others sort the products.
+constexpr int kClasses = 5, kHashClasses = 3;
+constexpr int kClassThreads[kClasses] = {8, 16, 64, 256, 1024};
+constexpr int kClassSlots[kClasses] = {32, 128, 1024, 2048, 8192};
+constexpr int kRowMax = kClassSlots[kClasses - 1];
 
-// nprod[i] = products of row i; per class the number of its rows; [kClasses]: rows beyond the classes,
-// [kClasses + 1]: all products.
+// nprod[i] = products of row i (some number above kRowMax where there are more); per class the number of its
+// rows; [kClasses]: rows beyond the classes, [kClasses + 1]: all products. A thread per row; rows of more than
+// kAlone entries are counted by the wavefront and only until they exceed kRowMax (a hub row of 20,000
+// entries took its thread 2.7 ms).
+constexpr int kAlone = 64;
 __global__ __launch_bounds__(kThreads) void row_products_kernel(int32_t n, const int32_t* __restrict__ lptr,
                                                                const int32_t* __restrict__ lcol,
                                                                const int32_t* __restrict__ mptr,
@@ -455,26 +459,44 @@ __global__ __launch_bounds__(kThreads) void row_products_kernel(int32_t n, const
     if (threadIdx.x < kClasses + 2) sums[threadIdx.x] = 0;
     __syncthreads();
     const int32_t i = blockIdx.x * kThreads + threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int32_t pb = i < n ? lptr[i] : 0, ne = i < n ? lptr[i + 1] - pb : 0;
     int64_t c = 0;
-    if (i < n) {
-        for (int32_t p = lptr[i]; p < lptr[i + 1]; ++p) {
-            const int32_t j = lcol[p];
+    if (ne <= kAlone)
+        for (int32_t e = 0; e < ne; ++e) {
+            const int32_t j = lcol[pb + e];
             c += mptr[j + 1] - mptr[j];
         }
-        nprod[i] = static_cast<int32_t>(c < INT32_MAX ? c : INT32_MAX);
+    for (uint64_t rows = __builtin_amdgcn_ballot_w64(ne > kAlone); rows; rows &= rows - 1) {
+        const int l = __builtin_ctzll(rows);
+        const int32_t b = __builtin_amdgcn_readlane(pb, l), m = __builtin_amdgcn_readlane(ne, l);
+        constexpr int kAhead = 4;
+        int64_t sum = 0;
+        for (int32_t e0 = 0; e0 < m && sum <= kRowMax; e0 += kAhead * 64) {
+            int64_t v = 0;
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int32_t e = e0 + q * 64 + lane, j = lcol[b + min(e, m - 1)];
+                v += e < m ? mptr[j + 1] - mptr[j] : 0;
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            sum += v;
+        }
+        if (lane == l) c = sum;
     }
+    if (i < n) nprod[i] = static_cast<int32_t>(c < INT32_MAX ? c : INT32_MAX);
     int cls = 0;
     while (cls < kClasses && c > kClassSlots[cls]) ++cls;
     // one LDS update per wavefront and value (64 lanes on one address take turns)
-    const bool first = (threadIdx.x & 63) == 0;
 #pragma unroll
     for (int k = 0; k <= kClasses; ++k) {
         const uint64_t m = __builtin_amdgcn_ballot_w64(c > 0 && cls == k);
-        if (first && m) atomicAdd(&sums[k], static_cast<unsigned long long>(__popcll(m)));
+        if (lane == 0 && m) atomicAdd(&sums[k], static_cast<unsigned long long>(__popcll(m)));
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-    if (first && c) atomicAdd(&sums[kClasses + 1], static_cast<unsigned long long>(c));
+    if (lane == 0 && c) atomicAdd(&sums[kClasses + 1], static_cast<unsigned long long>(c));
     __syncthreads();
     if (threadIdx.x < kClasses + 2 && sums[threadIdx.x]) atomicAdd(stats + threadIdx.x, sums[threadIdx.x]);
 }
@@ -504,81 +526,68 @@ __global__ __launch_bounds__(kThreads) void classify_rows_kernel(int32_t n, cons
     if (cls < kClasses) lists.rows[cls][at[cls] + pos] = i;
 }
 
-// Orders the LDS accesses of a group: a barrier where the group is a workgroup, else the group lies within
-// a wavefront, whose LDS accesses are in order.
-template <int G>
+// Orders the LDS accesses of a group of lanes of one wavefront, whose LDS accesses are in order.
 __device__ __forceinline__ void group_sync() {
-    if constexpr (G > 64) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Row i of C = L M (i one of the `count` listed rows, or of the first `count`) by G threads in a table of S slots. FILL: writes the
-// row's columns and values at cptr[i]; else its entry count. zeros: set to 1 if an exact zero is
-// written off the diagonal.
-// Bound by latency: an entry of L costs its row bounds of M, its row and the table. The row bounds of G
-// entries of L are loaded together and an entry's row of M while the one before it is added.
+// What the row kernels take: rows of C = L M (the listed ones, or the first `count`). FILL: a row's columns and
+// values are written at cptr[i]; else its entry count. zeros: set to 1 if an exact zero is written off
+// the diagonal.
+struct RowProducts {
+    int32_t count;
+    const int32_t* rows;
+    const int32_t *lptr, *lcol;
+    const double* lval;
+    const int32_t *mptr, *mcol;
+    const double* mval;
+    int32_t* cnt;
+    const int32_t* cptr;
+    int32_t* ccol;
+    double* cval;
+    int32_t* zeros;
+};
+
+// A row by G lanes in a table of S slots. Bound by latency: an entry of L costs its row bounds of M, its row and
+// the table. The row bounds of G entries of L are loaded together and an entry's row of M while the one
+// before it is added.
 template <int G, int S, bool FILL>
-__global__ __launch_bounds__(kThreads) void row_hash_kernel(
-    int32_t count, const int32_t* __restrict__ rows, const int32_t* __restrict__ lptr,
-    const int32_t* __restrict__ lcol, const double* __restrict__ lval, const int32_t* __restrict__ mptr,
-    const int32_t* __restrict__ mcol, const double* __restrict__ mval, int32_t* __restrict__ cnt,
-    const int32_t* __restrict__ cptr, int32_t* __restrict__ ccol, double* __restrict__ cval,
-    int32_t* __restrict__ zeros) {
+__global__ __launch_bounds__(kThreads) void row_hash_kernel(RowProducts a) {
     constexpr int kRows = kThreads / G;
-    constexpr int kVals = FILL ? S : 1;
-    __shared__ int32_t keys[kRows][S];
-    __shared__ double vals[kRows][kVals];
-    __shared__ uint16_t list[FILL ? kRows : 1][FILL ? S : 1];
-    __shared__ int32_t tl[G > 64 ? 3 : 1][G > 64 ? G : 1];  // a workgroup-wide group's exchange
-    __shared__ double tv[G > 64 ? G : 1];
+    __shared__ __align__(16) int32_t keys[kRows][S];
+    __shared__ double vals[kRows][FILL ? S : 1];
     const int g = threadIdx.x / G, t = threadIdx.x % G;
-    const bool mine = static_cast<int32_t>(blockIdx.x) * kRows + g < count;  // uniform over the group
     const int32_t at = static_cast<int32_t>(blockIdx.x) * kRows + g;
-    const int32_t i = !mine ? 0 : rows ? rows[at] : at;
+    const bool mine = at < a.count;  // uniform over the group
+    const int32_t i = !mine ? 0 : a.rows ? a.rows[at] : at;
     int32_t* const key = keys[g];
     double* const val = FILL ? vals[g] : nullptr;
     for (int k = t; k < S; k += G) {
         key[k] = -1;
         if constexpr (FILL) val[k] = 0.0;
     }
-    group_sync<G>();
-    const int32_t pb = mine ? lptr[i] : 0, pe = mine ? lptr[i + 1] : 0;
-    for (int32_t p0 = pb; p0 < pe; p0 += G) {
+    group_sync();
+    const int32_t pb = mine ? a.lptr[i] : 0, np = mine ? a.lptr[i + 1] - pb : 0;
+    for (int32_t e0 = 0; e0 < np; e0 += G) {
         // the next G entries of L, one per thread
-        const int32_t p = min(p0 + t, pe - 1);
-        const int32_t j = lcol[p];
-        const int32_t mb0 = mptr[j], me0 = mptr[j + 1];
-        const double lv0 = FILL ? lval[p] : 0.0;
-        if constexpr (G > 64) {
-            __syncthreads();
-            tl[0][t] = mb0;
-            tl[1][t] = me0;
-            tv[t] = lv0;
-            __syncthreads();
-        }
+        const int32_t p = pb + min(e0 + t, np - 1);
+        const int32_t j = a.lcol[p];
+        const int32_t mb0 = a.mptr[j], me0 = a.mptr[j + 1];
+        const double lv0 = FILL ? a.lval[p] : 0.0;
         auto bounds = [&](int e, int32_t& b, int32_t& x, double& v) {
-            if constexpr (G > 64) {
-                b = tl[0][e];
-                x = tl[1][e];
-                v = tv[e];
-            } else {
-                b = __shfl(mb0, e, G);
-                x = __shfl(me0, e, G);
-                v = FILL ? __shfl(lv0, e, G) : 0.0;
-            }
+            b = __shfl(mb0, e, G);
+            x = __shfl(me0, e, G);
+            v = FILL ? __shfl(lv0, e, G) : 0.0;
         };
-        const int32_t ne = min(pe - p0, G);
+        const int32_t ne = min(np - e0, G);
         int32_t b, x, kn = 0;
         double lv, vn = 0.0;
         bounds(0, b, x, lv);
-        if (b + t < x) {
-            kn = mcol[b + t];
-            if constexpr (FILL) vn = mval[b + t];
+        if (t < x - b) {
+            kn = a.mcol[b + t];
+            if constexpr (FILL) vn = a.mval[b + t];
         }
         for (int e = 0; e < ne; ++e) {
             const int32_t bc = b, xc = x;
@@ -587,15 +596,15 @@ __global__ __launch_bounds__(kThreads) void row_hash_kernel(
             double m = vn;
             if (e + 1 < ne) {
                 bounds(e + 1, b, x, lv);
-                if (b + t < x) {
-                    kn = mcol[b + t];
-                    if constexpr (FILL) vn = mval[b + t];
+                if (t < x - b) {
+                    kn = a.mcol[b + t];
+                    if constexpr (FILL) vn = a.mval[b + t];
                 }
             }
-            for (int32_t q = bc + t; q < xc; q += G) {
-                if (q != bc + t) {
-                    k = mcol[q];
-                    if constexpr (FILL) m = mval[q];
+            for (int32_t q = t; q < xc - bc; q += G) {
+                if (q != t) {
+                    k = a.mcol[bc + q];
+                    if constexpr (FILL) m = a.mval[bc + q];
                 }
                 unsigned int s = static_cast<unsigned int>(k) * 2654435769u >> (32 - __builtin_ctz(S));
                 for (;;) {  // ends: the table has a slot for every product
@@ -605,68 +614,170 @@ __global__ __launch_bounds__(kThreads) void row_hash_kernel(
                 }
                 if constexpr (FILL) val[s] = val[s] + lc * m;  // no other thread has column k in this step
             }
-            group_sync<G>();
+            group_sync();
         }
     }
-    // entries of the row
+    // entries of the row, moved to the front of the table: a round's entries go to places that it or an
+    // earlier round has read
+    const int sh = threadIdx.x & 63 & ~(G - 1);
+    const uint64_t gm = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
     int32_t u = 0;
-    if constexpr (G > 64) {
-        for (int k0 = 0; k0 < S; k0 += G) {
-            const bool in = key[k0 + t] >= 0;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in);
-            if ((t & 63) == 0) tl[2][t / 64] = __popcll(m);
-            __syncthreads();
-            int32_t before = u;
-            for (int w = 0; w < t / 64; ++w) before += tl[2][w];
-            if constexpr (FILL)
-                if (in) list[g][before + __popcll(m & ((1ull << (t & 63)) - 1))] = static_cast<uint16_t>(k0 + t);
-            for (int w = 0; w < G / 64; ++w) u += tl[2][w];
-            __syncthreads();
+    for (int k0 = 0; k0 < S; k0 += G) {
+        const int32_t k = key[k0 + t];
+        const uint64_t m = __builtin_amdgcn_ballot_w64(k >= 0) >> sh & gm;
+        if constexpr (FILL) {
+            const double v = val[k0 + t];
+            group_sync();
+            if (k >= 0) {
+                const int to = u + __popcll(m & ((1ull << t) - 1));
+                key[to] = k;
+                val[to] = v;
+            }
+            group_sync();
         }
-    } else {
-        const int sh = threadIdx.x & 63 & ~(G - 1);
-        const uint64_t gm = G == 64 ? ~0ull : (1ull << (G & 63)) - 1;
-        for (int k0 = 0; k0 < S; k0 += G) {
-            const bool in = key[k0 + t] >= 0;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(in) >> sh & gm;
-            if constexpr (FILL)
-                if (in) list[g][u + __popcll(m & ((1ull << t) - 1))] = static_cast<uint16_t>(k0 + t);
-            u += __popcll(m);
-        }
+        u += __popcll(m);
     }
     if constexpr (!FILL) {
-        if (t == 0 && mine) cnt[i] = u;
+        if (t == 0 && mine) a.cnt[i] = u;
     } else {
-        group_sync<G>();
+        if (t < (4 - u % 4) % 4) key[u + t] = INT32_MAX;
+        group_sync();
         if (!mine) return;
-        const int32_t base = cptr[i];
+        // an entry's place is the number of smaller columns, four per read (broadcast) of the table
+        const int32_t base = a.cptr[i];
         bool zero = false;
         for (int32_t r = t; r < u; r += G) {
-            const int s = list[g][r];
-            const int32_t k = key[s];
+            const int32_t k = key[r];
             int32_t rank = 0;
-            for (int32_t q = 0; q < u; ++q) rank += key[list[g][q]] < k ? 1 : 0;
-            const double v = val[s];
-            ccol[base + rank] = k;
-            cval[base + rank] = v;
+            for (int32_t q = 0; q < u; q += 4) {
+                const int4 o = *reinterpret_cast<const int4*>(key + q);
+                rank += (o.x < k) + (o.y < k) + (o.z < k) + (o.w < k);
+            }
+            const double v = val[r];
+            a.ccol[base + rank] = k;
+            a.cval[base + rank] = v;
             zero = zero || (v == 0.0 && k != i);
         }
-        if (zero && zeros) *zeros = 1;
+        if (zero && a.zeros) *a.zeros = 1;
     }
 }
 
-template <bool FILL, typename... Args>
-void launch_row_hash(const unsigned long long* rows, const ClassLists& lists, hipStream_t st, Args... args) {
+// A long row by a workgroup of T threads, at most S products: its products are laid out in LDS in their order
+// (the threads find a product's entry of L by bisection in the scanned lengths), sorted by (column, place), and
+// each column's are added from its first to its last. All threads work whatever the lengths of the rows of
+// M; a table takes one entry of L after the other, two products at a time where M is a prolongation, and
+// ranks by the square of the row's entries. Whole call, ms, with tables of 8192 slots, sorted and
+// expanding: a 90k-row grid with a hub of 3900 neighbours 15.1 / 1.6 / 5.1, with 40 of them 15.9 / 1.6 / 6.2,
+// 1500 rows of 700 entries 3.5 / 1.7 / 2.9.
+template <int T, int S, bool FILL>
+__global__ __launch_bounds__(T) void row_sort_kernel(RowProducts a) {
+    static_assert(S <= 1 << 16, "places take 16 bits of a key");
+    __shared__ uint64_t keys[S];
+    __shared__ double vals[FILL ? S : 1];
+    __shared__ int32_t ends[T], begs[T], wsum[T / 64];
+    __shared__ double lvals[FILL ? T : 1];
+    const int t = threadIdx.x;
+    const int32_t i = a.rows ? a.rows[blockIdx.x] : static_cast<int32_t>(blockIdx.x);
+    const int32_t pb = a.lptr[i], np = a.lptr[i + 1] - pb;
+    int32_t total = 0;
+    for (int32_t e0 = 0; e0 < np; e0 += T) {
+        int32_t len = 0, incl;
+        if (e0 + t < np) {
+            const int32_t j = a.lcol[pb + e0 + t], b = a.mptr[j];
+            len = a.mptr[j + 1] - b;
+            begs[t] = b;
+            if constexpr (FILL) lvals[t] = a.lval[pb + e0 + t];
+        }
+        incl = len;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t o = __shfl_up(incl, off, 64);
+            if ((t & 63) >= off) incl += o;
+        }
+        if ((t & 63) == 63) wsum[t / 64] = incl;
+        __syncthreads();
+        for (int w = 0; w < t / 64; ++w) incl += wsum[w];
+        ends[t] = incl;
+        __syncthreads();
+        const int32_t chunk = ends[T - 1];
+        for (int32_t s = t; s < chunk; s += T) {
+            int32_t lo = 0, hi = T - 1;  // the first entry that ends past s
+            while (lo < hi) {
+                const int32_t mid = (lo + hi) / 2;
+                if (ends[mid] > s)
+                    hi = mid;
+                else
+                    lo = mid + 1;
+            }
+            const int32_t q = begs[lo] + s - (lo > 0 ? ends[lo - 1] : 0), at = total + s;
+            keys[at] = static_cast<uint64_t>(a.mcol[q]) << 16 | static_cast<uint32_t>(at);
+            if constexpr (FILL) vals[at] = lvals[lo] * a.mval[q];
+        }
+        total += chunk;
+        __syncthreads();
+    }
+    int32_t span = 2;
+    while (span < total) span *= 2;
+    for (int32_t k = total + t; k < span; k += T) keys[k] = ~0ull;
+    __syncthreads();
+    for (int32_t size = 2; size <= span; size *= 2)  // bitonic
+        for (int32_t step = size / 2; step > 0; step /= 2) {
+            for (int32_t k = t; k < span / 2; k += T) {
+                const int32_t lo = 2 * k - (k & (step - 1)), hi = lo + step;
+                const uint64_t x = keys[lo], y = keys[hi];
+                if ((x > y) == ((lo & size) == 0)) {
+                    keys[lo] = y;
+                    keys[hi] = x;
+                }
+            }
+            __syncthreads();
+        }
+    const int32_t base = FILL ? a.cptr[i] : 0;
+    int32_t u = 0;  // entries so far
+    bool zero = false;
+    for (int32_t k0 = 0; k0 < total; k0 += T) {
+        const int32_t k = k0 + t;
+        const uint64_t c = k < total ? keys[k] >> 16 : 0;
+        const bool head = k < total && (k == 0 || keys[k - 1] >> 16 != c);
+        const uint64_t m = __builtin_amdgcn_ballot_w64(head);
+        if ((t & 63) == 0) wsum[t / 64] = __popcll(m);
+        __syncthreads();
+        int32_t before = u + __popcll(m & ((1ull << (t & 63)) - 1));
+        for (int w = 0; w < T / 64; ++w) {
+            if (w < t / 64) before += wsum[w];
+            u += wsum[w];
+        }
+        if constexpr (FILL)
+            if (head) {
+                double s = 0.0;
+                for (int32_t q = k; q < total && keys[q] >> 16 == c; ++q) s = s + vals[keys[q] & 0xffff];
+                a.ccol[base + before] = static_cast<int32_t>(c);
+                a.cval[base + before] = s;
+                zero = zero || (s == 0.0 && static_cast<int32_t>(c) != i);
+            }
+        __syncthreads();
+    }
+    if constexpr (!FILL) {
+        if (t == 0) a.cnt[i] = u;
+    } else {
+        if (zero && a.zeros) *a.zeros = 1;
+    }
+}
+
+template <bool FILL>
+void launch_rows(const unsigned long long* rows, const ClassLists& lists, hipStream_t st, RowProducts a) {
     auto go = [&](auto kernel, int cls) {
         if (rows[cls] == 0) return;
-        const unsigned per = kThreads / kClassThreads[cls];
-        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rows[cls] + per - 1) / per)), dim3(kThreads), 0, st,
-                           static_cast<int32_t>(rows[cls]), static_cast<const int32_t*>(lists.rows[cls]), args...);
+        const unsigned threads = std::max(kThreads, kClassThreads[cls]), per = threads / kClassThreads[cls];
+        a.count = static_cast<int32_t>(rows[cls]);
+        a.rows = lists.rows[cls];
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rows[cls] + per - 1) / per)), dim3(threads), 0, st, a);
     };
+    static_assert(kHashClasses == 3 && kClasses == 5, "one launch per class");
     go(row_hash_kernel<kClassThreads[0], kClassSlots[0], FILL>, 0);
     go(row_hash_kernel<kClassThreads[1], kClassSlots[1], FILL>, 1);
     go(row_hash_kernel<kClassThreads[2], kClassSlots[2], FILL>, 2);
-    go(row_hash_kernel<kClassThreads[3], kClassSlots[3], FILL>, 3);
+    go(row_sort_kernel<kClassThreads[3], kClassSlots[3], FILL>, 3);
+    go(row_sort_kernel<kClassThreads[4], kClassSlots[4], FILL>, 4);
     check(hipGetLastError(), "row products");
 }
 
@@ -697,15 +808,17 @@ bool spgemm_rows(Pool& pool, const ConstCsr& L, const ConstCsr& M, int32_t* zero
         launch(classify_rows_kernel, n, st, n, nprod, lists, used, cnt);
     else
         lists = ClassLists{};
-    launch_row_hash<false>(rows, lists, st, L.ptr, L.col, L.val, M.ptr, M.col, M.val, cnt,
-                           static_cast<const int32_t*>(nullptr), static_cast<int32_t*>(nullptr),
-                           static_cast<double*>(nullptr), static_cast<int32_t*>(nullptr));
+    RowProducts a{0, nullptr, L.ptr, L.col, L.val, M.ptr, M.col, M.val, cnt, nullptr, nullptr, nullptr, nullptr};
+    launch_rows<false>(rows, lists, st, a);
     exclusive_scan_i32(pool, cnt, C.ptr, static_cast<int64_t>(n) + 1, st);
     C.nnz = read_back(C.ptr + n, st);
     C.col = pool.get<int32_t>(C.nnz);
     C.val = pool.get<double>(C.nnz);
-    launch_row_hash<true>(rows, lists, st, L.ptr, L.col, L.val, M.ptr, M.col, M.val, static_cast<int32_t*>(nullptr),
-                          static_cast<const int32_t*>(C.ptr), C.col, C.val, zeros);
+    a.cptr = C.ptr;
+    a.ccol = C.col;
+    a.cval = C.val;
+    a.zeros = zeros;
+    launch_rows<true>(rows, lists, st, a);
     return true;
 }
 

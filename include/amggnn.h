@@ -180,8 +180,12 @@ int amgg_interp_device(int device, int32_t n, const int32_t* rowptr, const int32
  * checked on the device before use. Device memory comes from alloc(bytes, user); temporaries are
  * handed back through release(ptr, user) before the call returns, also on error. On
  * success *ac_rowptr (nc + 1 entries), *ac_col and *ac_val (*ac_nnz entries) were obtained
- * from alloc and belong to the caller. chunk_products bounds the expanded products sorted
- * at once, which sets the temporary memory (about 24 bytes per product); 0 selects 2^27.
+ * from alloc and belong to the caller. With chunk_products 0 the products are formed row by row,
+ * with about 20 bytes of temporary memory per row
+ * beside A P and R; where a row has more than 8192 products, or
+ * a product more than 2^31 - 1, its products are expanded and sorted, at most 2^27 at once.
+ * chunk_products > 0 asks for the expanding form and bounds the products sorted at once, which set
+ * its temporary memory (about 24 bytes per product). The result does not depend on the form.
  * Work is queued on `stream` (hipStream_t), which the call synchronises to read sizes.
  * Errors: AMGG_EINVAL (NULL, bad sizes or pattern, more than 2^31 - 1 result entries),
  * AMGG_EWORKSPACE (alloc returned NULL), AMGG_EHIP (runtime error). */

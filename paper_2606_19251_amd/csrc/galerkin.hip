@@ -229,6 +229,13 @@ void check(hipError_t e, const char* where) {
     if (e != hipSuccess) throw Failure{AMGG_EHIP, std::string(where) + ": " + hipGetErrorString(e)};
 }
 
+struct DevCsr {
+    int32_t nrows = 0, ncols = 0, nnz = 0;
+    int32_t* ptr = nullptr;
+    int32_t* col = nullptr;
+    double* val = nullptr;
+};
+
 // Device memory from the caller's allocator; what is not taken as a result is released
 // when the pool goes out of scope.
 class Pool {
@@ -254,6 +261,9 @@ class Pool {
         release_(*it, user_);
         live_.erase(it);
     }
+    size_t mark() const { return live_.size(); }
+    // Releases what was taken since mark() and is still held, except the arrays of `kept` (null: of none).
+    void put_since(size_t from, const DevCsr* kept);
     void keep(const void* p) {  // hand to the caller
         auto it = std::find(live_.begin(), live_.end(), p);
         if (it != live_.end()) live_.erase(it);
@@ -267,13 +277,11 @@ class Pool {
     std::vector<void*> live_;
 };
 
-
-struct DevCsr {
-    int32_t nrows = 0, ncols = 0, nnz = 0;
-    int32_t* ptr = nullptr;
-    int32_t* col = nullptr;
-    double* val = nullptr;
-};
+void Pool::put_since(size_t from, const DevCsr* kept) {
+    const std::vector<void*> taken(live_.begin() + from, live_.end());
+    for (void* p : taken)
+        if (!kept || (p != kept->ptr && p != kept->col && p != kept->val)) put(p);
+}
 
 struct ConstCsr {
     int32_t nrows, ncols, nnz;
@@ -1074,20 +1082,35 @@ extern "C" int amgg_galerkin_device(int device, int32_t n, int32_t nc, const int
             check(transpose_csr(n, nc, p_nnz, p_rowptr, p_col, p_val, R.ptr, R.col, R.val, cursor, st), "transpose");
             const ConstCsr A{n, n, a_nnz, a_rowptr, a_col, a_val};
             const ConstCsr P{n, nc, p_nnz, p_rowptr, p_col, p_val};
+            // The row-wise products' temporaries (a few integers a row) stay until the call returns, each
+            // release being a wait; the expanding form, whose memory the caller may bound, starts
+            // without them.
             const bool expand = chunk_products > 0;  // the caller bounds the expansion
             int32_t* zeros = bad;                     // 0 again after the checks
-            DevCsr AP, G;
-            if (expand || !spgemm_rows(pool, A, P, nullptr, AP, st)) AP = spgemm(pool, A, P, budget, st);
+            DevCsr AP, G, Ac;
+            size_t from = pool.mark();
+            if (expand || !spgemm_rows(pool, A, P, nullptr, AP, st)) {
+                pool.put_since(from, nullptr);
+                AP = spgemm(pool, A, P, budget, st);
+                pool.put(cursor);
+            }
             const ConstCsr Rc{R.nrows, R.ncols, R.nnz, R.ptr, R.col, R.val};
             const ConstCsr APc{AP.nrows, AP.ncols, AP.nnz, AP.ptr, AP.col, AP.val};
-            DevCsr Ac;
+            // exact zeros off the diagonal are rare: the row-wise product tells whether there are any
+            bool drop = true;
             if (!expand && spgemm_rows(pool, Rc, APc, zeros, G, st)) {
-                // an exact zero off the diagonal is rare: the pass that drops them runs only if there is one
-                Ac = read_back(zeros, st) ? drop_zeros(pool, G, st) : G;
+                drop = read_back(zeros, st) != 0;
             } else {
+                pool.put_since(from, &AP);
                 G = spgemm(pool, Rc, APc, budget, st);
-                Ac = drop_zeros(pool, G, st);
             }
+            if (drop) {
+                pool.put_since(from, &G);  // A P and the temporaries
+                pool.put(R.ptr);
+                pool.put(R.col);
+                pool.put(R.val);
+            }
+            Ac = drop ? drop_zeros(pool, G, st) : G;
             pool.keep(Ac.ptr);
             pool.keep(Ac.col);
             pool.keep(Ac.val);

@@ -107,8 +107,10 @@ int gcin_backward(gcin_batch* b, int degree, int precision, const float* params,
 
 /* Self-check of the dense 64 x 64 tile product used by the GCIN layers: with A, B device FP32
  * 64 x 64 row-major, writes A B computed by the FP32 path to D_fp32 and by the BF16 MFMA path
- * (v_mfma_f32_16x16x32_bf16, FP32 accumulation) to D_bf16. */
+ * (v_mfma_f32_16x16x32_bf16, FP32 accumulation, A as the sum of two BF16 parts) to D_bf16. */
 int gcin_tile_gemm_check(const float* A, const float* B, float* D_fp32, float* D_bf16, void* stream);
+/* The same with B as the sum of two BF16 parts as well (GCIN_BF16X3). */
+int gcin_tile_gemm_check_x3(const float* A, const float* B, float* D, void* stream);
 
 /* Adam step with global-norm gradient clipping (App. B.1, Tab. 7: Adam, learning rate 1e-3,
  * clipping at max norm 1.0): g <- g min(1, clip/||g||) (clip <= 0: no clipping), then

@@ -147,6 +147,7 @@ SIGNATURES = {
     "gcin_forward": (_I, [_VP, _I, _I, _VP, _VP, _VP]),
     "gcin_backward": (_I, [_VP, _I, _I, _VP, _VP, _VP, _VP]),
     "gcin_tile_gemm_check": (_I, [_VP, _VP, _VP, _VP, _VP]),
+    "gcin_tile_gemm_check_x3": (_I, [_VP, _VP, _VP, _VP]),
     "adam_scratch_bytes": (C.c_size_t, []),
     "adam_step": (_I, [_VP, _VP, _VP, _VP, C.c_int64, C.c_float, C.c_float, C.c_float, C.c_float, _I, C.c_float,
                        _VP, _VP, _VP]),
@@ -570,3 +571,7 @@ def adam_step_noalloc(params, grads, m, v, n, lr, b1, b2, eps, step, clip, gnorm
 
 def gcin_tile_gemm_check(A, B, D_fp32, D_bf16, stream):
     return _check(lib().gcin_tile_gemm_check(A, B, D_fp32, D_bf16, stream), "gcin_tile_gemm_check")
+
+
+def gcin_tile_gemm_check_x3(A, B, D, stream):
+    return _check(lib().gcin_tile_gemm_check_x3(A, B, D, stream), "gcin_tile_gemm_check_x3")

@@ -466,7 +466,8 @@ __device__ __forceinline__ void split_bf16_pair(float x0, float x1, unsigned int
     lo = __builtin_bit_cast(unsigned int, __builtin_convertvector(r, bf16x2));
 }
 
-template <int HD, bool MFMA, bool SPLIT = false, int LD = HD + 1>
+// D = A B, a group of HD lanes its 16 rows. FP32: B from memory (Bf); MFMA: bf16 parts of both (B as Bt).
+template <int HD, bool MFMA, int LD = HD + 1>
 __device__ __forceinline__ void tile_gemm(const float (*A)[LD], const float* __restrict__ Bf,
                                           const unsigned short (*Bt)[HD + 8], float (*D)[LD]) {
     static_assert(!MFMA || HD == 64, "the MFMA tiling is written for 64 channels");
@@ -505,28 +506,14 @@ __device__ __forceinline__ void tile_gemm(const float (*A)[LD], const float* __r
         f32x4 acc[4];
         for (int nb = 0; nb < 4; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
         for (int ks = 0; ks < HD; ks += 32) {
-            bf16x8 a, al;
-            if constexpr (SPLIT) {
-                u32x4 av, alv;
-                for (int e = 0; e < 4; ++e) {
-                    unsigned int h, l;
-                    split_bf16_pair(A[wv * 16 + i][ks + kq + 2 * e], A[wv * 16 + i][ks + kq + 2 * e + 1], h, l);
-                    av[e] = h;
-                    alv[e] = l;
-                }
-                a = __builtin_bit_cast(bf16x8, av);
-                al = __builtin_bit_cast(bf16x8, alv);
-            } else {
-                u16x8 av;
-                for (int e = 0; e < 8; ++e) av[e] = f2bf(A[wv * 16 + i][ks + kq + e]);
-                a = __builtin_bit_cast(bf16x8, av);
-            }
+            u16x8 av;
+            for (int e = 0; e < 8; ++e) av[e] = f2bf(A[wv * 16 + i][ks + kq + e]);
+            const bf16x8 a = __builtin_bit_cast(bf16x8, av);
             for (int nb = 0; nb < 4; ++nb) {
                 u16x8 bv;
                 for (int e = 0; e < 8; ++e) bv[e] = Bt[nb * 16 + i][ks + kq + e];
                 const bf16x8 b = __builtin_bit_cast(bf16x8, bv);
                 acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nb], 0, 0, 0);
-                if constexpr (SPLIT) acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, b, acc[nb], 0, 0, 0);
             }
         }
         for (int nb = 0; nb < 4; ++nb)
@@ -580,17 +567,20 @@ __device__ __forceinline__ void tile_product(const float (*A)[LD], const unsigne
     }
 }
 
-// Stage a 64 x 64 FP32 matrix M (row-major [k][c]) for tile_gemm: bf16 copy as Bt[c][k] when
-// `transpose`, else as Bt[k'][c'] = M[k'][c'] (used for products with M^T).
+// bf16 copy of a 64 x 64 FP32 matrix M (row-major) for tile_gemm's product with M^T.
 template <int HD>
-__device__ __forceinline__ void stage_bf16(const float* __restrict__ M, bool transpose, unsigned short (*Bt)[HD + 8]) {
-    for (int e = threadIdx.x; e < HD * HD; e += 4 * HD) {
-        const int k = e / HD, c = e % HD;
-        if (transpose)
-            Bt[c][k] = f2bf(M[e]);
-        else
-            Bt[k][c] = f2bf(M[e]);
-    }
+__device__ __forceinline__ void stage_bf16(const float* __restrict__ M, unsigned short (*Bt)[HD + 8]) {
+    for (int e = threadIdx.x; e < HD * HD; e += 4 * HD) Bt[e / HD][e % HD] = f2bf(M[e]);
+}
+
+// Entry e of the weights W ([k][col]) as tile_product reads them: bf16 hi part at [col][k], lo part HD^2 on.
+template <int HD>
+__device__ __forceinline__ void weight_parts(const float* __restrict__ W, int e, unsigned short* hi) {
+    const int k = e / HD, c = e % HD;
+    unsigned short h, lo;
+    split_bf16(W[e], h, lo);
+    hi[c * HD + k] = h;
+    hi[HD * HD + c * HD + k] = lo;
 }
 
 // bf16 hi / lo parts of the 64 x 64 weights of layers 1 .. NL-1, transposed ([col][k]) for
@@ -605,11 +595,7 @@ __global__ __launch_bounds__(256) void weights_bf16_kernel(const float* __restri
     unsigned short* hi = wbf + static_cast<int64_t>(blockIdx.x) * 2 * HD * HD;
     const int e = static_cast<int>(blockIdx.y) * 256 + threadIdx.x;
     if (e >= HD * HD) return;
-    const int k = e / HD, c = e % HD;
-    unsigned short h, lo;
-    split_bf16(W[e], h, lo);
-    hi[c * HD + k] = h;
-    hi[HD * HD + c * HD + k] = lo;
+    weight_parts<HD>(W, e, hi);
 }
 
 // Tile of a workgroup. Workgroups go to the 8 XCDs in turn, each with an L2 of its own: within every 256
@@ -729,7 +715,7 @@ __global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kern
 #pragma unroll
         for (int e = 0; e < 4; ++e) yv[e] = make_float4(acc[0][e], acc[1][e], acc[2][e], acc[3][e]);
     } else {
-        tile_gemm<HD, false, false, LD>(Hs, W, nullptr, Hs);
+        tile_gemm<HD, false, LD>(Hs, W, nullptr, Hs);
         wave_sync();
 #pragma unroll
         for (int e = 0; e < 4; ++e) yv[e] = *reinterpret_cast<const float4*>(hs + e * LD);
@@ -1323,7 +1309,7 @@ __global__ __launch_bounds__(4 * HD) void bwd_b_kernel(int ntiles, const int32_t
     const int wv = threadIdx.x / HD, c = threadIdx.x % HD;
     static_assert(!MFMA || HD == 64, "the MFMA tiling is written for 64 channels");
     constexpr int NW = HD / 4;  // dW entries per thread
-    if constexpr (MFMA) stage_bf16<HD>(W, false, Bt);  // dH = dY W^T: B[c'][k] = W[k][c'] read as rows of W
+    if constexpr (MFMA) stage_bf16<HD>(W, Bt);  // dH = dY W^T: B[c'][k] = W[k][c'] read as rows of W
     float wr[MFMA ? 1 : HD];                           // FP32: row c of W
     if constexpr (!MFMA)
 #pragma unroll
@@ -1525,23 +1511,39 @@ __global__ __launch_bounds__(4 * HD) void bwd_b0_kernel(int ntiles, const int32_
     }
 }
 
-// One workgroup: D1 = A B by the FP32 path and D2 = A B by the BF16 MFMA path of tile_gemm.
+// One workgroup: A B by the layer kernel's products, over the same tile and with the same rows and columns per
+// lane: D1 in FP32, D2 by MFMA with B in bf16 (hi parts), D3 with B's lo parts too. Any of them may be null.
 __global__ __launch_bounds__(256) void tile_gemm_check_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                              float* __restrict__ D1, float* __restrict__ D2) {
-    constexpr int HD = 64, NT = 256;
-    __shared__ float As[TILE][HD + 1];
-    __shared__ float Ds[TILE][HD + 1];
-    __shared__ unsigned short Bt[HD][HD + 8];
-    for (int e = threadIdx.x; e < TILE * HD; e += NT) As[e / HD][e % HD] = A[e];
-    stage_bf16<HD>(B, true, Bt);
+                                                              float* __restrict__ D1, float* __restrict__ D2,
+                                                              float* __restrict__ D3) {
+    constexpr int HD = 64, NT = 256, LD = HD + 4, G = HD / 4;
+    __shared__ __align__(16) float Hs[TILE][LD];
+    __shared__ __align__(16) unsigned short wbf[2 * HD * HD];
+    for (int e = threadIdx.x; e < TILE * HD; e += NT) Hs[e / HD][e % HD] = A[e];
+    for (int e = threadIdx.x; e < HD * HD; e += NT) weight_parts<HD>(B, e, wbf);
     __syncthreads();
-    tile_gemm<HD, false>(As, B, Bt, Ds);
-    __syncthreads();
-    for (int e = threadIdx.x; e < TILE * HD; e += NT) D1[e] = Ds[e / HD][e % HD];
-    __syncthreads();
-    tile_gemm<HD, true, true>(As, B, Bt, Ds);
-    __syncthreads();
-    for (int e = threadIdx.x; e < TILE * HD; e += NT) D2[e] = Ds[e / HD][e % HD];
+    const int wv = threadIdx.x / HD, c = threadIdx.x % HD;
+    const int row0 = wv * 16 + 4 * (c / G), c4 = 4 * static_cast<int>(threadIdx.x % G);
+    auto write = [&](float* D, const f32x4 (&acc)[4]) {
+        for (int e = 0; e < 4; ++e)
+            for (int nb = 0; nb < 4; ++nb) D[(row0 + e) * HD + c4 + nb] = acc[nb][e];
+    };
+    f32x4 acc[4];
+    if (D2) {
+        tile_product<HD, false, LD>(Hs, wbf, acc);
+        write(D2, acc);
+    }
+    if (D3) {
+        tile_product<HD, true, LD>(Hs, wbf, acc);
+        write(D3, acc);
+    }
+    if (D1) {
+        wave_sync();
+        tile_gemm<HD, false, LD>(Hs, B, nullptr, Hs);
+        wave_sync();
+        for (int e = 0; e < 4; ++e)
+            for (int k = 0; k < 4; ++k) D1[(row0 + e) * HD + c4 + k] = Hs[row0 + e][c4 + k];
+    }
 }
 
 // out[e] = sum over the `parts` partial arrays (stride `stride`) of part[k][e], e < count, in FP64 and in a
@@ -2080,9 +2082,17 @@ extern "C" int gcin_backward(gcin_batch* b, int degree, int precision, const flo
 
 extern "C" int gcin_tile_gemm_check(const float* A, const float* B, float* D_fp32, float* D_bf16, void* stream) {
     if (!A || !B || !D_fp32 || !D_bf16) return amgg::fail(AMGG_EINVAL, "gcin_tile_gemm_check: null argument");
-    tile_gemm_check_kernel<<<1, 256, 0, static_cast<hipStream_t>(stream)>>>(A, B, D_fp32, D_bf16);
+    tile_gemm_check_kernel<<<1, 256, 0, static_cast<hipStream_t>(stream)>>>(A, B, D_fp32, D_bf16, nullptr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e, "gcin_tile_gemm_check");
+    return AMGG_OK;
+}
+
+extern "C" int gcin_tile_gemm_check_x3(const float* A, const float* B, float* D, void* stream) {
+    if (!A || !B || !D) return amgg::fail(AMGG_EINVAL, "gcin_tile_gemm_check_x3: null argument");
+    tile_gemm_check_kernel<<<1, 256, 0, static_cast<hipStream_t>(stream)>>>(A, B, nullptr, nullptr, D);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_err(e, "gcin_tile_gemm_check_x3");
     return AMGG_OK;
 }
 

@@ -251,6 +251,10 @@ typedef struct {
     int32_t stream_cap[3];
 } amgg_level_view;
 int amgg_level_view_get(const amgg_ctx* ctx, int lvl, amgg_level_view* out);
+/* Widths of the padded rows of A_l, P_l and R_l that the paired passes of a small level read (residual with
+ * restriction, prolongation with a diagonal smoothing step), all 0 where the level keeps separate
+ * passes (diagnostics and tests). Errors: AMGG_EINVAL, AMGG_ESTATE (not finalized). */
+int amgg_pair_widths(const amgg_ctx* ctx, int lvl, int widths[3]);
 /* Number of captured solve graphs the context keeps (diagnostics and tests; see
  * amgg_solve_opts.graphs). Errors: AMGG_EINVAL (NULL). */
 int amgg_kept_graphs(const amgg_ctx* ctx, int* count);

@@ -122,6 +122,7 @@ SIGNATURES = {
     "amgg_level_apply": (_I, [_VP, _I, _I, _I, _VP, _VP, _VP, _VP]),
     "amgg_set_fusion": (_I, [_VP, _I]),
     "amgg_set_packed_columns": (_I, [_VP, _I]),
+    "amgg_pair_widths": (_I, [_VP, _I, C.POINTER(_I)]),
     "amgg_kept_graphs": (_I, [_VP, C.POINTER(_I)]),
     "amgg_level_apply_timed": (_I, [_VP, _I, _I, _I, _VP, _VP, _VP, _VP, _VP, _VP]),
     "amgg_solve": (_I, [_VP, C.POINTER(amgg_solve_opts), _VP, _VP, C.POINTER(amgg_solve_info), _VP, _I, _VP]),
@@ -446,6 +447,12 @@ def amgg_set_packed_columns(ctx, mode):
 
 def amgg_set_fusion(ctx, enable):
     return _check(lib().amgg_set_fusion(ctx, int(enable)), "amgg_set_fusion")
+
+
+def amgg_pair_widths(ctx, lvl):
+    w = (_I * 3)()
+    _check(lib().amgg_pair_widths(ctx, int(lvl), w), "amgg_pair_widths")
+    return [int(v) for v in w]
 
 
 def amgg_kept_graphs(ctx) -> int:

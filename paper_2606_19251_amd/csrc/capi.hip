@@ -617,6 +617,17 @@ extern "C" int amgg_set_packed_columns(amgg_ctx* c, int mode) {
     return AMGG_OK;
 }
 
+extern "C" int amgg_pair_widths(const amgg_ctx* c, int lvl, int widths[3]) {
+    if (!c || !widths || lvl < 0 || lvl >= c->nlevels) return fail(AMGG_EINVAL, "amgg_pair_widths: bad argument");
+    if (!c->finalized) return fail(AMGG_ESTATE, "amgg_pair_widths: hierarchy not finalized");
+    const Level& L = c->lv[lvl];
+    const bool use = lvl + 1 < c->nlevels && L.pairs();
+    widths[0] = use ? L.pad_a.w : 0;
+    widths[1] = use ? L.pad_p.w : 0;
+    widths[2] = use ? L.pad_r.w : 0;
+    return AMGG_OK;
+}
+
 extern "C" int amgg_kept_graphs(const amgg_ctx* c, int* count) {
     if (!c || !count) return fail(AMGG_EINVAL, "amgg_kept_graphs: null argument");
     *count = static_cast<int>(c->graphs.size());

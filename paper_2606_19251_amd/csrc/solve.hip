@@ -247,7 +247,7 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         }
         R.ok(vec_zero_bytes(s, sizeof(double) * kSlots, st));
         R.ok(vec_zero_bytes(x, sizeof(double) * n, st));
-        R.ok(vec_copy<double>(n, bb, c->ra, st));
+        if (o->outer != AMGG_OUTER_STATIONARY) R.ok(vec_copy<double>(n, bb, c->ra, st));
         R.ok(partial_dot(n, bb, bb, c->partial, st));
         R.ok(fcg_finish_rr(c->partial, reduce_blocks(n), s, st));
         if (!R.read_scalars(st)) return hip_fail(R.e, "amgg_solve");
@@ -275,9 +275,11 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         // Enqueue ahead only while the `flight` iterations in flight are not expected to converge (the
         // residual after the last of them, predicted from the last ratio, stays above twice the
         // tolerance): an iteration enqueued after the converging one would run its whole cycle for
-        // nothing.
+        // nothing. The stationary iteration, of which a direct solve needs one and a loose
+        // tolerance few, waits for the second ratio (the first says little: the initial residual is
+        // not the cycle's).
         auto ahead = [&](size_t flight) {
-            if (hist.size() < 3) return true;
+            if (hist.size() < 3) return o->outer != AMGG_OUTER_STATIONARY;
             const double last = hist[hist.size() - 1], ratio = std::min(1.0, last / hist[hist.size() - 2]);
             double pred = last;
             for (size_t m = 0; m < flight; ++m) pred *= ratio;
@@ -287,19 +289,20 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
             // As below, an iteration is a graph launch with an asynchronous copy of the scalars, and up
             // to kPipeline - 1 are in flight behind the one the host inspects. An iteration also
             // saves its iterate in one of kSavedIterates vectors in turn, so that the one the
-            // inspection stops at (by any criterion) is at hand whatever ran after it.
+            // inspection stops at (by any criterion) is at hand whatever ran after it; one that
+            // nothing follows before its inspection writes x itself.
             static_assert(kSavedIterates >= kPipeline, "in-flight iterations leave the inspected iterate alone");
             const SavedIterates saved{{c->rb, c->z, c->p, c->q}};
             double* r = L0.r64;  // free between cycles
-            R.ok(vec_zero_bytes(cur, sizeof(double) * n, st));
-            int launched = 0;
-            auto launch = [&]() -> hipError_t {
+            const bool graph = use_graph && c->nlevels > 1;  // a direct solve is five kernels, once
+            int launched = 0, in_x = 0;  // iterations enqueued; the one whose iterate x holds
+            auto launch = [&](bool alone) -> hipError_t {
                 const bool zero = first;
-                hipError_t e = run_body(c, use_graph, graph_key(c, zero ? "st0" : "st", 64, o->nu1, o->nu2, bb, cur, r),
+                hipError_t e = run_body(c, graph, graph_key(c, zero ? "st0" : "st", 64, o->nu1, o->nu2, bb, cur, r),
                                         st, R, [&](hipStream_t qs) {
                                             double* res = nullptr;
                                             int cnt = 0;
-                                            R.ok(vec_copy<double>(n, cur, L0.u64, qs));
+                                            if (!zero) R.ok(vec_copy<double>(n, cur, L0.u64, qs));
                                             R.ok(vcycle_level<double>(c, 0, bb, L0.u64, L0.t64, zero, o->nu1, o->nu2, qs,
                                                                       &res));
                                             R.ok(stationary_store(n, res, cur, saved, s, qs));
@@ -308,6 +311,10 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
                                         });
                 first = false;
                 if (e != hipSuccess) return e;
+                if (alone) {
+                    if ((e = vec_copy<double>(n, cur, x, st)) != hipSuccess) return e;
+                    in_x = launched + 1;
+                }
                 const int slot = launched % kPipeline;
                 if ((e = hipMemcpyAsync(hs + (1 + slot) * kSlots, s, sizeof(double) * kSlots, hipMemcpyDeviceToHost,
                                         st)) != hipSuccess ||
@@ -318,15 +325,17 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
             };
             auto iterate = [&]() { return saved.v[(k - 1) % kSavedIterates]; };  // after k iterations
             auto stop = [&](int status, double rel) -> int {
-                R.ok(vec_copy<double>(n, iterate(), x, st));
-                R.ok(hipStreamSynchronize(st));
+                if (in_x != k) {
+                    R.ok(vec_copy<double>(n, iterate(), x, st));
+                    R.ok(hipStreamSynchronize(st));
+                }
                 return R.e != hipSuccess ? hip_fail(R.e, "amgg_solve") : finish(status, rel, k);
             };
             for (;;) {
                 hipError_t e = hipSuccess;
                 while (e == hipSuccess && launched - k < kPipeline && launched < o->maxit &&
                        (launched == k || ahead(static_cast<size_t>(launched - k))))
-                    e = launch();
+                    e = launch(launched == k && (launched + 1 == o->maxit || !ahead(1)));
                 if (e == hipSuccess) e = hipEventSynchronize(c->ev[k % kPipeline]);
                 if (e != hipSuccess) return hip_fail(e, "amgg_solve");
                 const double rel = std::sqrt(hs[(1 + k % kPipeline) * kSlots + kRR]) / nb;
@@ -353,10 +362,7 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
                 inf.fell_back = 1;
                 set_all_jacobi(c, st);
                 first = !std::isfinite(rel);
-                if (first)
-                    R.ok(vec_zero_bytes(cur, sizeof(double) * n, st));
-                else
-                    R.ok(vec_copy<double>(n, iterate(), cur, st));
+                if (!first) R.ok(vec_copy<double>(n, iterate(), cur, st));
                 R.ok(stationary_set_iter(s, k, st));
                 launched = k;
                 stag_base = hist.size() - 1;

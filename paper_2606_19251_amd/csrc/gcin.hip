@@ -290,8 +290,10 @@ __device__ __forceinline__ double wave4_sum(double v, double (*sh)[HD]) {
 // self-loop of A_hat, whose entry also writes the a_ii feature). A copy: bound by memory on large
 // levels, by the latency of its few dependent loads on small ones, which is why the levels share one
 // launch (one launch per level of 256-row workgroups took 157 us on the hierarchy of 998k tetrahedral
-// cells, 83 of them on levels below 25k rows, and 28 us more for the pad rows; this one takes 85). A
-// tile whose entries do not fit the map (more than 64 per row on average) is copied row by row.
+// cells, 83 of them on levels below 25k rows, and 28 us more for the pad rows; this one takes 85). In a
+// tile whose entries do not fit the map (more than 64 per row on average) an entry finds its row by
+// bisection in the rows' ends (copied row by row, four threads each, a hub row of 5000 entries made the
+// batch of its 20k-row graph 209 us; 37 so).
 struct FillGraph {
     const int32_t* rp;
     const int32_t* cl;
@@ -306,6 +308,7 @@ __global__ __launch_bounds__(256) void fill_graph_kernel(int ntiles, const int32
                                                         int32_t* __restrict__ col, float* __restrict__ w,
                                                         float* __restrict__ x0) {
     __shared__ uint8_t rowof[kFillCap];
+    __shared__ int32_t ends[TILE];  // of the rows' entries, from the tile's first entry
     const int t = static_cast<int>(threadIdx.x);
     const FillGraph g = fg[tile_graph[blockIdx.x]];
     const int32_t r0 = static_cast<int32_t>(blockIdx.x) * TILE - g.row0;  // rows of the level matrix
@@ -325,21 +328,21 @@ __global__ __launch_bounds__(256) void fill_graph_kernel(int ntiles, const int32
         b = e = g.rp[g.n];  // a pad row
     }
     if (q == 0) {
+        ends[lr] = e - b0;
         ptr[g.row0 + i] = g.e0 + b;
         x0[2 * (g.row0 + i)] = 0.0f;  // a_ii; the diagonal entry writes it below
         x0[2 * (g.row0 + i) + 1] = i < r1 ? static_cast<float>(e - b - 1) : 0.0f;
         if (static_cast<int>(blockIdx.x) == ntiles - 1 && lr == TILE - 1) ptr[g.row0 + i + 1] = g.e0 + e;
     }
     __syncthreads();
-    if (!fits) {
-        for (int32_t p = b + q; p < e; p += 4) {
-            const int32_t j = g.cl[p];
-            col[g.e0 + p] = g.row0 + j;
-            w[g.e0 + p] = j == i ? 1.0f : static_cast<float>(g.va[p]);
-            if (j == i) x0[2 * (g.row0 + i)] = static_cast<float>(g.va[p]);
-        }
-        return;
-    }
+    auto row_of = [&](int32_t k) -> int32_t {
+        if (fits) return rowof[k];
+        int32_t r = 0;  // rows that end at or before entry k
+#pragma unroll
+        for (int step = TILE / 2; step > 0; step /= 2)
+            if (ends[r + step - 1] <= k) r += step;
+        return r;
+    };
     for (int32_t base = 0; base < ne; base += kFillChunk * 256) {
         int32_t j[kFillChunk];
         double a[kFillChunk];
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256) void fill_graph_kernel(int ntiles, const int32
         for (int u = 0; u < kFillChunk; ++u) {
             const int32_t k = base + t + u * 256;
             if (k < ne) {
-                const int32_t row = r0 + rowof[k];
+                const int32_t row = r0 + row_of(k);
                 col[g.e0 + b0 + k] = g.row0 + j[u];
                 if (j[u] == row) {
                     w[g.e0 + b0 + k] = 1.0f;  // self-loop of A_hat

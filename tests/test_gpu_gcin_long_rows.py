@@ -50,3 +50,30 @@ def test_hub_rows(n, hubs, k, hidden):
     ref = OG.forward_np(G.unpack(flat, 2, hidden), mats, 2)
     assert np.abs(out - ref).max() <= 1e-4 * np.abs(ref).max()
     batch.close()
+
+
+@pytest.mark.parametrize("n,hubs,k", [(3000, [0], 2900), (3000, [1500], 600), (3000, [17, 18, 19], 1500),
+                                      (3000, [16, 20, 24, 28], 1500), (2999, [2998], 2000)])
+@pytest.mark.parametrize("hidden", [32, 64])
+def test_hub_rows_backward(n, hubs, k, hidden):
+    """Hub rows alone in their wavefront's rows, several in one group of four, one in each group: the gradient
+    against the oracle's in FP64 (FP32 network), and the same bits from run to run."""
+    from paper_2606_19251_amd import capi
+    from paper_2606_19251_amd import gcin as G
+
+    dev = torch.device("cuda", 0)
+    mats = [hub_graph(n, hubs, k), hub_graph(130, [100], 60)]
+    graphs = [tuple(torch.from_numpy(t).cuda() for t in (A.indptr.astype(np.int32), A.indices.astype(np.int32), A.data))
+              for A in mats]
+    batch = G.GraphBatch(graphs, dev, hidden)
+    flat = G.init_flat(2, 5, hidden=hidden)
+    P = torch.from_numpy(flat).to(dev)
+    batch.forward(P, 2, capi.GCIN_FP32)
+    w = np.random.default_rng(3).standard_normal((2, 5))
+    d = torch.from_numpy(w.astype(np.float32)).to(dev)
+    g = batch.backward(P, d, 2, capi.GCIN_FP32)
+    assert torch.equal(g, batch.backward(P, d, 2, capi.GCIN_FP32))
+    ref = G.pack(OG.gradient(G.unpack(flat, 2, hidden), mats, w.astype(np.float32).astype(np.float64), 2), 2)
+    g, ref = g.cpu().numpy().astype(np.float64), np.asarray(ref, np.float64)
+    assert np.linalg.norm(g - ref) <= 1e-3 * np.linalg.norm(ref)
+    batch.close()

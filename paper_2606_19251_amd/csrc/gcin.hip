@@ -5,8 +5,9 @@
 // concatenated; each graph starts on a 64-row tile boundary (pad rows carry no edges and
 // are masked), so a tile belongs to exactly one graph and per-graph statistics are fixed
 // order sums of per-tile partials (no atomics, bitwise reproducible). Activations are
-// FP32 [N x 64] row-major; a tile is processed by one 256-thread workgroup (4 wavefronts x
-// 16 rows, lane = channel), so every row access is one coalesced 256-byte transaction.
+// FP32 [N x 64] (or [N x 32]) row-major; a tile is processed by one workgroup of four groups of
+// 64 (32) lanes with 16 rows each, a lane holding four neighbouring channels of four rows, so that a
+// row is 16 lanes' 16-byte accesses, one coalesced 256-byte transaction.
 //
 // Each GCIN layer is one pass: the neighbour features are normalised and rectified on
 // load (InstanceNorm + ReLU of the previous layer applied by the consumer), aggregated
@@ -197,20 +198,20 @@ __device__ __forceinline__ float group_bcast(float v) {
     return __builtin_bit_cast(float, group_bcast<Q, G>(__builtin_bit_cast(int, v)));
 }
 
-// Aggregation over the stored entries of rows of the batched graph with 16-byte gathers: group q of G = HD / 4 lanes (of the HD lanes that own rows
-// [r0, r0 + 16)) owns the rows [r0 + 4 q, r0 + 4 q + 4) and lane p of the group holds channels
-// 4 p .. 4 p + 3, so that one load instruction brings 64 / G neighbour rows. Each row's entries are
-// visited in stored order. A group's lanes hold
-// its next G entries (column, weight, row); eight gathers are in flight at a time, and the next
-// entries load meanwhile. What is bound here is instructions and latency, not bytes, so the steps are
-// straight-line code: entries are broadcast by DPP, a slot past the group's end has weight 0 and ends
-// no row, and whether any group ends a row at a step is a scalar test of a mask formed once per G
-// entries. rp is the lane's row pointer, ptr[g0 + min(p, 4)] of the group's first row g0; init() is called
-// once the first entries are on their way. use(w, v) gets what load(column) returned; with PAIR, load brings
-// two floats per node, which each lane then loads for the entry it holds (one load instruction per G
-// entries instead of one per entry: the address units take a wavefront's lanes four a cycle, whatever
-// they load). done(i) is called after the last entry of the
-// group's row i = 0..3 and never for a row without entries (the caller presets those).
+// Aggregation over the stored entries of rows of the batched graph with 16-byte gathers: group q of
+// G = HD / 4 lanes (of the HD lanes that own rows [r0, r0 + 16)) owns the rows [r0 + 4 q, r0 + 4 q + 4)
+// and lane p of the group holds channels 4 p .. 4 p + 3, so that one load instruction brings 64 / G
+// neighbour rows. Each row's entries are visited in stored order. A group's lanes hold its next G
+// entries (column, weight, row); eight gathers are in flight at a time, and the next entries load
+// meanwhile. What is bound here is instructions and latency, not bytes, so the steps are straight-line
+// code: entries are broadcast by DPP, a slot past the group's end has weight 0 and ends no row, and
+// whether any group ends a row at a step is a scalar test of a mask formed once per G entries. rp is the
+// lane's row pointer, ptr[g0 + min(p, 4)] of the group's first row g0; init() is called once the first
+// entries are on their way. use(w, v) gets what load(column) returned; with PAIR, load brings two
+// floats per node, which each lane then loads for the entry it holds (one load instruction per G entries
+// instead of one per entry: the address units take a wavefront's lanes four a cycle, whatever they
+// load). done(i) is called after the last entry of the group's row i = 0..3 and never for a row without
+// entries (the caller presets those).
 constexpr int kBatchX4 = 8;
 
 template <int G, bool PAIR, class Init, class Load, class Use, class Done>
@@ -675,7 +676,8 @@ __device__ __forceinline__ int dealt_tile() {
 // Y0: the layer below is layer 0, whose output is formed from H0 (y0_of) instead of read from Yp. Off: type
 // of the byte offsets into Yp (32 bits where they suffice).
 template <int HD, bool MFMA, bool X3, bool Y0, typename Off>
-__global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kernel(const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
+__global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kernel(
+                                                   const int32_t* __restrict__ ptr, const int32_t* __restrict__ col,
                                                    const float* __restrict__ w, const int32_t* __restrict__ tile_graph,
                                                    const int32_t* __restrict__ gend, const float* __restrict__ Yp,
                                                    const float* __restrict__ H0, const float* __restrict__ W0,
@@ -851,9 +853,10 @@ __global__ __launch_bounds__(4 * HD, MFMA && (Y0 || X3) ? 5 : 4) void layer_kern
 // time, so kAhead items' loads are issued together, all that a full chunk gives a group (with 4 groups a chunk
 // took four such rounds, 7.5 us against 4.7 on 625 tiles of 32 channels), and what can be summed apart
 // (y, y^2, the readout, the backward's four sums; blockIdx.y) gets its own workgroup. The statistics of
-// a layer and the readout of the layer below it share their launches, and where every graph is one chunk, stage 1 finishes it and there is no stage 2. On the
-// 998k-cell hierarchy the forward's reductions went from 16 launches and 180 us to 10 and 92, on the
-// 32-mesh training batch from 16 and 130 to 5 and 44, the backward's sums from 8 and 48 to 4 and 33.
+// a layer and the readout of the layer below it share their launches, and where every graph is one
+// chunk, stage 1 finishes it and there is no stage 2. On the 998k-cell hierarchy the forward's
+// reductions went from 16 launches and 180 us to 10 and 92, on the 32-mesh training batch from 16 and
+// 130 to 5 and 44, the backward's sums from 8 and 48 to 4 and 33.
 constexpr int kChunkTiles = 256;
 constexpr int kAhead = 16;
 constexpr int kSumGroups = 16;
@@ -1347,7 +1350,8 @@ __global__ __launch_bounds__(4 * HD, 5) void bwd_a_kernel(const int32_t* __restr
     if (wv == 0)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            tb[tile * 4 * HD + q * HD + c] = part(0)[q * HD + c] + part(1)[q * HD + c] + part(2)[q * HD + c] + part(3)[q * HD + c];
+            tb[tile * 4 * HD + q * HD + c] =
+                part(0)[q * HD + c] + part(1)[q * HD + c] + part(2)[q * HD + c] + part(3)[q * HD + c];
 }
 
 // Layer backward, second half. dY = rstd (dxhat - mean(dxhat) - xhat mean(dxhat xhat));
@@ -2011,7 +2015,7 @@ void forward_impl(gcin_batch* b, int degree, int precision, const float* P, floa
     // Statistics of layer l, then its readout, which feeds no later layer: pooling each layer as
     // soon as its statistics exist leaves every result as it is and lets an inference-only batch
     // reuse the buffer of layer l - 1 for layer l + 1. The readout partials of layer l are formed
-    // by the kernel of layer l + 1 (from the rows' own entries of A_hat), the last layer's by a
+    // by the kernel of layer l + 1 (from its tile's own rows of the layer below), the last layer's by a
     // pooling pass; the per-graph reductions of a layer's statistics and of the readout below it
     // share their launches (reduce_kernel).
     const int C = b->nchunks;

@@ -150,10 +150,12 @@ constexpr int64_t kScanPartsMax = 1024;  // scratch of pack_columns: kScanPartsM
 // plain columns) stream from HBM: there the packing pays however many far entries it has (8M-cell
 // mesh: fine-level residual 91 -> 84 us). One that stays in the 256 MB last-level cache gains less, and
 // the pass over its far entries costs it a barrier and two dependent loads: it pays where almost no
-// entry is far and the matrix is no longer latency-bound. us per pass with plain and packed columns:
-// 7.0M entries with 0.35 % far 12.7 / 11.8, 4.4M with 0.30 % 8.6 / 7.5, 5.2M with none 11.2 / 10.5, 2.3M
-// with none 6.4 / 6.2; 8.5M with 2.4 % 13.9 / 14.2, 5.0M with 2.4 % 9.8 / 10.4; below 2M entries equal
-// or slower.
+// entry is far and the matrix is no longer latency-bound. us per pass with plain and packed columns, in turn
+// on one box (boxes differ by more than the two do): 7.0M entries with 0.4 % far 12.0 / 11.7 in FP32 and 16.8 / 16.4
+// in FP64, 4.4M with 0.30 % 8.6 / 7.5, 5.2M with none 11.1 / 10.6 and 14.3 / 13.4; 8.5M with 2.4 % 13.9 / 14.2, 5.0M
+// with 2.4 % 9.8 / 10.4. Whole flexible-CG solves, ms, plain / by this rule / every matrix packed: 1M-point
+// triangulation 4.98 / 4.79 / 4.79, 1M-point Delaunay mesh 5.33 / 5.18 / 5.32, 1M-point layer mesh 5.82 / 5.56 / 5.44,
+// 1024 x 1024 grid 1.64 / 1.60 / 1.59; 4.5M tetrahedra, refinement, 29.9 / 28.8 / 29.5.
 constexpr int32_t kPackMinCached = 1 << 21;
 constexpr int kPackFarCached = 128;  // at most one far entry in so many
 constexpr int32_t kPackMinEntries = 1 << 24;
@@ -234,10 +236,14 @@ hipError_t jacobi_pre_step(const CsrView& m, const T* a, const T* d, const T* f,
 // 24k rows (w = 32) 14.9 / 15.9, 11k rows with some of 60 entries (w = 64) 14.8 / 15.4, 91k 21.3 / 30.
 // A restriction forms the residual of every entry of R's padded rows, so the two widths count together: levels
 // of more than kPairMaxWork such products keep the separate passes, whose matrix is smaller and stays in
-// cache. Whole solves, us, with the pairs by kPairMaxSlots alone, with this limit, without pairs: 59k-row
-// triangulation 5730 / 5248 / 5338, 64k tetrahedral cells (levels of 1.1M products) 2249 / 2081 / 2079, 12k-row
-// triangulation (0.4M) 1457 / 1479 / 1749, 11k-cell layer mesh (0.4M) 1320 / 1319 / 1523, 64 x 64 grid (0.13M)
-// 469 / 478 / 577; with the limit at 0.25M the 12k-row one takes 1661.
+// cache. Whole solves, us, in turn on one box, with this limit, with 2^19, with 2^18, without pairs (the largest level
+// the limit admits in brackets): 12k-row triangulation (0.63M products) 1018 / 1117 / 1179 / 1245 and with FP64 cycles
+// 1102 / 1149 / 1197 / 1255, 11k-cell layer mesh (0.38M) 966 / 982 / 1089 / 1247 and 1025 / 1039 / 1111 / 1268, 59k-row
+// triangulation (0.37M) 1533 / 1560 / 1600 / 1674 and, stationary in FP64, 5646 / 5667 / 5683 / 5845, 64 x 64 grid
+// 467 / 493 / 480 / 585. Above it (by kPairMaxSlots alone, on another box): the 59k-row one 5730 against 5248 and
+// 64k tetrahedral cells (1.1M) 2249 against 2081. The limit counts products, not bytes: of those cells the level of
+// 1363 rows of up to 60 entries (0.36M) gains nothing in FP32, 1254 / 1261 / 1250 / 1246, and loses in FP64,
+// 1370 / 1396 / 1321 / 1325.
 // Both pairs are for diagonal smoothing steps: around the sparse smoother's fused step the restriction's alone
 // lost (64k tetrahedral cells 2936, without 2759).
 constexpr int64_t kPairMaxSlots = 1 << 19;

@@ -4,17 +4,18 @@
 //   * stationary  u <- V(u, f)                              (FP64 cycle)
 //   * iterative refinement  x <- x + V(0, b - A x)          (FP64 residual, FP32/FP64 cycle)
 //   * flexible CG with z = V(0, r) as preconditioner        (FP64 vectors, FP32/FP64 cycle)
-// The FP32 cycle receives r / ||r|| so that its input is O(1) whatever the residual
-// level; the correction is scaled back in FP64. Scalars live on the device; the host
-// reads one small block of them per iteration to decide on convergence, one iteration late
-// while convergence is not in sight: iteration k + 1 is already enqueued while the host waits
-// for iteration k's block, and the guarded steps leave x unchanged once the device has seen
-// convergence, divergence or a breakdown, so an extra iteration is a no-op for the result.
+// The FP32 cycle receives the residual scaled by a power of two so that its input is O(1) whatever the
+// residual's level; the correction is scaled back in FP64. Scalars live on the device; the host
+// reads one small block of them per iteration to decide on convergence, up to kPipeline - 1
+// iterations late while convergence is not in sight: those are already enqueued while the host
+// waits for a block. Under refinement and flexible CG the guarded steps leave x unchanged once the
+// device has seen convergence, divergence or a breakdown, so an extra iteration is a no-op for the
+// result; a stationary solve returns the saved iterate of the iteration it stops at.
 //
-// One outer iteration of IR or flexible CG is a fixed sequence of ~50 kernels (most of
-// them on small coarse levels, where launch latency dominates). With opts.graphs the
-// sequence is captured once per configuration into a HIP graph on the context's private
-// stream and replayed on the caller's stream, one graph launch per iteration.
+// One outer iteration is a fixed sequence of a few tens of kernels (most of them on small coarse levels, where
+// launch latency dominates). With opts.graphs the sequence is captured once per configuration into
+// a HIP graph on the context's private stream and replayed on the caller's stream, one graph launch
+// per iteration.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -276,12 +276,15 @@ extern "C" int amgg_solve(amgg_ctx* c, const amgg_solve_opts* o, const double* b
         // Enqueue ahead only while the `flight` iterations in flight are not expected to converge (the
         // residual after the last of them, predicted from the last ratio, stays above twice the
         // tolerance): an iteration enqueued after the converging one would run its whole cycle for
-        // nothing. The stationary iteration, of which a direct solve needs one and a loose
-        // tolerance few, waits for the second ratio (the first says little: the initial residual is
-        // not the cycle's).
+        // nothing. The stationary iteration, of which a direct solve needs one and a loose tolerance few,
+        // is taken to gain two digits until two ratios are known (the first says little: the initial
+        // residual is not the cycle's).
         auto ahead = [&](size_t flight) {
-            if (hist.size() < 3) return o->outer != AMGG_OUTER_STATIONARY;
-            const double last = hist[hist.size() - 1], ratio = std::min(1.0, last / hist[hist.size() - 2]);
+            const bool stationary = o->outer == AMGG_OUTER_STATIONARY;
+            if (hist.size() < 3 && !stationary) return true;
+            const double last = hist.back();
+            double ratio = hist.size() > 1 ? std::min(1.0, last / hist[hist.size() - 2]) : 1.0;
+            if (hist.size() < 3) ratio = c->nlevels > 1 ? std::min(ratio, 1e-2) : 0.0;
             double pred = last;
             for (size_t m = 0; m < flight; ++m) pred *= ratio;
             return pred > 2.0 * o->tol;

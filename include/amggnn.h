@@ -362,7 +362,7 @@ typedef struct {
     double stag_ratio;    /* stagnated if ||r_k|| > stag_ratio ||r_{k-w}||; <= 0 means 0.99 */
     int stag_window;      /* w; <= 0 means 10 */
     int graphs;           /* nonzero: replay each iteration as one captured HIP graph (captured on
-                             first use per configuration; the context keeps the last 32 used). With
+                             first use per configuration; the context keeps the last 256 used). With
                              IR and flexible CG the addresses of x (and b) belong to the
                              configuration */
 } amgg_solve_opts;

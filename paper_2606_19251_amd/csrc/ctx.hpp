@@ -22,9 +22,10 @@ constexpr int kMaxCoef = 2 * AMGG_MAX_DEGREE + 1;
 constexpr int kPipeline = 3;
 // Captured iterations a context keeps. Those of refinement and flexible CG hold the addresses of the caller's x
 // (and b), so a program with new tensors per solve makes new ones: beyond this many the one unused for the
-// longest goes. A solve launches at most three in turn (flexible CG: the first iteration and the two
-// places of the residual), times the smoother forms and cycles a program alternates between.
-constexpr size_t kKeptGraphs = 32;
+// longest goes. Flexible CG takes three per x (the first iteration and the two places of the residual),
+// so that a program that goes round some 80 tensors, or alternates between as many smoother forms and
+// cycles, still finds them all; a graph of 30 kernels is some tens of KB of host memory.
+constexpr size_t kKeptGraphs = 256;
 
 struct Level {
     bool loaded = false, p_loaded = false;

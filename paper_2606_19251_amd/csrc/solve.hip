@@ -165,10 +165,10 @@ hipError_t run_body(amgg_ctx* c, bool use_graph, const std::string& key, hipStre
         body(st);
         return R.e;
     }
-    for (auto& g : c->graphs)
-        if (g.key == key) {
-            g.used = ++c->graph_uses;
-            return hipGraphLaunch(g.exec, st);
+    for (auto g = c->graphs.rbegin(); g != c->graphs.rend(); ++g)  // the newest first
+        if (g->key == key) {
+            g->used = ++c->graph_uses;
+            return hipGraphLaunch(g->exec, st);
         }
     hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;

@@ -42,16 +42,16 @@ def test_kept_graphs_are_bounded(outer, precision):
     ds = DeviceSolver(HostHierarchy.build(A.rowptr, A.col, A.val))
     ds.set_jacobi()
     how = dict(outer={"ir": capi.AMGG_OUTER_IR, "fcg": capi.AMGG_OUTER_FCG}[outer], precision=precision, tol=1e-8)
-    bs = [torch.from_numpy(W.rhs_uniform(A.nrows, s)).cuda() for s in range(40)]
+    bs = [torch.from_numpy(W.rhs_uniform(A.nrows, s)).cuda() for s in range(90 if outer == "fcg" else 270)]
     xs = [torch.empty_like(b) for b in bs]
     kept = []
     for b, x in zip(bs, xs):
         assert ds.solve(b, x, **how)[1] == 0
         kept.append(capi.amgg_kept_graphs(ds.ctx))
-    assert max(kept) == kept[-1] == 32
-    for k in (0, 1, 39, 0):
+    assert max(kept) == kept[-1] == 256
+    for k in (0, 1, len(bs) - 1, 0):
         y = xs[k].clone()
         assert ds.solve(bs[k], xs[k], **how)[1] == 0 and torch.equal(xs[k], y)
-        assert ds.solve(bs[k], graphs=False, **how)[1] == 0 and capi.amgg_kept_graphs(ds.ctx) == 32
+        assert ds.solve(bs[k], graphs=False, **how)[1] == 0 and capi.amgg_kept_graphs(ds.ctx) == 256
         assert torch.equal(ds.solve(bs[k], graphs=False, **how)[0], y)
     ds.close()

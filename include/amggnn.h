@@ -322,8 +322,9 @@ int amgg_level_apply(amgg_ctx* ctx, int lvl, int op, int precision, const void* 
 /* Kernel fusion switch (diagnostics and tests). With enable = 1 (the default) the cycle
  * fuses, on every level that admits it, the first pre-smoothing step from u = 0 with the
  * residual after it, and each later smoothing step u <- u + Q^{-1}(f - A u) into one
- * kernel (the residual of a row block and of its halo rows is kept in LDS). Every row sum
- * keeps its order, so the results are bitwise the same as with enable = 0, where each
+ * kernel (the residual of a row block and of its halo rows is kept in LDS), and on small levels
+ * around diagonal steps the residual with the restriction and the prolongation with the step
+ * after it (amgg_pair_widths). Every row sum keeps its order, so the results are bitwise the same as with enable = 0, where each
  * operator is its own pass. Drops the captured solve graphs. */
 int amgg_set_fusion(amgg_ctx* ctx, int enable);
 
